@@ -28,9 +28,16 @@ FLAGS = [
 ]
 
 
-def _compile(src: str) -> str:
-    obj = os.path.join(OBJ, os.path.basename(src) + ".o")
-    cmd = [HIPCC, *FLAGS, "-c", src, "-o", obj]
+# sources whose kernels are instantiated per sweep depth: compiled once
+# without TWG_DEPTH (everything else) and once for each depth
+DEPTH_SOURCES = ("solve.hip", "sor_stream.hip", "batch.hip")
+DEPTHS = range(1, 9)
+
+
+def _compile(job) -> str:
+    src, depth = job
+    obj = os.path.join(OBJ, os.path.basename(src) + (f".d{depth}" if depth else "") + ".o")
+    cmd = [HIPCC, *FLAGS, *([f"-DTWG_DEPTH={depth}"] if depth else []), "-c", src, "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError(f"hipcc failed for {src}:\n{res.stderr}")
@@ -40,8 +47,11 @@ def _compile(src: str) -> str:
 def build(verbose: bool = False) -> str:
     os.makedirs(OBJ, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
-    with cf.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as ex:
-        objs = list(ex.map(_compile, srcs))
+    jobs = [(s, 0) for s in srcs]
+    # the deepest kernels take longest: first in the queue
+    jobs = [(s, d) for d in reversed(DEPTHS) for s in srcs if os.path.basename(s) in DEPTH_SOURCES] + jobs
+    with cf.ThreadPoolExecutor(max_workers=8) as ex:
+        objs = list(ex.map(_compile, jobs))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -549,6 +549,26 @@ int last_status_b() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEV
 
 }  // namespace
 
+// Each depth's kernels are instantiated in a translation unit of their own
+// (this file compiled with TWG_DEPTH set), so that they build in parallel.
+template <int S>
+int launch_batch_slot_depth(const BatchArgs &a, int blocks, bool pair, hipStream_t st)
+{
+    if (pair)
+        hipLaunchKernelGGL((k_batch_slot<S, true>), dim3(blocks), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_batch_slot<S, false>), dim3(blocks), dim3(256), 0, st, a);
+    return last_status_b();
+}
+
+#ifdef TWG_DEPTH
+template int launch_batch_slot_depth<TWG_DEPTH>(const BatchArgs &, int, bool, hipStream_t);
+#else
+#define TWG_BSLOT_DEPTH(SV) extern template int launch_batch_slot_depth<SV>(const BatchArgs &, int, bool, hipStream_t);
+TWG_BSLOT_DEPTH(1) TWG_BSLOT_DEPTH(2) TWG_BSLOT_DEPTH(3) TWG_BSLOT_DEPTH(4)
+TWG_BSLOT_DEPTH(5) TWG_BSLOT_DEPTH(6) TWG_BSLOT_DEPTH(7) TWG_BSLOT_DEPTH(8)
+#undef TWG_BSLOT_DEPTH
+
 size_t batch_hdr_bytes() { return (sizeof(BatchHdr) + 255) & ~size_t(255); }
 size_t batch_run_bytes() { return sizeof(GridRun); }
 size_t batch_ctl_bytes() { return sizeof(GridCtl); }
@@ -584,27 +604,22 @@ int launch_batch_slot(const BatchArgs &a, int max_tiles, bool pair, hipStream_t 
     // one wave per tile of the whole batch (the finishing slot's copy loops
     // over its items with the same waves)
     const int blocks = std::max(1, (max_tiles + 3) / 4);
-#define TWG_BSLOT_CASE(SV)                                                                          \
-    case SV:                                                                                        \
-        if (pair)                                                                                   \
-            hipLaunchKernelGGL((k_batch_slot<SV, true>), dim3(blocks), dim3(256), 0, st, a);        \
-        else                                                                                        \
-            hipLaunchKernelGGL((k_batch_slot<SV, false>), dim3(blocks), dim3(256), 0, st, a);       \
-        break;
+    int rc;
     switch (a.S) {
-        TWG_BSLOT_CASE(1)
-        TWG_BSLOT_CASE(2)
-        TWG_BSLOT_CASE(3)
-        TWG_BSLOT_CASE(4)
-        TWG_BSLOT_CASE(5)
-        TWG_BSLOT_CASE(6)
-        TWG_BSLOT_CASE(7)
-        TWG_BSLOT_CASE(8)
+    case 1: rc = launch_batch_slot_depth<1>(a, blocks, pair, st); break;
+    case 2: rc = launch_batch_slot_depth<2>(a, blocks, pair, st); break;
+    case 3: rc = launch_batch_slot_depth<3>(a, blocks, pair, st); break;
+    case 4: rc = launch_batch_slot_depth<4>(a, blocks, pair, st); break;
+    case 5: rc = launch_batch_slot_depth<5>(a, blocks, pair, st); break;
+    case 6: rc = launch_batch_slot_depth<6>(a, blocks, pair, st); break;
+    case 7: rc = launch_batch_slot_depth<7>(a, blocks, pair, st); break;
+    case 8: rc = launch_batch_slot_depth<8>(a, blocks, pair, st); break;
     default: return TWG_EUNSUPPORTED;
     }
-#undef TWG_BSLOT_CASE
+    if (rc) return rc;
     hipLaunchKernelGGL(k_batch_ctrl, dim3(1), dim3(256), 0, st, a);
     return last_status_b();
 }
+#endif
 
 }  // namespace twg

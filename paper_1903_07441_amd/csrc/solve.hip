@@ -717,6 +717,27 @@ int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVIC
 
 }  // namespace
 
+// Each depth's kernels are instantiated in a translation unit of their own
+// (this file compiled with TWG_DEPTH set), so that they build in parallel.
+template <int S>
+int launch_relax_slot_depth(const SlotArgs &a, hipStream_t st)
+{
+    const int blocks = (a.tiles + 3) / 4;
+    if (a.pair)
+        hipLaunchKernelGGL((k_relax_slot<S, true>), dim3(blocks), dim3(256), 0, st, a);
+    else
+        hipLaunchKernelGGL((k_relax_slot<S, false>), dim3(blocks), dim3(256), 0, st, a);
+    return last_status();
+}
+
+#ifdef TWG_DEPTH
+template int launch_relax_slot_depth<TWG_DEPTH>(const SlotArgs &, hipStream_t);
+#else
+#define TWG_SLOT_DEPTH(SV) extern template int launch_relax_slot_depth<SV>(const SlotArgs &, hipStream_t);
+TWG_SLOT_DEPTH(1) TWG_SLOT_DEPTH(2) TWG_SLOT_DEPTH(3) TWG_SLOT_DEPTH(4)
+TWG_SLOT_DEPTH(5) TWG_SLOT_DEPTH(6) TWG_SLOT_DEPTH(7) TWG_SLOT_DEPTH(8)
+#undef TWG_SLOT_DEPTH
+
 size_t relax_ctl_bytes() { return (sizeof(RelaxCtl) + 255) & ~size_t(255); }
 
 int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st)
@@ -727,27 +748,18 @@ int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st)
 
 int launch_relax_slot(const SlotArgs &a, int S, hipStream_t st)
 {
-    const int blocks = (a.tiles + 3) / 4;
-#define TWG_SLOT_CASE(SV)                                                                          \
-    case SV:                                                                                       \
-        if (a.pair)                                                                                \
-            hipLaunchKernelGGL((k_relax_slot<SV, true>), dim3(blocks), dim3(256), 0, st, a);       \
-        else                                                                                       \
-            hipLaunchKernelGGL((k_relax_slot<SV, false>), dim3(blocks), dim3(256), 0, st, a);      \
-        break;
     switch (S) {
-        TWG_SLOT_CASE(1)
-        TWG_SLOT_CASE(2)
-        TWG_SLOT_CASE(3)
-        TWG_SLOT_CASE(4)
-        TWG_SLOT_CASE(5)
-        TWG_SLOT_CASE(6)
-        TWG_SLOT_CASE(7)
-        TWG_SLOT_CASE(8)
+    case 1: return launch_relax_slot_depth<1>(a, st);
+    case 2: return launch_relax_slot_depth<2>(a, st);
+    case 3: return launch_relax_slot_depth<3>(a, st);
+    case 4: return launch_relax_slot_depth<4>(a, st);
+    case 5: return launch_relax_slot_depth<5>(a, st);
+    case 6: return launch_relax_slot_depth<6>(a, st);
+    case 7: return launch_relax_slot_depth<7>(a, st);
+    case 8: return launch_relax_slot_depth<8>(a, st);
     default: return TWG_EUNSUPPORTED;
     }
-#undef TWG_SLOT_CASE
-    return last_status();
 }
+#endif
 
 }  // namespace twg

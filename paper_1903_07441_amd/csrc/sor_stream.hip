@@ -62,18 +62,43 @@ bool pairable(const T *src, const T *dst, const void *wsrc, size_t wbytes, const
            al(wsrc, 2 * wbytes) && (!f || al(f, 2 * sizeof(T)));
 }
 
+}  // namespace
+
+// Each depth's kernels are instantiated in a translation unit of their own
+// (this file compiled with TWG_DEPTH set), so that they build in parallel.
+template <typename T, bool RHS, bool PAIR, int S>
+int launch_stream_depth(const T *src, T *dst, const void *wsrc, T omega, const T *f, int nx, int ny, int pitch,
+                        const Geometry &g, hipStream_t st)
+{
+    hipLaunchKernelGGL((k_sor_stream<T, S, RHS, PAIR>), dim3((g.tiles + 3) / 4), dim3(256), 0, st, src, dst, wsrc,
+                       omega, f, nx, ny, pitch, g.strips, g.RH, g.tiles);
+    return last_status();
+}
+
+#define TWG_STREAM_INST(EX, T, RHS, PAIR, SV)                                                              \
+    EX template int launch_stream_depth<T, RHS, PAIR, SV>(const T *, T *, const void *, T, const T *, int, \
+                                                          int, int, const Geometry &, hipStream_t);
+#define TWG_STREAM_DEPTH(EX, SV)                                                                   \
+    TWG_STREAM_INST(EX, float, false, false, SV) TWG_STREAM_INST(EX, float, false, true, SV)       \
+    TWG_STREAM_INST(EX, float, true, false, SV) TWG_STREAM_INST(EX, float, true, true, SV)         \
+    TWG_STREAM_INST(EX, double, false, false, SV) TWG_STREAM_INST(EX, double, false, true, SV)
+
+#ifdef TWG_DEPTH
+TWG_STREAM_DEPTH(, TWG_DEPTH)
+#else
+TWG_STREAM_DEPTH(extern, 1) TWG_STREAM_DEPTH(extern, 2) TWG_STREAM_DEPTH(extern, 3) TWG_STREAM_DEPTH(extern, 4)
+TWG_STREAM_DEPTH(extern, 5) TWG_STREAM_DEPTH(extern, 6) TWG_STREAM_DEPTH(extern, 7) TWG_STREAM_DEPTH(extern, 8)
+
+namespace {
+
 template <typename T, bool RHS, bool PAIR>
 int launch_stream(const T *src, T *dst, const void *wsrc, T omega, const T *f, int nx, int ny, int pitch,
                   const Geometry &geo, hipStream_t st)
 {
     const int cap = stream_rows_cap(pitch, sizeof(T), geo.S);
     const Geometry g = geo.RH > cap ? stream_geometry(nx, ny, geo.S, cap) : geo;
-    const int blocks = (g.tiles + 3) / 4;
-#define TWG_STREAM_CASE(SV)                                                                           \
-    case SV:                                                                                          \
-        hipLaunchKernelGGL((k_sor_stream<T, SV, RHS, PAIR>), dim3(blocks), dim3(256), 0, st, src, dst, \
-                           wsrc, omega, f, nx, ny, pitch, g.strips, g.RH, g.tiles);                   \
-        break;
+#define TWG_STREAM_CASE(SV) \
+    case SV: return launch_stream_depth<T, RHS, PAIR, SV>(src, dst, wsrc, omega, f, nx, ny, pitch, g, st);
     switch (g.S) {
         TWG_STREAM_CASE(1)
         TWG_STREAM_CASE(2)
@@ -86,7 +111,6 @@ int launch_stream(const T *src, T *dst, const void *wsrc, T omega, const T *f, i
     default: return TWG_EUNSUPPORTED;
     }
 #undef TWG_STREAM_CASE
-    return last_status();
 }
 
 }  // namespace
@@ -129,5 +153,7 @@ int launch_stream_f64(const double *src, double *dst, const uint8_t *fmask, doub
         return launch_stream<double, false, true>(src, dst, fmask, omega, nullptr, nx, ny, pitch, geo, st);
     return launch_stream<double, false, false>(src, dst, fmask, omega, nullptr, nx, ny, pitch, geo, st);
 }
+
+#endif
 
 }  // namespace twg
