@@ -170,21 +170,43 @@ double omega_open(int nx, int ny)
     return 2.0 / (1.0 + std::sqrt(std::max(0.0, 1.0 - rho * rho)));
 }
 
-// Sweeps per tile load and rows per tile for a grid (fixed table; the
-// autotuner may override through hpf_params.sweeps_per_pass).
-void default_tiling(int nx, int ny, int *S, int *RH)
+// Smallest even tile height whose tile count (one wave per tile) fits k
+// rounds of the device's SIMDs, at least 4: a tile of RH rows costs a wave
+// RH + 2S - 1 full row steps (its first turn always covers 4 rows), and a
+// second wave on a SIMD gains only 7 %, so one full round of the lowest tiles
+// is the shortest pass.
+int round_height(const twg_ctx *ctx, int nx, int ny, int S, int k)
+{
+    const int simds = 4 * std::max(1, ctx->num_cu);
+    const int strips = (nx + (128 - 4 * S) - 1) / (128 - 4 * S);
+    const int segs = std::max(1, (int)((long long)k * simds / strips));
+    const int RH = (ny + segs - 1) / segs;
+    return std::max(4, RH + (RH & 1));
+}
+
+// Rows per tile for a grid the autotuner has not seen: the lowest tiles of
+// one round of the SIMDs, or of as few rounds as keep them at 160 rows.
+int default_height(const twg_ctx *ctx, int nx, int ny, int S)
+{
+    int RH, k = 1;
+    while ((RH = round_height(ctx, nx, ny, S, k)) > 160 && k < 64) ++k;
+    return RH;
+}
+
+// Sweeps per tile load and rows per tile for a grid the autotuner has not
+// seen (S from a fixed table: a solve's checks fall on multiples of it).
+void default_tiling(const twg_ctx *ctx, int nx, int ny, int *S, int *RH)
 {
     const long long cells = (long long)nx * ny;
-    if (cells >= (1LL << 22)) { *S = 4; *RH = 32; }
-    else if (cells >= (1LL << 18)) { *S = 4; *RH = 16; }
-    else { *S = 2; *RH = 8; }
+    *S = cells >= (1LL << 18) ? 4 : 2;
+    *RH = default_height(ctx, nx, ny, *S);
 }
 
 // Tiling and SOR factor for a grid: the autotuned entry of this size if the
 // context has one, else the fixed table and the open-rectangle optimum.
 void tiling_for(twg_ctx *ctx, int nx, int ny, int *S, int *RH, float *omega)
 {
-    default_tiling(nx, ny, S, RH);
+    default_tiling(ctx, nx, ny, S, RH);
     *omega = (float)omega_open(nx, ny);
     auto it = ctx->tuned.find({nx, ny});
     if (it != ctx->tuned.end()) {
@@ -195,35 +217,23 @@ void tiling_for(twg_ctx *ctx, int nx, int ny, int *S, int *RH, float *omega)
 }
 
 // Tile heights to try for S sweeps per load: a fixed set plus, for k = 1..kmax,
-// the smallest even height whose tile count (one wave per tile) fits k rounds
-// of the device's SIMDs, and the tallest height with the same row steps per
-// tile.  A tile streams RH + 4S rows in whole windows of 2S + 2 row steps, so
-// that height fills the last window: the same time per wave, fewer tiles.
+// the lowest that fits k rounds of the device's SIMDs.
 std::vector<int> tile_heights(const twg_ctx *ctx, int nx, int ny, int S, int kmax)
 {
     std::vector<int> RHs = {8, 16, 32, 64, 128};
-    const int simds = 4 * std::max(1, ctx->num_cu);
-    const int strips = (nx + (128 - 4 * S) - 1) / (128 - 4 * S);
-    const int NW = 2 * S + 2;
-    auto add = [&](int RH) {
-        if (RH >= 2 && std::find(RHs.begin(), RHs.end(), RH) == RHs.end()) RHs.push_back(RH);
-    };
     for (int k = 1; k <= kmax; ++k) {
-        const int segs = (k * simds) / strips;
-        if (segs < 1) continue;
-        int RH = (ny + segs - 1) / segs;
-        RH += RH & 1;
-        add(RH);
-        add((RH + 4 * S + NW - 1) / NW * NW - 4 * S);  // even: NW and 4S are
+        const int RH = round_height(ctx, nx, ny, S, k);
+        if (std::find(RHs.begin(), RHs.end(), RH) == RHs.end()) RHs.push_back(RH);
     }
     return RHs;
 }
 
-// FP64 tiling for a grid: the autotuned one, else 4 sweeps per load and 32 rows
+// FP64 tiling for a grid: the autotuned one, else 4 sweeps per load and the
+// lowest tiles of one round of the SIMDs
 void tiling64_for(twg_ctx *ctx, int nx, int ny, int *S, int *RH)
 {
     *S = 4;
-    *RH = 32;
+    *RH = default_height(ctx, nx, ny, *S);
     auto it = ctx->tuned.find({nx, ny});
     if (it != ctx->tuned.end() && it->second.S64 > 0) {
         *S = it->second.S64;
@@ -407,7 +417,10 @@ RelaxPlan plan_for(twg_ctx *ctx, const twg_grid &g, const hpf_params &p)
             pl.lead = it->second.lead_dc;
         }
     }
-    if (p.sweeps_per_pass) pl.S = p.sweeps_per_pass;
+    if (p.sweeps_per_pass && p.sweeps_per_pass != pl.S) {
+        pl.S = p.sweeps_per_pass;
+        if (!ctx->tuned.count({g.nx, g.ny})) pl.RH = default_height(ctx, g.nx, g.ny, pl.S);
+    }
     if (p.rows_per_tile) pl.RH = p.rows_per_tile;
     return pl;
 }
@@ -626,8 +639,20 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         RH = ctx->batch_RH;
     }
     if (p.sweeps_per_pass) S = p.sweeps_per_pass;
-    if (p.rows_per_tile) RH = p.rows_per_tile;
     const int VW = 128 - 4 * S;
+    if (ctx->batch_S <= 0 && !ctx->tuned.count({grids[big].nx, grids[big].ny})) {
+        // an untuned batch: the lowest tiles that fit the kernel's three
+        // waves per SIMD, at most 128 rows (lower tiles spend more row steps
+        // on their halo, taller ones leave SIMDs idle)
+        const long long waves = 3LL * 4 * std::max(1, ctx->num_cu);
+        for (RH = 8; RH < 128; RH *= 2) {
+            long long tiles = 0;
+            for (int k = 0; k < n; ++k)
+                tiles += (long long)((grids[k].nx + VW - 1) / VW) * ((grids[k].ny + RH - 1) / RH);
+            if (tiles <= waves) break;
+        }
+    }
+    if (p.rows_per_tile) RH = p.rows_per_tile;
     bool pair = (reinterpret_cast<uintptr_t>(psi) & 7) == 0;  // the partner and mask are context-owned (aligned)
     int max_pitch = 1;
     for (int k = 0; k < n; ++k) {

@@ -16,8 +16,8 @@
 // stage sees neighbour rows that are exactly one half-sweep older.  Vertical
 // neighbours come from the rolling register window, horizontal ones from the
 // adjacent lane through wave-wide DPP shifts (no LDS traffic).  The row loop
-// has no per-row branches (its trip count is padded to whole windows, halo
-// lanes store out of range) and is fenced so that each prefetch stays in its
+// has no per-row branches but in its last steps (halo lanes store out of
+// range; the first turn runs only the stages that a stored row needs) and is fenced so that each prefetch stays in its
 // row step; rows live in a register ring of two windows, so no value moves
 // between registers and no row step waits for a load younger than a window.  Each
 // half-sweep invalidates one column at each edge of the strip, so S lanes on

@@ -61,8 +61,13 @@ __device__ __forceinline__ int xcd_remap(int b, int nb)
 constexpr uint32_t kNoStore = 0x80000000u;
 constexpr int64_t kMaxTileBytes = 1LL << 30;
 
+// The base (wave-uniform) passes through an empty asm, so that the compiler
+// knows nothing of what it points to: a load it took for invariant (the mask
+// is never written) would sink to its use, and the row step would wait a
+// whole memory latency for it.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes)
 {
+    asm volatile("" : "+s"(base));
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
 __device__ __forceinline__ float bload(float *, __amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
@@ -165,6 +170,13 @@ constexpr int kSrcNone = 0, kSrcF = 1, kSrcC = 2;
 // row step waits for a load younger than NW row steps.  Cells outside the
 // grid read as zeros with factor 0, straight from the out-of-range loads.
 //
+// Measured at 2048 x 2048 (S = 6, 46 rows: 900 waves on 1024 SIMDs, bound by
+// VALU issue): the trimmed first turn took a replanning step from 6.16 to
+// 5.65 ms; 256 FP64 sweeps (S = 4) from 1.13 to 1.10 ms, and to 0.92 ms with
+// lower tiles that end at their own last row.  1001 x 743 to residual 1e-6
+// (unpaired): 5.5 to 2.96 ms, where the mask bytes used to be loaded at their
+// use.
+//
 // CHECK: the pass also measures the residual of its INPUT field, in FP64:
 // r = ((E + W) + (S + N)) / 4 (+ f) - c over the FREE cells of its output
 // rows and columns, the expression of the standalone residual kernels.  Row
@@ -183,6 +195,12 @@ template <class F, int... U>
 __device__ __forceinline__ void static_for(std::integer_sequence<int, U...>, F &&f)
 {
     (f(std::integral_constant<int, U>{}), ...);
+}
+// the same, up to the first U whose f returns false
+template <class F, int... U>
+__device__ __forceinline__ void static_while(std::integer_sequence<int, U...>, F &&f)
+{
+    (void)(f(std::integral_constant<int, U>{}) && ...);
 }
 __device__ __forceinline__ float nan_maxf(float a, float b) { return (b > a || b != b) ? b : a; }
 
@@ -257,8 +275,10 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         } else {
             P0[slot] = bload((T *)nullptr, rs, b0, vo);
             P1[slot] = bload((T *)nullptr, rs, b1, vo);
-            M0[slot] = __builtin_amdgcn_raw_buffer_load_b8(rw, (int)m0, (int)mo, 0);
-            M1[slot] = __builtin_amdgcn_raw_buffer_load_b8(rw, (int)m1, (int)mo, 0);
+            // sign-extended by the load itself: extended at its use instead,
+            // the byte is loaded there, and every row step waits for it
+            M0[slot] = (uint32_t)(int32_t)(int8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (int)m0, (int)mo, 0);
+            M1[slot] = (uint32_t)(int32_t)(int8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (int)m1, (int)mo, 0);
             if (RHS) {
                 F0[slot] = bload((T *)nullptr, rf, b0, vo);
                 F1[slot] = bload((T *)nullptr, rf, b1, vo);
@@ -328,15 +348,17 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
     }
 
     // One row step: row t (ring slot u, pipeline index u mod NW) enters the
-    // pipeline, row t + NW is fetched, the 2S stages advance and row t - 2S
-    // is stored.  u is a constant wherever the step is inlined.
-    auto step = [&](const int u, const int t, const bool prefetch) __attribute__((always_inline)) {
+    // pipeline, row t + NW is fetched, the first `stages` stages advance and
+    // row t - 2S is stored (`out`).  u, stages and the flags are constants
+    // wherever the step is inlined.
+    auto step = [&](const int u, const int t, const bool prefetch, const int stages,
+                    const bool out) __attribute__((always_inline)) {
         const int uw = u % NW;
         {
             // the mask bytes sign-extended (all ones on a FREE cell); the
             // factor is omega or +0, bit for bit omega x (0 or 1)
-            const int32_t e0 = (int32_t)(M0[u] << 24) >> 24;
-            const int32_t e1 = PAIR ? (int32_t)(M0[u] << 16) >> 24 : (int32_t)(M1[u] << 24) >> 24;
+            const int32_t e0 = PAIR ? (int32_t)(M0[u] << 24) >> 24 : (int32_t)M0[u];
+            const int32_t e1 = PAIR ? (int32_t)(M0[u] << 16) >> 24 : (int32_t)M1[u];
             const bool ev = (u & 1) == 0;
             if constexpr (RHS != kSrcC) {
                 const T w0 = keep(omega, e0), w1 = keep(omega, e1);
@@ -408,14 +430,16 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         };
         // each stage's sum is formed one stage ahead of its update, which
         // gives the scheduler two independent chains to interleave
-        T e_next = ewn(0);
+        T e_next = T(0);
+        if (stages > 0) e_next = ewn(0);
 #pragma unroll
         for (int k = 0; k < 2 * S; ++k) {
+            if (k >= stages) continue;
             const int s = (u - 1 - k + 2 * NR) % NR;
             const int sp = (s + 1) % NR;
             const int sw = (uw - 1 - k + 2 * NW) % NW;
             const T e = e_next;
-            if (k + 1 < 2 * S) e_next = ewn(k + 1);
+            if (k + 1 < stages) e_next = ewn(k + 1);
             if constexpr (RHS != kSrcNone) {
                 if ((k & 1) == 0)
                     red(s) = upd_src(red(s), e, blk(sp), kR[sw]);
@@ -430,7 +454,7 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         }
         // the row finished by this step (row t - 2S) is stored; rows
         // outside [ybeg, yend) fall outside the write resource
-        {
+        if (out) {
             const int s = (u - 2 * S + 2 * NR) % NR;
             const uint32_t ro = (uint32_t)(orow0 + t * (int)rowb);
             if constexpr (PAIR) {
@@ -445,20 +469,54 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // The trip count is padded to whole windows so that the unrolled body
-    // has no per-row branches: fetches are unconditional (rows past the grid
-    // read zeros) and rows past the tile are computed but never stored.  The
-    // loop body is one turn of the ring (two windows); an odd window count
-    // ends with one more window, which fetches nothing.
-    const int windows = (T_rows + NW - 1) / NW;
-    const int T_turns = (windows / 2) * NR;
-    int tb = 0;
-    for (; tb < T_turns; tb += NR)
-        static_for(std::make_integer_sequence<int, NR>{},
-                   [&](auto U) __attribute__((always_inline)) { step(decltype(U)::value, tb + U, true); });
-    if (windows & 1)
-        static_for(std::make_integer_sequence<int, NW>{},
-                   [&](auto U) __attribute__((always_inline)) { step(decltype(U)::value, tb + U, false); });
+    // The first turn fills the pipeline: a stored row depends on the rows
+    // within 2S - 1 - k of it after stage k, so stage k first matters at row
+    // k + 1, which it meets at step 2k + 2, and the first stored row leaves
+    // at step 4S.  Step u of that turn therefore runs u / 2 stages and stores
+    // from u = 4S on: 2S(2S + 1) of a tile's 2S(RH + 4S) stage steps drop out
+    // (19 % at S = 6 and 46 rows).  A tile of two rows or fewer ends inside
+    // that turn (rows past its last one are computed but never stored).
+    static_for(std::make_integer_sequence<int, NR>{}, [&](auto U) __attribute__((always_inline)) {
+        constexpr int u = decltype(U)::value;
+        step(u, u, true, u / 2 < 2 * S ? u / 2 : 2 * S, u >= 4 * S);
+    });
+    // Whole turns have no per-row branches: fetches are unconditional (rows
+    // past the grid read zeros).
+    const int T_end = SLOT_OFS ? T_rows : (T_rows + NW - 1) / NW * NW;
+    int tb = NR;
+    for (; tb + NR <= T_end; tb += NR)
+        static_for(std::make_integer_sequence<int, NR>{}, [&](auto U) __attribute__((always_inline)) {
+            step(decltype(U)::value, tb + U, true, 2 * S, true);
+        });
+    // The rest, fewer than NR steps: a whole window without branches if there
+    // is one (fetching if more follows it), then single steps that leave at
+    // the tile's last row, so any height costs only its own row steps.  The
+    // kernels held to fewer registers (SLOT_OFS = false) pad the rest to
+    // whole windows instead: their single steps spill (a batch of 64 grids
+    // at S = 8 took 8.25 against 7.87 ms).
+    auto window = [&](auto more) __attribute__((always_inline)) {
+        static_for(std::make_integer_sequence<int, NW>{}, [&](auto U) __attribute__((always_inline)) {
+            step(decltype(U)::value, tb + U, decltype(more)::value, 2 * S, true);
+        });
+    };
+    auto last_steps = [&](auto from) __attribute__((always_inline)) {
+        static_while(std::make_integer_sequence<int, NW - 1>{}, [&](auto U) __attribute__((always_inline)) {
+            constexpr int u = decltype(from)::value + decltype(U)::value;
+            if (tb + u >= T_rows) return false;
+            step(u, tb + u, false, 2 * S, true);
+            return true;
+        });
+    };
+    if (T_end - tb == NW) {
+        window(std::false_type{});
+    } else if constexpr (SLOT_OFS) {
+        if (T_end - tb > NW) {
+            window(std::true_type{});
+            last_steps(std::integral_constant<int, NW>{});
+        } else {
+            last_steps(std::integral_constant<int, 0>{});
+        }
+    }
     if constexpr (CHECK) {
         *rmax = nan_max(*rmax, cmax);
         *rrel = nan_maxf(*rrel, crel);
