@@ -20,8 +20,8 @@
  *     released by twg_ctx_destroy).
  *   - Grids are row-major, x fastest: a[y * pitch + x], nx <= pitch <= 65536,
  *     in elements of the array's type, and pitch * ny < 2^31.
- *     1 <= nx, ny <= 32767.  Even nx and pitch (with bases aligned to two
- *     elements) take the faster paired-column relaxation.
+ *     1 <= nx, ny <= 32767.  Rows need no alignment beyond the element's; an even
+ *     nx relaxes a few percent faster.
  *   - The potential is stored as psi = 1 - phi, phi being the paper's
  *     potential: the goal holds psi = 1, obstacles and walls psi = 0, free
  *     space starts at psi = 0.5 (phi = 0.5).  The equation is linear, so psi
@@ -310,7 +310,7 @@ int32_t hpf_relax_async(twg_ctx *ctx, twg_grid g, const uint8_t *cls, float *psi
  * every scratch buffer (control block, FP32 ping-pong partner, defect,
  * correction and the defect's products with the two correction factors,
  * free mask) inside one static device array of the library, 21 bytes per
- * cell for at most 4194304 cells plus 4 KiB (84 MiB and 4 KiB),
+ * cell for at most 4194304 cells plus 4.25 KiB (84 MiB and 4352 B),
  * which each GPU the library runs on holds until the process ends.  The call
  * itself allocates nothing on the device (no hipMalloc, no hipFree).
  * Limit: pitch * ny <= 4194304 (e.g. 2048 x 2048); larger grids return
@@ -415,7 +415,7 @@ int32_t hpf_sweeps(twg_ctx *ctx, twg_grid g, const uint8_t *cls, float *psi, con
  * -psi), psi) (N the row above, S the row below, each operation rounded
  * once), the expression the oracle's FP64 sweep evaluates, bit for bit.  tiled = 0: one launch per colour;
  * tiled = 1: sweeps_per_pass (1 to 8; 0 = the autotuned FP64
- * tiling of this grid size, else 4) sweeps per tile load, bit-identical.  Asynchronous.  Errors: TWG_EINVAL. */
+ * tiling of this grid size, else the library's choice) sweeps per tile load, bit-identical.  Asynchronous.  Errors: TWG_EINVAL. */
 int32_t hpf_sweeps64(twg_ctx *ctx, twg_grid g, const uint8_t *cls, double *psi64, double omega,
                      int32_t sweeps, int32_t tiled, int32_t sweeps_per_pass, void *stream);
 

@@ -26,7 +26,7 @@ constexpr size_t kNoAllocCtlBytes = 4096;
 constexpr size_t kNoAllocAlt = kNoAllocCtlBytes;
 constexpr size_t kNoAllocPol = kNoAllocAlt + 4 * kNoAllocMaxCells;
 constexpr size_t kNoAllocMask = kNoAllocPol + 16 * kNoAllocMaxCells;
-constexpr size_t kNoAllocBytes = kNoAllocMask + kNoAllocMaxCells;
+constexpr size_t kNoAllocBytes = kNoAllocMask + kNoAllocMaxCells + 256;  // (the passes read one byte past the mask)
 constexpr int kNoAllocDevices = 64;
 }  // namespace
 
@@ -228,11 +228,14 @@ std::vector<int> tile_heights(const twg_ctx *ctx, int nx, int ny, int S, int kma
     return RHs;
 }
 
-// FP64 tiling for a grid: the autotuned one, else 4 sweeps per load and the
-// lowest tiles of one round of the SIMDs
+// FP64 tiling for a grid: the autotuned one, else 6 sweeps per load (8 on
+// small grids, whose passes are mostly launch and first-load latency) and the
+// lowest tiles of one round of the SIMDs.  Per sweep at S = 4, 6 and 8: 3.45,
+// 2.64 and 2.94 us at 2048 x 2048, 1.46, 1.33 and 1.62 us at 1024 x 1024,
+// 1.26, 1.08 and 0.99 us at 512 x 512.
 void tiling64_for(twg_ctx *ctx, int nx, int ny, int *S, int *RH)
 {
-    *S = 4;
+    *S = (long long)nx * ny < (1LL << 19) ? 8 : 6;
     *RH = default_height(ctx, nx, ny, *S);
     auto it = ctx->tuned.find({nx, ny});
     if (it != ctx->tuned.end() && it->second.S64 > 0) {
@@ -273,7 +276,7 @@ struct Runner {
     int fmask(const uint8_t **m)
     {
         if (!have_fmask) {
-            int rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, (size_t)g.pitch * g.ny);
+            int rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, (size_t)g.pitch * g.ny + 1);
             if (rc) return rc;
             rc = launch_fmask(cls, static_cast<uint8_t *>(ctx->fmask), g.nx, g.ny, g.pitch, st);
             if (rc) return set_err(ctx, rc, "free mask launch failed");
@@ -283,7 +286,13 @@ struct Runner {
         return TWG_OK;
     }
 
-    // `sweeps` FP32 sweeps on a <-> b, S per pass (remainder one per pass);
+    // tiling of a pass of the last `rest` sweeps
+    Geometry rest_geometry(int rest, int RH) const
+    {
+        return stream_geometry(g.nx, g.ny, rest, std::min(RH, default_height(ctx, g.nx, g.ny, rest)));
+    }
+
+    // `sweeps` FP32 sweeps on a <-> b, S per pass (the remainder in one pass);
     // on return *a holds the newest field.  Runs of kGraphPasses full passes
     // are replayed from a captured graph.
     int sweep32(float **a, float **b, const float *f, float omega, int S, int RH, int64_t sweeps)
@@ -291,7 +300,6 @@ struct Runner {
         const uint8_t *m = nullptr;
         if (int rc = fmask(&m)) return rc;
         const Geometry geo = stream_geometry(g.nx, g.ny, S, RH);
-        const Geometry geo1 = stream_geometry(g.nx, g.ny, 1, RH);
         int64_t done = 0;
         const int64_t reps = ctx->use_graphs ? sweeps / ((int64_t)S * kGraphPasses) : 0;
         if (reps > 0) {
@@ -312,11 +320,28 @@ struct Runner {
             done = reps * S * kGraphPasses;
         }
         while (done < sweeps) {
-            const bool full = sweeps - done >= S;
-            int rc = launch_stream_f32(*a, *b, m, omega, f, g.nx, g.ny, g.pitch, full ? geo : geo1, st);
+            const int n = (int)std::min<int64_t>(S, sweeps - done);
+            int rc = launch_stream_f32(*a, *b, m, omega, f, g.nx, g.ny, g.pitch, n == S ? geo : rest_geometry(n, RH),
+                                       st);
             if (rc) return set_err(ctx, rc, "relaxation kernel launch failed");
             std::swap(*a, *b);
-            done += full ? S : 1;
+            done += n;
+        }
+        return TWG_OK;
+    }
+
+    // the same in FP64, without graphs
+    int sweep64(double **a, double **b, double omega, int S, int RH, int64_t sweeps)
+    {
+        const uint8_t *m = nullptr;
+        if (int rc = fmask(&m)) return rc;
+        const Geometry geo = stream_geometry(g.nx, g.ny, S, RH);
+        for (int64_t done = 0; done < sweeps;) {
+            const int n = (int)std::min<int64_t>(S, sweeps - done);
+            int rc = launch_stream_f64(*a, *b, m, omega, g.nx, g.ny, g.pitch, n == S ? geo : rest_geometry(n, RH), st);
+            if (rc) return set_err(ctx, rc, "relaxation kernel launch failed");
+            std::swap(*a, *b);
+            done += n;
         }
         return TWG_OK;
     }
@@ -332,18 +357,17 @@ struct Runner {
         return TWG_OK;
     }
 
-    // FP64 red-black SOR on `field` (ping-pong with ctx->alt64), four sweeps
-    // per tile load, until the FP64 residual is <= tol or the budget is spent.
+    // FP64 red-black SOR on `field` (ping-pong with ctx->alt64) until the FP64 residual is <= tol or the budget is spent.
     int solve64(double *field, double omega, double tol, int64_t max_sweeps, int64_t *sweeps_out,
                 double *res_out, bool *converged)
     {
         int rc = ensure(ctx, &ctx->alt64, &ctx->alt64_bytes, (size_t)g.pitch * g.ny * sizeof(double));
         if (rc) return rc;
-        int S, RH;
-        tiling64_for(ctx, g.nx, g.ny, &S, &RH);
-        const Geometry geo = stream_geometry(g.nx, g.ny, S, RH);
-        const uint8_t *m = nullptr;
-        if ((rc = fmask(&m))) return rc;
+        // S: what the checks' spacing is rounded to; D: sweeps per pass
+        int D, RH;
+        tiling64_for(ctx, g.nx, g.ny, &D, &RH);
+        const auto it = ctx->tuned.find({g.nx, g.ny});
+        const int S = it != ctx->tuned.end() && it->second.S64 > 0 ? it->second.S64 : 4;
         double *a = field, *b = reinterpret_cast<double *>(ctx->alt64);
         double r;
         rc = residual64(a, &r);
@@ -361,11 +385,7 @@ struct Runner {
             if (last_chunk > 0) chunk = std::min(chunk, std::max<int64_t>(2 * last_chunk, 64 * S));
             chunk = ((std::min(chunk, max_sweeps - done) + S - 1) / S) * S;
             last_chunk = chunk;
-            for (int64_t k = 0; k < chunk; k += S) {
-                rc = launch_stream_f64(a, b, m, omega, g.nx, g.ny, g.pitch, geo, st);
-                if (rc) return set_err(ctx, rc, "relaxation kernel launch failed");
-                std::swap(a, b);
-            }
+            if ((rc = sweep64(&a, &b, omega, D, RH, chunk))) return rc;
             done += chunk;
             const double r_prev = r;
             rc = residual64(a, &r);
@@ -393,6 +413,7 @@ struct Runner {
 struct RelaxPlan {
     int S = 4, RH = 32;
     float omega = 1.0f, omega_dc = 1.0f;
+    int fuse = 1;  // passes between two checks that a blocking solve's slot may do at once
     StartPhase lead;
 };
 
@@ -421,6 +442,13 @@ RelaxPlan plan_for(twg_ctx *ctx, const twg_grid &g, const hpf_params &p)
         pl.S = p.sweeps_per_pass;
         if (!ctx->tuned.count({g.nx, g.ny})) pl.RH = default_height(ctx, g.nx, g.ny, pl.S);
     }
+    // A pass costs about 3 us of launch and first-load latency however few
+    // rows it has, so an untuned solve does up to 8 sweeps per launch between
+    // its checks (which stay where S puts them): per sweep at S = 4 and 8,
+    // 0.88 and 0.76 us at 512 x 512, 1.92 and 1.68 us at 2048 x 2048; at S = 2
+    // and 8, 1.33 and 0.73 us at 256 x 256.  A caller's or the tuner's own
+    // tiling is kept.
+    if (!p.rows_per_tile && !ctx->tuned.count({g.nx, g.ny})) pl.fuse = slot_fuse_limit(pl.S);
     if (p.rows_per_tile) pl.RH = p.rows_per_tile;
     return pl;
 }
@@ -455,7 +483,7 @@ int relax_bufs_ctx(twg_ctx *ctx, const twg_grid &g, bool polish, RelaxBufs *b)
     const size_t n = (size_t)g.pitch * g.ny;
     int rc = ensure(ctx, &ctx->alt, &ctx->alt_bytes, n * sizeof(float));
     if (!rc && polish) rc = ensure(ctx, &ctx->pol, &ctx->pol_bytes, 4 * n * sizeof(float));
-    if (!rc) rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, n);
+    if (!rc) rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, n + 1);
     if (!rc) rc = ensure(ctx, &ctx->ctl, &ctx->ctl_bytes, relax_ctl_bytes() + 256);
     if (rc) return rc;
     b->alt = static_cast<float *>(ctx->alt);
@@ -476,6 +504,8 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     const int cap = stream_rows_cap(g.pitch, (int)sizeof(float), pl.S);
     const Geometry geo = stream_geometry(g.nx, g.ny, pl.S, std::min(pl.RH, cap));
     const double wb = std::pow((double)std::min(g.nx, g.ny) + 1.0, 2) / 2.0;
+    // an asynchronous call's slots are its caller's budget of passes: one each
+    const int fuse = slots > 0 ? 1 : pl.fuse;
 
     rc = launch_field_init(cls, psi, g.nx, g.ny, g.pitch, p.init, p.goal_x, p.goal_y, st);
     if (!rc) rc = launch_fmask(cls, bufs.fmask, g.nx, g.ny, g.pitch, st);
@@ -493,6 +523,7 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     cfg.polish = p.polish ? 1 : 0;
     cfg.check_passes = p.check_passes;
     cfg.max_rounds = kMaxRounds;
+    cfg.fuse = fuse;
     cfg.kept = cfg.polish && p.init == HPF_INIT_KEEP ? 1 : 0;
     rc = launch_relax_begin(ctl, cfg, st);
     if (rc) return set_err(ctx, rc, "relaxation begin launch failed");
@@ -511,11 +542,18 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     a.nx = g.nx;
     a.ny = g.ny;
     a.pitch = g.pitch;
-    a.strips = geo.strips;
-    a.RH = geo.RH;
-    a.tiles = geo.tiles;
-    const auto al8 = [](const void *q) { return (reinterpret_cast<uintptr_t>(q) & 7) == 0; };
-    a.pair = g.nx % 2 == 0 && g.pitch % 2 == 0 && al8(psi) && al8(a.alt) && (!p.polish || (al8(a.r32) && al8(a.e) && al8(a.cdc) && al8(a.clead)));
+    // fused passes are this call's own tilings: lowest tiles of one round
+    for (int l = 0; l < kSlotLevels; ++l) {
+        a.tiling[l] = SlotTiling{geo.strips, geo.RH, geo.tiles};
+        if (l == 0 || (1 << l) > fuse) continue;
+        const int D = pl.S << l;
+        const Geometry gl = stream_geometry(g.nx, g.ny, D,
+                                            std::min(default_height(ctx, g.nx, g.ny, D),
+                                                     stream_rows_cap(g.pitch, (int)sizeof(float), D)));
+        a.tiling[l] = SlotTiling{gl.strips, gl.RH, gl.tiles};
+    }
+    a.fuse = fuse;
+    a.even = g.nx % 2 == 0;
     a.final_slot = 0;
     a.slot = 0;
     a.polish = cfg.polish;
@@ -653,10 +691,10 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         }
     }
     if (p.rows_per_tile) RH = p.rows_per_tile;
-    bool pair = (reinterpret_cast<uintptr_t>(psi) & 7) == 0;  // the partner and mask are context-owned (aligned)
+    bool even = true;
     int max_pitch = 1;
     for (int k = 0; k < n; ++k) {
-        pair = pair && grids[k].nx % 2 == 0 && grids[k].pitch % 2 == 0 && grids[k].offset % 2 == 0;
+        even = even && grids[k].nx % 2 == 0;
         max_pitch = std::max(max_pitch, grids[k].pitch);
     }
     RH = std::min(RH < 2 ? 2 : (RH & ~1), stream_rows_cap(max_pitch, (int)sizeof(float), S));
@@ -703,7 +741,7 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     const void *old_batch = ctx->batch;
     int rc = ensure(ctx, &ctx->batch, &ctx->batch_bytes, bytes);
     if (!rc) rc = ensure(ctx, &ctx->alt, &ctx->alt_bytes, (size_t)total * sizeof(float));
-    if (!rc) rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, (size_t)total);
+    if (!rc) rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, (size_t)total + 1);
     if (rc) return rc;
     char *base = static_cast<char *>(ctx->batch);
     BatchGrid *d_grids = reinterpret_cast<BatchGrid *>(base + o_grids);
@@ -765,11 +803,11 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     if (slots > 0) {
         for (int64_t k = 0; k < slots; ++k) {
             a.slot = (int)k;
-            if ((rc = launch_batch_slot(a, mt, pair, st))) return set_err(ctx, rc, "batch slot launch failed");
+            if ((rc = launch_batch_slot(a, mt, even, st))) return set_err(ctx, rc, "batch slot launch failed");
         }
         a.final_slot = 1;
         a.slot = (int)slots;
-        rc = launch_batch_slot(a, mt, pair, st);
+        rc = launch_batch_slot(a, mt, even, st);
         return rc ? set_err(ctx, rc, "batch slot launch failed") : TWG_OK;
     }
 
@@ -793,7 +831,7 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         if (queued < target) {
             if (queued >= INT_MAX - 8) return set_err(ctx, TWG_EDEVICE, "batch slot count overflow");
             a.slot = (int)queued;
-            if ((rc = launch_batch_slot(a, mt, pair, st))) return set_err(ctx, rc, "batch slot launch failed");
+            if ((rc = launch_batch_slot(a, mt, even, st))) return set_err(ctx, rc, "batch slot launch failed");
             ++queued;
             continue;
         }
@@ -1349,9 +1387,11 @@ int32_t hpf_sweeps(twg_ctx *ctx, twg_grid g, const uint8_t *cls, float *psi, con
     int S = sweeps_per_pass, RH, dS;
     float om_unused;
     tiling_for(ctx, g.nx, g.ny, &dS, &RH, &om_unused);
-    if (!S) S = dS;
+    const bool tuned = ctx->tuned.count({g.nx, g.ny}) != 0;
+    if (!S) S = tuned ? dS : 8;  // the fewest launches (per-sweep times at plan_for)
     if (!stream_depth_supported(S))
         return set_err(ctx, TWG_EINVAL, "sweeps_per_pass must be 1 to 8");
+    if (!tuned) RH = default_height(ctx, g.nx, g.ny, S);
     rc = ensure(ctx, &ctx->alt, &ctx->alt_bytes, (size_t)g.pitch * g.ny * sizeof(float));
     if (rc) return rc;
     Runner run{ctx, g, cls, st};
@@ -1387,23 +1427,17 @@ int32_t hpf_sweeps64(twg_ctx *ctx, twg_grid g, const uint8_t *cls, double *psi64
     }
     int S, RH;
     tiling64_for(ctx, g.nx, g.ny, &S, &RH);
-    if (sweeps_per_pass) S = sweeps_per_pass;
-    if (!stream_depth_supported(S))
-        return set_err(ctx, TWG_EINVAL, "sweeps_per_pass must be 1 to 8");
+    if (sweeps_per_pass && sweeps_per_pass != S) {
+        if (!stream_depth_supported(sweeps_per_pass))
+            return set_err(ctx, TWG_EINVAL, "sweeps_per_pass must be 1 to 8");
+        S = sweeps_per_pass;
+        if (!ctx->tuned.count({g.nx, g.ny})) RH = default_height(ctx, g.nx, g.ny, S);
+    }
     rc = ensure(ctx, &ctx->alt64, &ctx->alt64_bytes, (size_t)g.pitch * g.ny * sizeof(double));
     if (rc) return rc;
     double *a = psi64, *b = reinterpret_cast<double *>(ctx->alt64);
     Runner run{ctx, g, cls, st};
-    const uint8_t *m = nullptr;
-    if ((rc = run.fmask(&m))) return rc;
-    const Geometry geo = stream_geometry(g.nx, g.ny, S, RH), geo1 = stream_geometry(g.nx, g.ny, 1, RH);
-    for (int64_t done = 0; done < sweeps;) {
-        const bool full = sweeps - done >= S;
-        rc = launch_stream_f64(a, b, m, omega, g.nx, g.ny, g.pitch, full ? geo : geo1, st);
-        if (rc) return set_err(ctx, rc, "relaxation kernel launch failed");
-        std::swap(a, b);
-        done += full ? S : 1;
-    }
+    if ((rc = run.sweep64(&a, &b, omega, S, RH, sweeps))) return rc;
     if (a != psi64 &&
         hipMemcpy2DAsync(psi64, (size_t)g.pitch * 8, a, (size_t)g.pitch * 8, (size_t)g.nx * 8, g.ny,
                          hipMemcpyDeviceToDevice, st) != hipSuccess)

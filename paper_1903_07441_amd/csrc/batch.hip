@@ -259,7 +259,7 @@ __device__ void batch_stats(const BatchArgs &a, int slot, bool forced)
 // At least three waves per SIMD (at most 168 VGPRs): the batch has several
 // tiles per SIMD, and the deepest tiling (S = 8) otherwise takes 171 and
 // runs at two (46.9 against 46.1 ms for the 256-grid batch).
-template <int S, bool PAIR>
+template <int S, bool EVEN>
 __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
 {
     BatchHdr *hp = static_cast<BatchHdr *>(a.hdr);
@@ -297,7 +297,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
             if (check) {
                 double rm = 0.0;
                 float rr = 0.0f;
-                stream_tile<float, S, kSrcNone, PAIR, true, kStoreBack, false>(src, dst, m, g.omega, nullptr, g.nx,
+                stream_tile<float, S, kSrcNone, EVEN, true, kStoreBack, false>(src, dst, m, g.omega, nullptr, g.nx,
                                                                                g.ny, g.pitch, xs, ybeg, yend, &rm,
                                                                                &rr);
                 for (int o = 32; o > 0; o >>= 1) {
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
                                            __HIP_MEMORY_SCOPE_AGENT);
                 }
             } else {
-                stream_tile<float, S, kSrcNone, PAIR, false, kStoreBack, false>(src, dst, m, g.omega, nullptr,
+                stream_tile<float, S, kSrcNone, EVEN, false, kStoreBack, false>(src, dst, m, g.omega, nullptr,
                                                                                 g.nx, g.ny, g.pitch, xs, ybeg,
                                                                                 yend);
             }
@@ -552,9 +552,9 @@ int last_status_b() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEV
 // Each depth's kernels are instantiated in a translation unit of their own
 // (this file compiled with TWG_DEPTH set), so that they build in parallel.
 template <int S>
-int launch_batch_slot_depth(const BatchArgs &a, int blocks, bool pair, hipStream_t st)
+int launch_batch_slot_depth(const BatchArgs &a, int blocks, bool even, hipStream_t st)
 {
-    if (pair)
+    if (even)
         hipLaunchKernelGGL((k_batch_slot<S, true>), dim3(blocks), dim3(256), 0, st, a);
     else
         hipLaunchKernelGGL((k_batch_slot<S, false>), dim3(blocks), dim3(256), 0, st, a);
@@ -599,21 +599,21 @@ int launch_batch_lds(const BatchArgs &a, size_t lds_bytes, size_t *lds_attr, hip
     return last_status_b();
 }
 
-int launch_batch_slot(const BatchArgs &a, int max_tiles, bool pair, hipStream_t st)
+int launch_batch_slot(const BatchArgs &a, int max_tiles, bool even, hipStream_t st)
 {
     // one wave per tile of the whole batch (the finishing slot's copy loops
     // over its items with the same waves)
     const int blocks = std::max(1, (max_tiles + 3) / 4);
     int rc;
     switch (a.S) {
-    case 1: rc = launch_batch_slot_depth<1>(a, blocks, pair, st); break;
-    case 2: rc = launch_batch_slot_depth<2>(a, blocks, pair, st); break;
-    case 3: rc = launch_batch_slot_depth<3>(a, blocks, pair, st); break;
-    case 4: rc = launch_batch_slot_depth<4>(a, blocks, pair, st); break;
-    case 5: rc = launch_batch_slot_depth<5>(a, blocks, pair, st); break;
-    case 6: rc = launch_batch_slot_depth<6>(a, blocks, pair, st); break;
-    case 7: rc = launch_batch_slot_depth<7>(a, blocks, pair, st); break;
-    case 8: rc = launch_batch_slot_depth<8>(a, blocks, pair, st); break;
+    case 1: rc = launch_batch_slot_depth<1>(a, blocks, even, st); break;
+    case 2: rc = launch_batch_slot_depth<2>(a, blocks, even, st); break;
+    case 3: rc = launch_batch_slot_depth<3>(a, blocks, even, st); break;
+    case 4: rc = launch_batch_slot_depth<4>(a, blocks, even, st); break;
+    case 5: rc = launch_batch_slot_depth<5>(a, blocks, even, st); break;
+    case 6: rc = launch_batch_slot_depth<6>(a, blocks, even, st); break;
+    case 7: rc = launch_batch_slot_depth<7>(a, blocks, even, st); break;
+    case 8: rc = launch_batch_slot_depth<8>(a, blocks, even, st); break;
     default: return TWG_EUNSUPPORTED;
     }
     if (rc) return rc;

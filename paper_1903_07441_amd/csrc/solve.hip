@@ -30,6 +30,7 @@
 // final slot that finishes whatever is left.
 #include "stream_tile.h"
 
+#include <algorithm>
 #include <cmath>
 
 namespace twg {
@@ -47,9 +48,9 @@ constexpr int64_t kStallSweeps = 256;
 // The words every slot reads when it starts, loaded together (one scalar
 // load): a run of passes of the current solve began at slot run_slot with
 // pass number `pass` and the field (or correction) in buffer parity
-// `parity` (`cparity`); slot k of the run does pass pass + (k - run_slot) on
-// parity ^ ((k - run_slot) & 1), so a pass that does not check writes
-// nothing to the control block.
+// `parity` (`cparity`); slot k of the run starts at the pass run_passes
+// gives, on parity ^ ((k - run_slot) & 1), so a pass that does not check
+// writes nothing to the control block.
 struct alignas(32) RelaxHot {
     int32_t phase;
     int32_t parity;        // FP32 field at run_slot: 0 in psi, 1 in alt
@@ -84,6 +85,35 @@ struct RelaxCtl {
     // part[b % kParts]); the slot's last workgroup combines and clears them
     unsigned long long part[kParts][2];
 };
+
+// A run of n passes before a check, fused `fuse` (a power of two) at a time:
+// passes done before slot k of the run, and (*level) the log2 of the passes
+// slot k does.  From the slot of the check on, one pass a slot.
+__device__ __forceinline__ int run_passes(int n, int fuse, int k, int *level)
+{
+    int done = 0;
+    for (int l = fuse >= 4 ? 2 : fuse >= 2 ? 1 : 0; l > 0; --l) {
+        const int q = max(n - done, 0) >> l;  // slots at this level
+        if (k < q) {
+            *level = l;
+            return done + (k << l);
+        }
+        done += q << l;
+        k -= q;
+    }
+    *level = 0;
+    return done + k;
+}
+// slots such a run takes
+__device__ __forceinline__ int run_slots(int n, int fuse)
+{
+    int slots = 0;
+    for (int l = fuse >= 4 ? 2 : fuse >= 2 ? 1 : 0; l > 0; --l) {
+        slots += n >> l;
+        n &= (1 << l) - 1;
+    }
+    return slots + n;
+}
 
 __device__ __forceinline__ unsigned long long dbits(double d) { return (unsigned long long)__double_as_longlong(d); }
 __device__ __forceinline__ double bitsd(unsigned long long b) { return __longlong_as_double((long long)b); }
@@ -311,7 +341,7 @@ __device__ void publish(const RelaxCtl *c, unsigned long long *mirror, int32_t s
         w = 1ull << 63;
     } else {
         int64_t next = slot_now + 1;  // DEFECT, UPDATE and FINISH decide in their own slot
-        if (c->h.phase == PH_PLAIN || c->h.phase == PH_CORR) next = slot_now + (c->h.next_check - c->h.pass) + 1;
+        if (c->h.phase == PH_PLAIN || c->h.phase == PH_CORR) next = slot_now + run_slots(c->h.next_check - c->h.pass, c->c.fuse) + 1;
         w = (unsigned long long)(next + 1);
     }
     *reinterpret_cast<volatile unsigned long long *>(mirror) = w;
@@ -498,7 +528,8 @@ __device__ __forceinline__ double defect_at(const T *u, int nx, int ny, int pitc
     return ((e + w) + (s + n)) * 0.25 - c;
 }
 
-template <int S, bool PAIR>
+// F: passes of S sweeps that one launch may do at once (1, 2 or 4)
+template <int S, int F, bool EVEN>
 __global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
 {
     RelaxCtl *c = static_cast<RelaxCtl *>(a.ctl);
@@ -508,9 +539,13 @@ __global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
     // position in the current run of passes (solve phases), derived before
     // any branch so that the words above arrive in one load
     const int k = __builtin_amdgcn_readfirstlane(a.slot - h.run_slot);
-    const int pass = __builtin_amdgcn_readfirstlane(h.pass) + k;
-    const int par = (__builtin_amdgcn_readfirstlane(was == PH_CORR ? h.cparity : h.parity) ^ k) & 1;
+    // slot k of a run: passes fused F (then F / 2, ...) at a time while that
+    // many are left before the next check, which starts a slot of its own
     const int next_check = __builtin_amdgcn_readfirstlane(h.next_check);
+    int level = 0;
+    const int pass = __builtin_amdgcn_readfirstlane(h.pass) +
+                     run_passes(__builtin_amdgcn_readfirstlane(next_check - h.pass), F > 1 ? a.fuse : 1, k, &level);
+    const int par = (__builtin_amdgcn_readfirstlane(was == PH_CORR ? h.cparity : h.parity) ^ k) & 1;
     const int hfresh = __builtin_amdgcn_readfirstlane(h.fresh), hwide = __builtin_amdgcn_readfirstlane(h.wide);
     const int hpar = __builtin_amdgcn_readfirstlane(h.parity), hcpar = __builtin_amdgcn_readfirstlane(h.cparity);
     if (was == PH_DONE) return;
@@ -531,26 +566,36 @@ __global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
         float *x0 = corr ? a.e : a.psi;
         float *src = par ? a.alt : x0, *dst = par ? x0 : a.alt;
         const float om = corr ? (pass < a.lead_passes ? a.omega_lead : a.omega_dc) : a.omega;
-        if (gw < a.tiles) {
-            constexpr int VW = 128 - 4 * S;
-            const int strip = gw % a.strips, seg = gw / a.strips;
-            const int ybeg = seg * a.RH, yend = min(ybeg + a.RH, a.ny);
-            const int xs = strip * VW - 2 * S;
-            if (corr) {
-                if (check)
-                    stream_tile<float, S, kSrcF, PAIR, true>(src, dst, a.mask, om, a.r32, a.nx, a.ny, a.pitch,
+        const SlotTiling t = a.tiling[F > 1 ? level : 0];
+        if (gw < t.tiles) {
+            const int strip = gw % t.strips, seg = gw / t.strips;
+            const int ybeg = seg * t.RH, yend = min(ybeg + t.RH, a.ny);
+            const float *cs = pass < a.lead_passes ? a.clead : a.cdc;
+            // a tile of D sweeps that does not check
+            auto tile = [&](auto D) __attribute__((always_inline)) {
+                constexpr int d = decltype(D)::value;
+                const int xs = strip * (128 - 4 * d) - 2 * d;
+                if (corr)
+                    stream_tile<float, d, kSrcC, EVEN, false>(src, dst, a.mask, om, cs, a.nx, a.ny, a.pitch, xs, ybeg,
+                                                              yend);
+                else
+                    stream_tile<float, d, kSrcNone, EVEN, false>(src, dst, a.mask, om, nullptr, a.nx, a.ny, a.pitch,
+                                                                 xs, ybeg, yend);
+            };
+            if (check) {
+                const int xs = strip * (128 - 4 * S) - 2 * S;
+                if (corr)
+                    stream_tile<float, S, kSrcF, EVEN, true>(src, dst, a.mask, om, a.r32, a.nx, a.ny, a.pitch,
                                                              xs, ybeg, yend, &m, &mr);
                 else
-                    stream_tile<float, S, kSrcC, PAIR, false>(src, dst, a.mask, om,
-                                                              pass < a.lead_passes ? a.clead : a.cdc, a.nx,
-                                                              a.ny, a.pitch, xs, ybeg, yend);
-            } else {
-                if (check)
-                    stream_tile<float, S, kSrcNone, PAIR, true>(src, dst, a.mask, om, nullptr, a.nx, a.ny,
+                    stream_tile<float, S, kSrcNone, EVEN, true>(src, dst, a.mask, om, nullptr, a.nx, a.ny,
                                                                 a.pitch, xs, ybeg, yend, &m, &mr);
-                else
-                    stream_tile<float, S, kSrcNone, PAIR, false>(src, dst, a.mask, om, nullptr, a.nx, a.ny,
-                                                                 a.pitch, xs, ybeg, yend);
+            } else if (F >= 4 && level == 2) {
+                tile(std::integral_constant<int, F >= 4 ? 4 * S : S>{});
+            } else if (F >= 2 && level == 1) {
+                tile(std::integral_constant<int, F >= 2 ? 2 * S : S>{});
+            } else {
+                tile(std::integral_constant<int, S>{});
             }
         }
         // a pass that does not check decides nothing: the next slot derives
@@ -722,11 +767,21 @@ int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVIC
 template <int S>
 int launch_relax_slot_depth(const SlotArgs &a, hipStream_t st)
 {
-    const int blocks = (a.tiles + 3) / 4;
-    if (a.pair)
-        hipLaunchKernelGGL((k_relax_slot<S, true>), dim3(blocks), dim3(256), 0, st, a);
-    else
-        hipLaunchKernelGGL((k_relax_slot<S, false>), dim3(blocks), dim3(256), 0, st, a);
+    constexpr int F = slot_fuse_limit(S);
+    int tiles = a.tiling[0].tiles;
+    for (const SlotTiling &t : a.tiling) tiles = std::max(tiles, t.tiles);
+    const dim3 blocks((tiles + 3) / 4);
+    if (F > 1 && a.fuse > 1) {
+        if (a.even)
+            hipLaunchKernelGGL((k_relax_slot<S, F, true>), blocks, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_relax_slot<S, F, false>), blocks, dim3(256), 0, st, a);
+    } else {
+        if (a.even)
+            hipLaunchKernelGGL((k_relax_slot<S, 1, true>), blocks, dim3(256), 0, st, a);
+        else
+            hipLaunchKernelGGL((k_relax_slot<S, 1, false>), blocks, dim3(256), 0, st, a);
+    }
     return last_status();
 }
 

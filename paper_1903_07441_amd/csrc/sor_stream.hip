@@ -34,7 +34,7 @@ using namespace sdev;
 
 int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE; }
 
-template <typename T, int S, bool RHS, bool PAIR>
+template <typename T, int S, bool RHS, bool EVEN>
 __global__ __launch_bounds__(256) void k_sor_stream(const T *__restrict__ src, T *__restrict__ dst,
                                                     const void *__restrict__ wsrc, T omega,
                                                     const T *__restrict__ f, int nx, int ny,
@@ -47,36 +47,25 @@ __global__ __launch_bounds__(256) void k_sor_stream(const T *__restrict__ src, T
     if (tile >= tiles) return;  // whole wave
     const int strip = tile % strips, seg = tile / strips;
     const int ybeg = seg * RH;
-    stream_tile<T, S, RHS, PAIR>(src, dst, static_cast<const uint8_t *>(wsrc), omega, f, nx, ny, pitch,
+    stream_tile<T, S, RHS, EVEN>(src, dst, static_cast<const uint8_t *>(wsrc), omega, f, nx, ny, pitch,
                                  strip * VW - 2 * S, ybeg, min(ybeg + RH, ny));
-}
-
-// Batched form: the tiles of many grids in one launch.  Grid g's arrays start
-// at element offset desc.off of the batch base pointers; the tile count is
-// read from device memory so that one captured launch serves any active set.
-template <typename T>
-bool pairable(const T *src, const T *dst, const void *wsrc, size_t wbytes, const T *f, int nx, int pitch)
-{
-    const auto al = [](const void *p, uintptr_t a) { return (reinterpret_cast<uintptr_t>(p) & (a - 1)) == 0; };
-    return nx % 2 == 0 && pitch % 2 == 0 && al(src, 2 * sizeof(T)) && al(dst, 2 * sizeof(T)) &&
-           al(wsrc, 2 * wbytes) && (!f || al(f, 2 * sizeof(T)));
 }
 
 }  // namespace
 
 // Each depth's kernels are instantiated in a translation unit of their own
 // (this file compiled with TWG_DEPTH set), so that they build in parallel.
-template <typename T, bool RHS, bool PAIR, int S>
+template <typename T, bool RHS, bool EVEN, int S>
 int launch_stream_depth(const T *src, T *dst, const void *wsrc, T omega, const T *f, int nx, int ny, int pitch,
                         const Geometry &g, hipStream_t st)
 {
-    hipLaunchKernelGGL((k_sor_stream<T, S, RHS, PAIR>), dim3((g.tiles + 3) / 4), dim3(256), 0, st, src, dst, wsrc,
+    hipLaunchKernelGGL((k_sor_stream<T, S, RHS, EVEN>), dim3((g.tiles + 3) / 4), dim3(256), 0, st, src, dst, wsrc,
                        omega, f, nx, ny, pitch, g.strips, g.RH, g.tiles);
     return last_status();
 }
 
-#define TWG_STREAM_INST(EX, T, RHS, PAIR, SV)                                                              \
-    EX template int launch_stream_depth<T, RHS, PAIR, SV>(const T *, T *, const void *, T, const T *, int, \
+#define TWG_STREAM_INST(EX, T, RHS, EVEN, SV)                                                              \
+    EX template int launch_stream_depth<T, RHS, EVEN, SV>(const T *, T *, const void *, T, const T *, int, \
                                                           int, int, const Geometry &, hipStream_t);
 #define TWG_STREAM_DEPTH(EX, SV)                                                                   \
     TWG_STREAM_INST(EX, float, false, false, SV) TWG_STREAM_INST(EX, float, false, true, SV)       \
@@ -91,14 +80,14 @@ TWG_STREAM_DEPTH(extern, 5) TWG_STREAM_DEPTH(extern, 6) TWG_STREAM_DEPTH(extern,
 
 namespace {
 
-template <typename T, bool RHS, bool PAIR>
+template <typename T, bool RHS, bool EVEN>
 int launch_stream(const T *src, T *dst, const void *wsrc, T omega, const T *f, int nx, int ny, int pitch,
                   const Geometry &geo, hipStream_t st)
 {
     const int cap = stream_rows_cap(pitch, sizeof(T), geo.S);
     const Geometry g = geo.RH > cap ? stream_geometry(nx, ny, geo.S, cap) : geo;
 #define TWG_STREAM_CASE(SV) \
-    case SV: return launch_stream_depth<T, RHS, PAIR, SV>(src, dst, wsrc, omega, f, nx, ny, pitch, g, st);
+    case SV: return launch_stream_depth<T, RHS, EVEN, SV>(src, dst, wsrc, omega, f, nx, ny, pitch, g, st);
     switch (g.S) {
         TWG_STREAM_CASE(1)
         TWG_STREAM_CASE(2)
@@ -139,7 +128,7 @@ Geometry stream_geometry(int nx, int ny, int S, int RH)
 int launch_stream_f32(const float *src, float *dst, const uint8_t *fmask, float omega, const float *f, int nx,
                       int ny, int pitch, const Geometry &geo, hipStream_t st)
 {
-    if (pairable(src, dst, fmask, 1, f, nx, pitch))
+    if (nx % 2 == 0)
         return f ? launch_stream<float, true, true>(src, dst, fmask, omega, f, nx, ny, pitch, geo, st)
                  : launch_stream<float, false, true>(src, dst, fmask, omega, f, nx, ny, pitch, geo, st);
     return f ? launch_stream<float, true, false>(src, dst, fmask, omega, f, nx, ny, pitch, geo, st)
@@ -149,7 +138,7 @@ int launch_stream_f32(const float *src, float *dst, const uint8_t *fmask, float 
 int launch_stream_f64(const double *src, double *dst, const uint8_t *fmask, double omega, int nx, int ny,
                       int pitch, const Geometry &geo, hipStream_t st)
 {
-    if (pairable(src, dst, fmask, 1, (const double *)nullptr, nx, pitch))
+    if (nx % 2 == 0)
         return launch_stream<double, false, true>(src, dst, fmask, omega, nullptr, nx, ny, pitch, geo, st);
     return launch_stream<double, false, false>(src, dst, fmask, omega, nullptr, nx, ny, pitch, geo, st);
 }

@@ -70,14 +70,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_
     asm volatile("" : "+s"(base));
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(base), 0, (int)bytes, 0x00020000);
 }
-__device__ __forceinline__ float bload(float *, __amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, (int)vo, (int)so, 0));
-}
-__device__ __forceinline__ double bload(double *, __amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
-{
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)vo, (int)so, 0));
-}
 // Store cache policy of the field rows.  kStoreThrough (sc1): the L2 writes
 // them through at agent scope, so its lines are clean when the kernel ends
 // and the release between two passes has nothing to write back.  Measured
@@ -103,9 +95,9 @@ __device__ __forceinline__ void bstore(double v, __amdgpu_buffer_rsrc_t r, uint3
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(bv2, v), r, (int)vo, (int)so, AUX);
 }
 
-// two adjacent elements in one access (PAIR tiles: even pitch, even nx and
-// aligned bases, so a pair never straddles a row, the grid's edge or the
-// resource's end)
+// Two adjacent elements in one access.  Rows need no alignment beyond the
+// element's (buffer accesses of several dwords are dword aligned), and the
+// range check of such an access is made dword by dword.
 template <typename T> struct Pair { T a, b; };
 __device__ __forceinline__ Pair<float> bload2(float *, __amdgpu_buffer_rsrc_t r, uint32_t vo, uint32_t so)
 {
@@ -155,10 +147,14 @@ constexpr int kSrcNone = 0, kSrcF = 1, kSrcC = 2;
 // rows [ybeg, yend) of a grid; x0 and ybeg are even, all tile values are
 // wave-uniform.  wsrc is the one-byte free mask (0xFF on FREE cells, else
 // 0): a FREE cell takes the factor omega, any other cell 0 (it is rewritten
-// unchanged).  f is the source term of mode RHS.  PAIR tiles move each
-// lane's two columns in one access (three memory operations per row instead
-// of six), which keeps a whole window of prefetches within the hardware's
-// count of outstanding vector memory operations.
+// unchanged).  f is the source term of mode RHS.  Each lane moves its two
+// columns in one access (three memory operations per row), which keeps a whole window
+// of prefetches within the hardware's count of outstanding vector memory
+// operations.  EVEN: nx is even, so a lane's two columns lie on the same side
+// of the grid's edge; else the lane at the edge has its second column masked
+// off as its row enters the pipeline and stores its first one alone (1001 x
+// 743, S = 4: 6.3 us a pass with two accesses per lane for odd widths and
+// pitches, before).
 //
 // Registers.  The pipeline needs NW = 2S + 2 rows at a time (the rows its
 // stages touch and the row the last stage finishes), and each row is fetched
@@ -204,7 +200,7 @@ __device__ __forceinline__ void static_while(std::integer_sequence<int, U...>, F
 }
 __device__ __forceinline__ float nan_maxf(float a, float b) { return (b > a || b != b) ? b : a; }
 
-template <typename T, int S, int RHS, bool PAIR, bool CHECK = false, int STORE = kStoreThrough, bool SLOT_OFS = true>
+template <typename T, int S, int RHS, bool EVEN, bool CHECK = false, int STORE = kStoreThrough, bool SLOT_OFS = true>
 __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__restrict__ dst,
                                             const uint8_t *__restrict__ wsrc, T omega,
                                             const T *__restrict__ f, int nx, int ny, int pitch,
@@ -229,7 +225,9 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
     const uint32_t outc = (uint32_t)(yend - ybeg - 1) * (uint32_t)pitch + (uint32_t)nx;
     const size_t base = (size_t)lo * pitch;
     const __amdgpu_buffer_rsrc_t rs = rsrc(src + base, cells * sizeof(T));
-    const __amdgpu_buffer_rsrc_t rw = rsrc(wsrc + base, cells);
+    // the mask's two bytes are read in one access, whole or not at all: its
+    // resource ends one byte later (the mask buffer has that byte)
+    const __amdgpu_buffer_rsrc_t rw = rsrc(wsrc + base, cells + 1);
     const __amdgpu_buffer_rsrc_t rf = rsrc(RHS ? f + base : src + base, cells * sizeof(T));
     const __amdgpu_buffer_rsrc_t rd = rsrc(dst + (size_t)ybeg * pitch, outc * sizeof(T));
     // per-lane constants: a column outside the grid gets an out-of-range
@@ -238,11 +236,11 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
     const int xa = x0 + 2 * lane;
     const bool in0 = xa >= 0 && xa < nx, in1 = xa + 1 >= 0 && xa + 1 < nx;
     const bool writer = lane >= S && lane < kWave - S;
-    const uint32_t xb0 = in0 ? (uint32_t)xa * sizeof(T) : kNoStore;
-    const uint32_t xb1 = in1 ? (uint32_t)(xa + 1) * sizeof(T) : kNoStore;
-    const uint32_t xm0 = in0 ? (uint32_t)xa : kNoStore, xm1 = in1 ? (uint32_t)(xa + 1) : kNoStore;
-    const uint32_t so0 = writer ? xb0 : kNoStore;
-    const uint32_t so1 = writer ? xb1 : kNoStore;
+    const uint32_t xb = in0 ? (uint32_t)xa * sizeof(T) : kNoStore;
+    const uint32_t xm = in0 ? (uint32_t)xa : kNoStore;
+    const uint32_t so2 = writer && (EVEN || in1) ? xb : kNoStore;  // both columns
+    const uint32_t so1 = writer && !in1 ? xb : kNoStore;           // the first alone
+    const int32_t in1m = in1 ? -1 : 0;
     // row offsets (bytes) of streamed row t and of output row t - 4S;
     // negative ones are far out of range as unsigned sums
     const int vrow0 = (r0 - lo) * (int)rowb, mrow0 = (r0 - lo) * pitch;
@@ -251,38 +249,24 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
     // ring: the two columns of a row (P0 = column 2 lane, P1 = 2 lane + 1),
     // its raw mask bytes and, with a source term, its f (or c) values
     T P0[NR], P1[NR], F0[NR], F1[NR];
-    uint32_t M0[NR], M1[NR];
+    uint32_t M[NR];
     // factors of the rows in the pipeline, by row mod NW (red, black), and
     // with a source term the update constants of update.h
     T wR[NW], wB[NW];
     SrcConst<T> kR[NW], kB[NW];
-    // loads of a row into ring slot `slot`: lane offsets (columns 2 lane and
-    // 2 lane + 1 of the field, then of the mask) and scalar row offsets.
-    // The field is loaded before the mask: the row step that takes the row
-    // in needs both, and loads complete in order, so one wait (for the
-    // mask) covers the two.
-    auto fetch_at = [&](int slot, uint32_t b0, uint32_t b1, uint32_t m0, uint32_t m1, uint32_t vo, uint32_t mo) {
-        if constexpr (PAIR) {
-            const Pair<T> v = bload2((T *)nullptr, rs, b0, vo);
-            P0[slot] = v.a;
-            P1[slot] = v.b;
-            M0[slot] = __builtin_amdgcn_raw_buffer_load_b16(rw, (int)m0, (int)mo, 0);
-            if (RHS) {
-                const Pair<T> h = bload2((T *)nullptr, rf, b0, vo);
-                F0[slot] = h.a;
-                F1[slot] = h.b;
-            }
-        } else {
-            P0[slot] = bload((T *)nullptr, rs, b0, vo);
-            P1[slot] = bload((T *)nullptr, rs, b1, vo);
-            // sign-extended by the load itself: extended at its use instead,
-            // the byte is loaded there, and every row step waits for it
-            M0[slot] = (uint32_t)(int32_t)(int8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (int)m0, (int)mo, 0);
-            M1[slot] = (uint32_t)(int32_t)(int8_t)__builtin_amdgcn_raw_buffer_load_b8(rw, (int)m1, (int)mo, 0);
-            if (RHS) {
-                F0[slot] = bload((T *)nullptr, rf, b0, vo);
-                F1[slot] = bload((T *)nullptr, rf, b1, vo);
-            }
+    // loads of a row into ring slot `slot`: lane offsets (of the field, then
+    // of the mask) and scalar row offsets.  The field is loaded before the
+    // mask: the row step that takes the row in needs both, and loads complete
+    // in order, so one wait (for the mask) covers the two.
+    auto fetch_at = [&](int slot, uint32_t b, uint32_t m, uint32_t vo, uint32_t mo) {
+        const Pair<T> v = bload2((T *)nullptr, rs, b, vo);
+        P0[slot] = v.a;
+        P1[slot] = v.b;
+        M[slot] = __builtin_amdgcn_raw_buffer_load_b16(rw, (int)m, (int)mo, 0);
+        if (RHS) {
+            const Pair<T> h = bload2((T *)nullptr, rf, b, vo);
+            F0[slot] = h.a;
+            F1[slot] = h.b;
         }
     };
     // The first window (stream rows 0 .. NW - 1, some of them above the
@@ -294,27 +278,24 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
     // and tb + NW rows in one scalar offset per turn.  Both parts are
     // non-negative and the sums are the same as in one piece, so the range
     // check sees the same offsets and no sum wraps; the row steps spend no
-    // scalar instruction on load offsets.  That costs 2 NR registers (4 NR
-    // unpaired); SLOT_OFS = false (kernels that run several waves per SIMD)
+    // scalar instruction on load offsets.  That costs 2 NR registers;
+    // SLOT_OFS = false (kernels that run several waves per SIMD)
     // forms every fetch's offsets in the scalar part instead.
-    uint32_t lb0[NR], lb1[NR], lm0[NR], lm1[NR];
+    uint32_t lb[NR], lm[NR];
 #pragma unroll
     for (int u = 0; u < NR && SLOT_OFS; ++u) {
-        lb0[u] = xb0 + (uint32_t)u * rowb;
-        lm0[u] = xm0 + (uint32_t)u * (uint32_t)pitch;
-        lb1[u] = PAIR ? 0u : xb1 + (uint32_t)u * rowb;
-        lm1[u] = PAIR ? 0u : xm1 + (uint32_t)u * (uint32_t)pitch;
+        lb[u] = xb + (uint32_t)u * rowb;
+        lm[u] = xm + (uint32_t)u * (uint32_t)pitch;
         // kept as registers (not re-formed in the loop, where they would
         // cost an instruction each)
-        asm volatile("" : "+v"(lb0[u]), "+v"(lm0[u]));
-        if constexpr (!PAIR) asm volatile("" : "+v"(lb1[u]), "+v"(lm1[u]));
+        asm volatile("" : "+v"(lb[u]), "+v"(lm[u]));
     }
     auto fetch = [&](int slot, int t) {
-        fetch_at(slot, xb0, xb1, xm0, xm1, (uint32_t)(vrow0 + t * (int)rowb), (uint32_t)(mrow0 + t * pitch));
+        fetch_at(slot, xb, xm, (uint32_t)(vrow0 + t * (int)rowb), (uint32_t)(mrow0 + t * pitch));
     };
     auto fetch_loop = [&](int slot, int u, int tb) {
         if constexpr (SLOT_OFS)
-            fetch_at(slot, lb0[u], lb1[u], lm0[u], lm1[u], (uint32_t)(vrow0 + (tb + NW) * (int)rowb),
+            fetch_at(slot, lb[u], lm[u], (uint32_t)(vrow0 + (tb + NW) * (int)rowb),
                      (uint32_t)(mrow0 + (tb + NW) * pitch));
         else
             fetch(slot, tb + u + NW);
@@ -337,7 +318,7 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
 #pragma unroll
     for (int i = 0; i < NR; ++i) {
         P0[i] = P1[i] = F0[i] = F1[i] = T(0);
-        M0[i] = M1[i] = 0u;
+        M[i] = 0u;
     }
 #pragma unroll
     for (int i = 0; i < NW; ++i) wR[i] = wB[i] = T(0);
@@ -357,8 +338,14 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         {
             // the mask bytes sign-extended (all ones on a FREE cell); the
             // factor is omega or +0, bit for bit omega x (0 or 1)
-            const int32_t e0 = PAIR ? (int32_t)(M0[u] << 24) >> 24 : (int32_t)M0[u];
-            const int32_t e1 = PAIR ? (int32_t)(M0[u] << 16) >> 24 : (int32_t)M1[u];
+            const int32_t e0 = (int32_t)(M[u] << 24) >> 24;
+            int32_t e1 = (int32_t)(M[u] << 16) >> 24;
+            if constexpr (!EVEN) {
+                // a second column outside the grid reads as zero and fixed
+                e1 &= in1m;
+                P1[u] = keep(P1[u], in1m);
+                if (RHS) F1[u] = keep(F1[u], in1m);
+            }
             const bool ev = (u & 1) == 0;
             if constexpr (RHS != kSrcC) {
                 const T w0 = keep(omega, e0), w1 = keep(omega, e1);
@@ -457,12 +444,8 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         if (out) {
             const int s = (u - 2 * S + 2 * NR) % NR;
             const uint32_t ro = (uint32_t)(orow0 + t * (int)rowb);
-            if constexpr (PAIR) {
-                bstore2<STORE>(P0[s], P1[s], rd, so0, ro);
-            } else {
-                bstore<STORE>(P0[s], rd, so0, ro);
-                bstore<STORE>(P1[s], rd, so1, ro);
-            }
+            bstore2<STORE>(P0[s], P1[s], rd, so2, ro);
+            if constexpr (!EVEN) bstore<STORE>(P0[s], rd, so1, ro);
         }
         // keep this row's prefetch in this row step: without the fence
         // the scheduler sinks every prefetch of the window to its end

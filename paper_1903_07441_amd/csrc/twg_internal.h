@@ -187,10 +187,16 @@ struct RelaxConfig {
     int32_t polish;      // 1: FP64 defect correction after the FP32 solve
     int32_t check_passes;  // > 0: check every this many passes
     int32_t max_rounds;  // defect-correction rounds at most
+    int32_t fuse;        // 1, 2 or 4: passes between two checks that one slot may do at once
     int32_t kept;        // 1: polish of the caller's kept FP32 field, whose first
                          // defect also checks the FP32 stage (0 sweeps when it
                          // meets tol)
 };
+// SOR tiling of a slot: strips of 128 - 4 depth columns, RH rows per tile
+struct SlotTiling {
+    int strips = 0, RH = 0, tiles = 0;
+};
+constexpr int kSlotLevels = 3;
 struct SlotArgs {
     const uint8_t *mask;  // free mask (0xFF on FREE cells), the grid's layout
     float *psi;           // caller's FP32 field
@@ -203,8 +209,9 @@ struct SlotArgs {
     hpf_stats *stats;     // device stats, written when the solve ends
     unsigned long long *mirror;  // host-mapped decision word, or null
     int nx, ny, pitch;
-    int strips, RH, tiles;  // SOR tiling (S sweeps per pass)
-    int pair;             // paired-column access
+    SlotTiling tiling[kSlotLevels];  // SOR tiling of a pass (S sweeps), and of 2 and 4 passes fused
+    int fuse;             // passes a launch may fuse (RelaxConfig::fuse)
+    int even;             // nx is even
     int final_slot;       // 1: finish what is left (the solve is then NOT_CONVERGED)
     int slot;             // this launch's number in the call's sequence (0, 1, ...)
     int polish;           // RelaxConfig::polish
@@ -214,6 +221,8 @@ struct SlotArgs {
 size_t relax_ctl_bytes();
 int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st);
 int launch_relax_slot(const SlotArgs &a, int S, hipStream_t st);
+// passes a slot may fuse at S sweeps per pass (their kernels exist)
+constexpr int slot_fuse_limit(int S) { return S == 2 ? 4 : S == 4 ? 2 : 1; }
 
 // batch.hip: the device-driven relaxation of a batch of grids.  BatchArgs
 // are the arguments of the begin kernel and of every slot launch.
@@ -246,7 +255,7 @@ size_t batch_hdr_bytes();
 size_t batch_run_bytes();
 size_t batch_ctl_bytes();
 int launch_batch_begin(const BatchArgs &a, hipStream_t st);
-int launch_batch_slot(const BatchArgs &a, int max_tiles, bool pair, hipStream_t st);
+int launch_batch_slot(const BatchArgs &a, int max_tiles, bool even, hipStream_t st);
 // LDS bytes k_batch_lds needs for a grid of `cells` cells; the solve of the
 // LDS grids (one workgroup each), launched after launch_batch_begin
 size_t batch_lds_bytes(long long cells);
