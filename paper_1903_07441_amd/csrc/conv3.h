@@ -1,0 +1,33 @@
+// The network's 3x3 convolutions (conv3.hip): forward layers and input
+// gradients.
+#pragma once
+
+#include "twg_internal.h"
+
+namespace twg {
+
+// Where a convolution's input comes from: one tensor [B][H][W][CIN], or the
+// concatenation of a half-resolution tensor (nearest upsampling, channels
+// < CA) with a full-resolution one.
+constexpr int kPlain = 0, kUpCat = 1;
+
+// What becomes of its output: bf16(relu(acc + bias)); the same and its 2x2
+// mean (the next level's input); the network's head on the same, not stored;
+// or the FP32 accumulators (input gradients).
+constexpr int kOutAct = 0, kOutPool = 1, kOutHead = 2, kOutF32 = 3;
+
+struct ConvArgs {
+    const uint16_t *A, *Bs;  // input (Bs: the full-resolution half of kUpCat)
+    const uint16_t *wt;      // weights [COUT][9][CIN]
+    const float *bias;
+    void *out;               // [B][H][W][COUT] bf16 (FP32 for kOutF32); unused by kOutHead
+    uint16_t *pool;          // kOutPool: [B][H/2][W/2][COUT]
+    const float *hw, *hb;    // kOutHead: the head's weights and bias
+    float *y;                // kOutHead: [B][H][W]
+    int nb, H, W;
+};
+
+template <int CIN, int COUT, int MODE, int CA, int OUT>
+int launch_conv3(const ConvArgs &a, int num_cu, hipStream_t st);
+
+}  // namespace twg

@@ -1,0 +1,276 @@
+// The network's 3x3 convolutions on gfx950 matrix cores, as an implicit GEMM
+// on v_mfma_f32_16x16x32_bf16: D[cout][pixel] = sum_k W[cout][k] In[k][pixel].
+//
+// A workgroup (4 waves) computes 32 output channels of a tile 16 pixels wide
+// and 4 R high (R rows a wave).  Per 32-channel chunk of the input, the
+// tile's halo and the chunk's weights are copied to LDS by the memory system
+// itself (buffer loads with LDS as the destination: no staging registers, and
+// the range check fills the pixels outside the image with zeros), then every
+// wave keeps the chunk's 18 weight fragments in registers and walks its rows:
+// R + 2 halo rows are read once per column shift for 9 R products of each
+// fragment.  LDS holds the weights in fragment order and the halo with its
+// 16-byte groups swizzled by the pixel's column, so every LDS read is free of
+// bank conflicts.  A pixel's products are added in the order chunk, tap,
+// whatever the tile, so every tiling gives the same bits.
+//
+// The tile height is chosen for the number of workgroups: R = 8 (67 KB of
+// LDS reads feed 1152 products per chunk, so the matrix cores bound it) as
+// long as that leaves two workgroups per CU, else lower tiles (a 32 x 32 layer
+// has four 16 x 16 tiles, on a device of 256 CUs).
+//
+// The epilogue goes through LDS: stores are 16-byte runs of channels, the
+// layers that the encoder pools write the 2x2 means as well (their consumers
+// then read a quarter of the bytes, once, instead of pooling while staging),
+// and the last layer's head is evaluated from LDS instead of from a stored
+// activation.
+//
+// Measured (whole calls, against 16 x 16 tiles that staged through registers,
+// pooled while staging and loaded every wave's weights from global memory one
+// tap ahead of their use): warm start at 2048 x 2048 1231 -> 644 us, at 1/8
+// of it 214 -> 92 us, loss and gradients of 16 x 256 x 256 1676 -> 1379 us.
+#include "conv3.h"
+#include "tile_map.h"
+#include "unet_dev.h"
+
+#include <algorithm>
+
+namespace twg {
+
+namespace {
+
+using namespace ndev;
+
+constexpr int kTW = 16;         // tile width
+constexpr int kHW = kTW + 2;    // halo width
+constexpr int kCK = 32;         // input channels per chunk
+constexpr int kCO = 32;         // output channels per workgroup
+constexpr int kSS = kCO + 8;    // LDS stride of an output pixel (bf16)
+constexpr uint32_t kOutside = 0x80000000u;  // a byte offset no resource reaches
+
+typedef __attribute__((address_space(3))) void lds_void;
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+template <int CIN, int COUT, int MODE, int CA, int OUT, int R>
+__global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
+{
+    constexpr int NCO = COUT / kCO, NCH = CIN / kCK, CB = CIN - CA;
+    constexpr int TH = 4 * R, NPX = (TH + 2) * kHW;
+    constexpr int HG = (NPX * 4 + 63) / 64;  // halo copies of 64 x 16 bytes
+    constexpr int HPW = (HG + 3) / 4, WPW = (18 + 3) / 4;  // per wave
+    constexpr int HALO = HG * 512, LDS = std::max(HALO + 18 * 512, TH * kTW * kSS);  // bf16
+    __shared__ __align__(16) uint16_t lds[LDS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int j = lane & 15, g = lane >> 4;
+    const int H = a.H, W = a.W;
+    const int id = xcd_remap(blockIdx.x, gridDim.x);
+    const int co0 = (id % NCO) * kCO, t = id / NCO;
+    const int b = t / (tx * ty), r = t - b * (tx * ty);
+    const int x0 = (r % tx) * kTW, y0 = (r / tx) * TH;
+
+    // resources of the image rows the halo touches, and each lane's offsets
+    // in them: slot 4 p + s of LDS takes channel group s ^ (column / 4) of
+    // halo pixel p
+    const int ylo = max(y0 - 1, 0), yhi = min(y0 + TH + 1, H);
+    const size_t row = (size_t)b * H + ylo;
+    __amdgpu_buffer_rsrc_t ra, rb;
+    if constexpr (MODE == kPlain) {
+        ra = rsrc(a.A + row * W * CIN, (uint32_t)(yhi - ylo) * W * CIN * 2);
+        rb = ra;
+    } else {
+        const int W2 = W / 2;
+        ra = rsrc(a.A + ((size_t)b * (H / 2) + ylo / 2) * W2 * CA,
+                  (uint32_t)((yhi - 1) / 2 - ylo / 2 + 1) * W2 * CA * 2);
+        rb = rsrc(a.Bs + row * W * CB, (uint32_t)(yhi - ylo) * W * CB * 2);
+    }
+    uint32_t oa[HPW], ob[HPW];
+#pragma unroll
+    for (int i = 0; i < HPW; ++i) {
+        const int slot = (i * 4 + wave) * 64 + lane, p = slot >> 2;
+        const int hy = p / kHW, hx = p - hy * kHW;
+        const int cg = (slot & 3) ^ ((hx >> 2) & 3);
+        const int yy = y0 + hy - 1, xx = x0 + hx - 1;
+        const bool in = p < NPX && yy >= 0 && yy < H && xx >= 0 && xx < W;
+        if constexpr (MODE == kPlain) {
+            oa[i] = in ? (uint32_t)((yy - ylo) * W + xx) * (CIN * 2) + cg * 16 : kOutside;
+        } else {
+            oa[i] = in ? (uint32_t)((yy / 2 - ylo / 2) * (W / 2) + xx / 2) * (CA * 2) + cg * 16 : kOutside;
+            ob[i] = in ? (uint32_t)((yy - ylo) * W + xx) * (CB * 2) + cg * 16 : kOutside;
+        }
+    }
+    const __amdgpu_buffer_rsrc_t rw = rsrc(a.wt + (size_t)co0 * 9 * CIN, kCO * 9 * CIN * 2);
+    const uint32_t ow = (uint32_t)(j * 9 * CIN + g * 8) * 2;
+    auto copy16 = [&](__amdgpu_buffer_rsrc_t rs, int at, uint32_t vo, uint32_t so) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void *)(lds + at), 16, (int)vo, (int)so, 0, 0);
+    };
+    auto load = [&](int ch) __attribute__((always_inline)) {
+        const bool low = MODE == kPlain || ch < CA / kCK;
+        const uint32_t so = (uint32_t)(low ? ch : ch - CA / kCK) * (kCK * 2);
+#pragma unroll
+        for (int i = 0; i < HPW; ++i) {
+            const int q = i * 4 + wave;
+            if (q >= HG) continue;
+            if (low) copy16(ra, q * 512, oa[i], so);
+            else copy16(rb, q * 512, MODE == kPlain ? oa[i] : ob[i], so);
+        }
+#pragma unroll
+        for (int i = 0; i < WPW; ++i) {
+            const int q = i * 4 + wave;  // tap * 2 + row block
+            if (q >= 18) continue;
+            copy16(rw, HALO + q * 512, ow, (uint32_t)((q & 1) * 16 * 9 * CIN + (q >> 1) * CIN + ch * kCK) * 2);
+        }
+    };
+
+    f32x4 acc[R][2];
+#pragma unroll
+    for (int ct = 0; ct < R; ++ct)
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) acc[ct][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // this lane's halo fragment of row 0 of its wave at the three shifts
+    const uint16_t *hp[3];
+#pragma unroll
+    for (int dx = 0; dx < 3; ++dx)
+        hp[dx] = lds + (((wave * R) * kHW + j + dx) * 4 + (g ^ (((j + dx) >> 2) & 3))) * 8;
+    const uint16_t *wp = lds + HALO + lane * 8;
+
+    load(0);
+    for (int ch = 0; ch < NCH; ++ch) {
+        // the copies of every wave have landed
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+        uint4 w[18];
+#pragma unroll
+        for (int q = 0; q < 18; ++q) w[q] = *reinterpret_cast<const uint4 *>(wp + q * 512);
+        // two rows at a time: four independent chains of products
+        constexpr int RB = R > 1 ? 2 : 1;
+#pragma unroll
+        for (int c0 = 0; c0 < R; c0 += RB) {
+            uint4 h[RB + 2][3];
+#pragma unroll
+            for (int q = 0; q < RB + 2; ++q)
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+                    h[q][dx] = *reinterpret_cast<const uint4 *>(hp[dx] + (c0 + q) * kHW * 32);
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap)
+#pragma unroll
+                for (int c = 0; c < RB; ++c)
+#pragma unroll
+                    for (int rt = 0; rt < 2; ++rt)
+                        acc[c0 + c][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            as_bf8(w[tap * 2 + rt]), as_bf8(h[c + tap / 3][tap % 3]), acc[c0 + c][rt], 0, 0, 0);
+        }
+        __syncthreads();
+        if (ch + 1 < NCH) load(ch + 1);
+    }
+
+    if constexpr (OUT == kOutF32) {
+        const int x = x0 + j;
+#pragma unroll
+        for (int ct = 0; ct < R; ++ct) {
+            const int y = y0 + wave * R + ct;
+            if (y >= H || x >= W) continue;
+            float *o = static_cast<float *>(a.out) + (((size_t)b * H + y) * W + x) * COUT + co0 + g * 4;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                const f32x4 v = acc[ct][rt];
+                *reinterpret_cast<float4 *>(o + rt * 16) = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        }
+    } else {
+        // the tile as bf16(relu(acc + bias)) in LDS, pixel by pixel
+#pragma unroll
+        for (int rt = 0; rt < 2; ++rt) {
+            const float *bp = a.bias + co0 + rt * 16 + g * 4;
+            const float b0 = bp[0], b1 = bp[1], b2 = bp[2], b3 = bp[3];
+#pragma unroll
+            for (int ct = 0; ct < R; ++ct) {
+                const f32x4 v = acc[ct][rt];
+                *reinterpret_cast<uint2 *>(lds + ((wave * R + ct) * kTW + j) * kSS + rt * 16 + g * 4) =
+                    make_uint2(pack2(relu(v[0] + b0), relu(v[1] + b1)), pack2(relu(v[2] + b2), relu(v[3] + b3)));
+            }
+        }
+        __syncthreads();
+        if constexpr (OUT == kOutHead) {
+            for (int p = tid; p < TH * kTW; p += 256) {
+                const int y = y0 + p / kTW, x = x0 + p % kTW;
+                uint4 v[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = *reinterpret_cast<const uint4 *>(lds + p * kSS + q * 8);
+                float d[32];
+                const float yv = head_value(v, a.hw, a.hb[0], d);
+                if (y < H && x < W) a.y[((size_t)b * H + y) * W + x] = yv;
+            }
+        } else {
+            uint16_t *out = static_cast<uint16_t *>(a.out);
+#pragma unroll
+            for (int q = tid; q < TH * kTW * 4; q += 256) {
+                const int p = q >> 2, c8 = q & 3;
+                const int y = y0 + p / kTW, x = x0 + p % kTW;
+                const uint4 v = *reinterpret_cast<const uint4 *>(lds + p * kSS + c8 * 8);
+                if (y < H && x < W)
+                    *reinterpret_cast<uint4 *>(out + (((size_t)b * H + y) * W + x) * COUT + co0 + c8 * 8) = v;
+            }
+            if constexpr (OUT == kOutPool) {
+                const int H2 = H / 2, W2 = W / 2;
+                for (int q = tid; q < TH * kTW; q += 256) {  // TH / 2 x kTW / 2 pixels, 4 groups each
+                    const int p = q >> 2, c8 = q & 3, py = p / (kTW / 2), px = p % (kTW / 2);
+                    const int y = y0 / 2 + py, x = x0 / 2 + px;
+                    const uint16_t *s = lds + ((2 * py) * kTW + 2 * px) * kSS + c8 * 8;
+                    const uint4 v = mean4(*reinterpret_cast<const uint4 *>(s), *reinterpret_cast<const uint4 *>(s + kSS),
+                                          *reinterpret_cast<const uint4 *>(s + kTW * kSS),
+                                          *reinterpret_cast<const uint4 *>(s + kTW * kSS + kSS));
+                    if (y < H2 && x < W2)
+                        *reinterpret_cast<uint4 *>(a.pool + (((size_t)b * H2 + y) * W2 + x) * COUT + co0 + c8 * 8) = v;
+                }
+            }
+        }
+    }
+}
+
+template <int CIN, int COUT, int MODE, int CA, int OUT, int R>
+int launch_r(const ConvArgs &a, hipStream_t st)
+{
+    const int tx = (a.W + kTW - 1) / kTW, ty = (a.H + 4 * R - 1) / (4 * R);
+    hipLaunchKernelGGL((k_conv3<CIN, COUT, MODE, CA, OUT, R>), dim3((unsigned)(a.nb * tx * ty * (COUT / kCO))),
+                       dim3(256), 0, st, a, tx, ty);
+    return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE;
+}
+
+}  // namespace
+
+template <int CIN, int COUT, int MODE, int CA, int OUT>
+int launch_conv3(const ConvArgs &a, int num_cu, hipStream_t st)
+{
+    // workgroups at R rows per wave
+    auto groups = [&](int R) {
+        return (long long)a.nb * ((a.W + kTW - 1) / kTW) * ((a.H + 4 * R - 1) / (4 * R)) * (COUT / kCO);
+    };
+    const long long want = 2LL * std::max(1, num_cu);
+    if (groups(8) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 8>(a, st);
+    if (groups(4) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 4>(a, st);
+    if (groups(2) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 2>(a, st);
+    return launch_r<CIN, COUT, MODE, CA, OUT, 1>(a, st);
+}
+
+// forward
+template int launch_conv3<32, 64, kPlain, 0, kOutPool>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 128, kPlain, 0, kOutPool>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<128, 128, kPlain, 0, kOutAct>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<256, 64, kUpCat, 128, kOutAct>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<128, 32, kUpCat, 64, kOutAct>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 32, kUpCat, 32, kOutAct>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 32, kUpCat, 32, kOutHead>(const ConvArgs &, int, hipStream_t);
+// input gradients
+template int launch_conv3<32, 64, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 128, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 256, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<128, 128, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<128, 64, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 32, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+
+}  // namespace twg

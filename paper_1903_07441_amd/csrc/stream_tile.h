@@ -7,6 +7,7 @@
 #include <type_traits>
 #include <utility>
 
+#include "tile_map.h"
 #include "twg_internal.h"
 #include "update.h"
 
@@ -37,16 +38,6 @@ __device__ __forceinline__ double shl1(double v)
     int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);
     int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
-}
-
-// Blocks are dispatched round-robin over the 8 XCDs; give each XCD a
-// contiguous range of tiles so that its L2 sees a compact band of the grid.
-__device__ __forceinline__ int xcd_remap(int b, int nb)
-{
-    constexpr int X = 8;
-    int per = nb / X, rem = nb % X;
-    int xcd = b % X, local = b / X;
-    return xcd < rem ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
 // ---- buffer addressing ---------------------------------------------------

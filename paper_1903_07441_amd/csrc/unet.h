@@ -35,6 +35,8 @@ struct twg_unet {
     long long fwd_pixels = 0;
     uint16_t *xp = nullptr, *e0 = nullptr, *e1 = nullptr, *e2 = nullptr, *e3 = nullptr;
     uint16_t *d2 = nullptr, *d1 = nullptr, *d0 = nullptr;
+    uint16_t *p0 = nullptr, *p1 = nullptr, *p2 = nullptr;  // 2x2 means of e0, e1, e2
+    float *y = nullptr;                                     // the head's output
     // backward buffers for up to bwd_pixels
     void *bblock = nullptr;
     long long bwd_pixels = 0;
@@ -46,14 +48,13 @@ struct twg_unet {
     unsigned int *counts = nullptr;  // FREE cells per image
     // small device words: [0] ring maximum, [1] non-finite network output flag
     unsigned int *words = nullptr;
-    // coarse output of a coarse-scale warm start (yc_pixels floats)
-    float *yc = nullptr;
-    long long yc_pixels = 0;
 };
 
 namespace twg {
 
-int net_forward(twg_unet *n, int nb, int H, int W, hipStream_t st);
+// y: the head's output per pixel, or null to keep the last activation d0
+// instead (training)
+int net_forward(twg_unet *n, int nb, int H, int W, float *y, hipStream_t st);
 int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const uint8_t *cls, float *loss,
                  hipStream_t st);
 int net_adam(twg_unet *n, float lr, hipStream_t st);
@@ -61,7 +62,6 @@ int net_params_in(twg_unet *n, const float *ext, hipStream_t st);
 int net_params_out(twg_unet *n, float *ext, hipStream_t st);
 int net_grads_out(twg_unet *n, float *ext, hipStream_t st);
 int net_pack_input(twg_unet *n, const float *x, long long total, hipStream_t st);
-int net_head_plain(twg_unet *n, float *y, int total, hipStream_t st);
 // the field of a warm start; a non-finite network output at a FREE cell
 // makes every FREE cell 0.5 instead, and *status (if given) receives
 // TWG_OK or TWG_NET_FALLBACK

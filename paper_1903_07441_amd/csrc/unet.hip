@@ -24,14 +24,9 @@
 // that layout.  The input-gradient pass uses a second copy with the taps
 // flipped and the channel roles swapped, [Cin][9][Cout].
 //
-// Conv as implicit GEMM on v_mfma_f32_16x16x32_bf16: D[cout][pixel] =
-// sum_k W[cout][k] * In[k][pixel].  A workgroup (4 waves) produces a 16 x 16
-// pixel tile for all output channels; the 18 x 18 input halo of a 32-channel
-// chunk is staged in LDS (pooling and upsample + concatenation are applied
-// while staging, so pooled and concatenated tensors are never stored), the
-// next chunk's global loads are in flight while the current one is
-// multiplied.  Each wave owns 4 output rows; a lane's accumulator holds four
-// consecutive output channels of one pixel, stored as one 8-byte bf16 vector.
+// The 3x3 convolutions (forward and input gradients) are in conv3.hip; the
+// first layer, with its three input channels, is here.  The layers that are
+// pooled write their 2x2 means next to their output.
 //
 // Weight gradient: dW[cout][tap][c] = sum_pixels dOut[p][cout] * In[p + tap][c]
 // with the reduction over pixels on the matrix cores: the output-gradient tile
@@ -40,7 +35,9 @@
 // reduction is split over workgroups; partial sums are added in a fixed order
 // by a second kernel, so gradients are deterministic.
 #include "twg_internal.h"
+#include "conv3.h"
 #include "unet.h"
+#include "unet_dev.h"
 
 #include <cmath>
 #include <cstring>
@@ -50,46 +47,11 @@ namespace twg {
 
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+using namespace ndev;
 
 int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE; }
 
-// ---- bf16 helpers -------------------------------------------------------
-// round to nearest even; NaN stays a quiet NaN.  Both results are formed
-// and one selected, so the conversion never branches.
-__device__ __forceinline__ uint32_t f2bf(float f)
-{
-    const uint32_t u = __float_as_uint(f);
-    const uint32_t rounded = (u + 0x7fffu + ((u >> 16) & 1u)) >> 16;
-    const uint32_t qnan = ((u >> 16) | 0x40u) & 0xffffu;
-    return (u & 0x7fffffffu) > 0x7f800000u ? qnan : rounded;
-}
-__device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) { return f2bf(lo) | (f2bf(hi) << 16); }
-// ReLU that keeps a NaN a NaN (the hardware max would turn it into 0), so a
-// broken parameter shows up in the network's output
-__device__ __forceinline__ float relu(float v) { return v != v ? v : fmaxf(v, 0.f); }
-__device__ __forceinline__ bool bf_pos(uint32_t h) { return (h & 0x8000u) == 0 && (h & 0x7fffu) != 0; }
-
-__device__ __forceinline__ bf16x8 as_bf8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
-
-__device__ __forceinline__ void unpack8(uint4 v, float *f)
-{
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = bf_lo(w[i]);
-        f[2 * i + 1] = bf_hi(w[i]);
-    }
-}
-__device__ __forceinline__ uint4 pack8(const float *f)
-{
-    return make_uint4(pack2(f[0], f[1]), pack2(f[2], f[3]), pack2(f[4], f[5]), pack2(f[6], f[7]));
-}
-
-constexpr int kPlain = 0, kPool = 1, kUpCat = 2, kIn4 = 3;
+constexpr int kIn4 = 2;  // (kPlain, kUpCat: conv3.h)
 
 constexpr int kTS = 16;       // output tile side
 constexpr int kHS = 18;       // halo side
@@ -101,7 +63,6 @@ constexpr int kVPT = (kNV + 255) / 256;
 // 8 channels [c, c + 8) of the conv input at pixel (yy, xx) of image b, at
 // the conv's own resolution H x W (in bounds).
 //   kPlain: A is [B][H][W][CIN].
-//   kPool:  A is [B][2H][2W][CIN]; the 2x2 mean, rounded to bf16.
 //   kUpCat: channels < CA from A = [B][H/2][W/2][CA] (nearest), the rest
 //           from Bs = [B][H][W][CIN - CA].
 //   kIn4:   A is the network input [B][H][W][4] (3 channels and a zero);
@@ -116,20 +77,6 @@ __device__ __forceinline__ uint4 gather8(const uint16_t *__restrict__ A, const u
         return make_uint4(v.x, v.y, 0, 0);
     } else if (MODE == kPlain) {
         return *reinterpret_cast<const uint4 *>(A + (((size_t)b * H + yy) * W + xx) * CIN + c);
-    } else if (MODE == kPool) {
-        const size_t W2 = 2 * (size_t)W;
-        const uint16_t *p = A + (((size_t)b * 2 * H + 2 * yy) * W2 + 2 * xx) * CIN + c;
-        float a[8], t[8];
-        unpack8(*reinterpret_cast<const uint4 *>(p), a);
-        unpack8(*reinterpret_cast<const uint4 *>(p + CIN), t);
-        float s0[8], s1[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s0[i] = a[i] + t[i];
-        unpack8(*reinterpret_cast<const uint4 *>(p + W2 * CIN), a);
-        unpack8(*reinterpret_cast<const uint4 *>(p + W2 * CIN + CIN), t);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) s1[i] = (s0[i] + (a[i] + t[i])) * 0.25f;
-        return pack8(s1);
     } else {
         // one load from whichever tensor holds channel c (no branch: the
         // channel group differs between lanes)
@@ -159,144 +106,6 @@ __device__ __forceinline__ uint4 halo8(const uint16_t *__restrict__ A, const uin
 }
 
 
-// ---- bf16 output tile ----------------------------------------------------
-// A lane's accumulators hold 4 consecutive output channels of one pixel,
-// 8 bytes, every 2 COUT bytes apart, so storing them directly writes every
-// output line in pieces.  Instead each wave puts its 4 rows x 16 pixels of
-// bf16(relu(acc + bias)) into LDS (a slice of at most 64 channels at a time)
-// and writes them back as 16-byte runs of consecutive channels.  stg must
-// hold 4 x 64 x (min(COB, 64) + 8) bf16; all threads of the workgroup call
-// this together (it synchronises).
-template <int COUT, int COB>
-__device__ __forceinline__ void store_tile(const f32x4 (&acc)[4][COB / 16], const float *__restrict__ bias,
-                                           uint16_t *__restrict__ out, uint16_t *stg_all, int b, int co0, int x0,
-                                           int y0, int H, int W)
-{
-    constexpr int CS = COB < 64 ? COB : 64, NS = COB / CS, RTS = CS / 16, PSO = CS + 8;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 15, g = lane >> 4;
-    uint16_t *stg = stg_all + wave * 64 * PSO;
-#pragma unroll
-    for (int sl = 0; sl < NS; ++sl) {
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-            for (int q = 0; q < RTS; ++q) {
-                const int rt = sl * RTS + q, o = co0 + rt * 16 + g * 4;
-                const f32x4 v = acc[ct][rt];
-                const float r0 = relu(v[0] + bias[o]), r1 = relu(v[1] + bias[o + 1]);
-                const float r2 = relu(v[2] + bias[o + 2]), r3 = relu(v[3] + bias[o + 3]);
-                *reinterpret_cast<uint2 *>(&stg[(ct * 16 + j) * PSO + q * 16 + g * 4]) =
-                    make_uint2(pack2(r0, r1), pack2(r2, r3));
-            }
-        __syncthreads();
-#pragma unroll
-        for (int q = lane; q < 64 * (CS / 8); q += 64) {
-            const int p = q / (CS / 8), c8 = q - p * (CS / 8);
-            const int y = y0 + wave * 4 + (p >> 4), x = x0 + (p & 15);
-            const uint4 v = *reinterpret_cast<const uint4 *>(&stg[p * PSO + c8 * 8]);
-            if (y < H && x < W)
-                *reinterpret_cast<uint4 *>(out + (((size_t)b * H + y) * W + x) * COUT + co0 + sl * CS + c8 * 8) = v;
-        }
-        __syncthreads();
-    }
-}
-
-// ---- forward conv (and input gradient with OUT_F32) ----------------------
-// grid (ceil(W/16), ceil(H/16), B * max(1, COUT / 128)), 256 threads (a
-// workgroup computes at most 128 output channels).  OUT_F32: FP32 output, no
-// bias, no ReLU (input gradients); else bf16(relu(acc + bias)).
-template <int CIN, int COUT, int MODE, int CA, bool OUT_F32>
-__global__ __launch_bounds__(256) void k_conv3(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bs,
-                                               const uint16_t *__restrict__ wt,
-                                               const float *__restrict__ bias, void *__restrict__ out, int H,
-                                               int W)
-{
-    // at most 128 output channels per workgroup (accumulator registers)
-    constexpr int COB = COUT < 128 ? COUT : 128, NCO = COUT / COB;
-    constexpr int NCH = CIN / kCK, RT = COB / 16;
-    __shared__ __align__(16) uint16_t lds[2][kHS * kHS * kPS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 15, g = lane >> 4;
-    const int b = blockIdx.z / NCO, co0 = (blockIdx.z % NCO) * COB;
-    const int x0 = blockIdx.x * kTS, y0 = blockIdx.y * kTS;
-
-    uint4 st[kVPT];
-    auto fetch = [&](int ch) {
-#pragma unroll
-        for (int r = 0; r < kVPT; ++r) st[r] = halo8<MODE, CIN, CA>(A, Bs, b, tid + 256 * r, x0, y0, ch, H, W);
-    };
-    auto commit = [&](int buf) {
-#pragma unroll
-        for (int r = 0; r < kVPT; ++r) {
-            const int v = tid + 256 * r;
-            if (v < kNV) *reinterpret_cast<uint4 *>(&lds[buf][(v >> 2) * kPS + (v & 3) * 8]) = st[r];
-        }
-    };
-
-    f32x4 acc[4][RT];
-#pragma unroll
-    for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt) acc[ct][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    fetch(0);
-    commit(0);
-    __syncthreads();
-    for (int ch = 0; ch < NCH; ++ch) {
-        const int buf = ch & 1;
-        if (ch + 1 < NCH) fetch(ch + 1);
-        const uint16_t *wrow = wt + (size_t)(co0 + j) * 9 * CIN + ch * kCK + g * 8;
-        uint4 a_next[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; ++rt)
-            a_next[rt] = *reinterpret_cast<const uint4 *>(wrow + (size_t)rt * 16 * 9 * CIN);
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap) {
-            const int dy = tap / 3, dx = tap % 3;
-            uint4 a[RT];
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) a[rt] = a_next[rt];
-            if (tap + 1 < 9) {
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    a_next[rt] = *reinterpret_cast<const uint4 *>(wrow + (size_t)rt * 16 * 9 * CIN + (tap + 1) * CIN);
-            }
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct) {
-                const int row = wave * 4 + ct;
-                const uint4 bv =
-                    *reinterpret_cast<const uint4 *>(&lds[buf][((row + dy) * kHS + j + dx) * kPS + g * 8]);
-#pragma unroll
-                for (int rt = 0; rt < RT; ++rt)
-                    acc[ct][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(a[rt]), as_bf8(bv), acc[ct][rt], 0, 0, 0);
-            }
-        }
-        if (ch + 1 < NCH) commit(buf ^ 1);
-        __syncthreads();
-    }
-
-    if (OUT_F32) {
-        const int x = x0 + j;
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct) {
-            const int y = y0 + wave * 4 + ct;
-            if (y >= H || x >= W) continue;
-            const size_t pix = ((size_t)b * H + y) * W + x;
-#pragma unroll
-            for (int rt = 0; rt < RT; ++rt) {
-                const int o = co0 + rt * 16 + g * 4;
-                const f32x4 v = acc[ct][rt];
-                *reinterpret_cast<float4 *>(static_cast<float *>(out) + pix * COUT + o) =
-                    make_float4(v[0], v[1], v[2], v[3]);
-            }
-        }
-    } else {
-        // the halo buffers are free after the loop's last barrier
-        store_tile<COUT, COB>(acc, bias, static_cast<uint16_t *>(out), &lds[0][0], b, co0, x0, y0, H, W);
-    }
-}
-
 // ---- first layer ---------------------------------------------------------
 // The input has 3 real channels, so one K = 32 slice of the implicit GEMM
 // covers all nine taps (k = 3 tap + c; k >= 27 is zero) and a 16-pixel row
@@ -309,8 +118,8 @@ __global__ __launch_bounds__(256) void k_conv3(const uint16_t *__restrict__ A, c
 // every tile would queue on the cache channels that hold them.
 // out = bf16(relu(acc + bias)), [B][H][W][32].
 __global__ __launch_bounds__(256) void k_conv3_in(const uint16_t *__restrict__ x4, const uint16_t *__restrict__ wt,
-                                                  const float *__restrict__ bias, uint16_t *__restrict__ out, int nb,
-                                                  int H, int W)
+                                                  const float *__restrict__ bias, uint16_t *__restrict__ out,
+                                                  uint16_t *__restrict__ pool, int nb, int H, int W)
 {
     constexpr int COUT = 32, RT = 2, ZERO = kHS * kHS * 4;  // lds[ZERO..ZERO + 3] stay zero
     __shared__ __align__(16) uint16_t lds[kHS * kHS * 4 + 4];
@@ -345,6 +154,11 @@ __global__ __launch_bounds__(256) void k_conv3_in(const uint16_t *__restrict__ x
             a[rt][h] = w2[0] | (w2[1] << 16);
         }
     if (tid == 0) *reinterpret_cast<uint2 *>(&lds[ZERO]) = make_uint2(0, 0);
+    float bs[RT][4];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) bs[rt][v] = bias[rt * 16 + g * 4 + v];
 
     for (int t = blockIdx.x; t < ntile; t += gridDim.x) {
         const int b = t / (tx * ty), r = t - b * (tx * ty);
@@ -377,9 +191,40 @@ __global__ __launch_bounds__(256) void k_conv3_in(const uint16_t *__restrict__ x
                     as_bf8(make_uint4(a[rt][0], a[rt][1], a[rt][2], a[rt][3])), as_bf8(bv),
                     f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
         }
-        // store_tile synchronises before and after its LDS round trip, so
-        // the halo is free for the next tile when it returns
-        store_tile<COUT, COUT>(acc, bias, out, stg, b, 0, x0, y0, H, W);
+        // A lane's accumulators hold 4 consecutive channels of one pixel:
+        // each wave puts its 4 rows of bf16(relu(acc + bias)) into its part
+        // of LDS and writes 16-byte runs of channels, and the 2x2 means
+        // (two rows of eight pixels, one 16-byte run a lane)
+        uint16_t *sw = stg + wave * 64 * (COUT + 8);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int ct = 0; ct < 4; ++ct) {
+                const f32x4 v = acc[ct][rt];
+                *reinterpret_cast<uint2 *>(sw + (ct * 16 + j) * (COUT + 8) + rt * 16 + g * 4) =
+                    make_uint2(pack2(relu(v[0] + bs[rt][0]), relu(v[1] + bs[rt][1])),
+                               pack2(relu(v[2] + bs[rt][2]), relu(v[3] + bs[rt][3])));
+            }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int p = i * 16 + (lane >> 2), c8 = lane & 3;
+            const int y = y0 + wave * 4 + (p >> 4), x = x0 + (p & 15);
+            const uint4 v = *reinterpret_cast<const uint4 *>(sw + p * (COUT + 8) + c8 * 8);
+            if (y < H && x < W) *reinterpret_cast<uint4 *>(out + (((size_t)b * H + y) * W + x) * COUT + c8 * 8) = v;
+        }
+        {
+            const int p = lane >> 2, c8 = lane & 3, y = y0 / 2 + wave * 2 + (p >> 3), x = x0 / 2 + (p & 7);
+            const uint16_t *q = sw + ((p >> 3) * 32 + (p & 7) * 2) * (COUT + 8) + c8 * 8;
+            const uint4 v = mean4(*reinterpret_cast<const uint4 *>(q), *reinterpret_cast<const uint4 *>(q + COUT + 8),
+                                  *reinterpret_cast<const uint4 *>(q + 16 * (COUT + 8)),
+                                  *reinterpret_cast<const uint4 *>(q + 17 * (COUT + 8)));
+            if (y < H / 2 && x < W / 2)
+                *reinterpret_cast<uint4 *>(pool + (((size_t)b * (H / 2) + y) * (W / 2) + x) * COUT + c8 * 8) = v;
+        }
+        // the next tile's halo overwrites what every wave has read above
+        // (its products precede the barrier), and its staging follows the
+        // next barrier
     }
 }
 
@@ -510,18 +355,6 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
-// y = hb + sum_c hw[c] d0[c] for every pixel (FP32, channel order).
-__device__ __forceinline__ float head_value(const uint16_t *__restrict__ d0p, const float *__restrict__ hw,
-                                            float hb, float *d)
-{
-#pragma unroll
-    for (int q = 0; q < 4; ++q) unpack8(reinterpret_cast<const uint4 *>(d0p)[q], d + 8 * q);
-    float y = hb;
-#pragma unroll
-    for (int c = 0; c < 32; ++c) y = y + hw[c] * d[c];
-    return y;
-}
-
 // Training head: masked MSE over FREE cells.  Per pixel: y, diff = y - t
 // (0 outside the mask), loss += diff^2 / (n_b B), dy = 2 diff / (n_b B),
 // dd0 = bf16(dy * hw * [d0 > 0]); block partial sums of the head gradients
@@ -542,7 +375,10 @@ __global__ __launch_bounds__(256) void k_head_loss(const uint16_t *__restrict__ 
     if (p < total) {
         const int b = p / hw_pixels;
         float d[32];
-        const float y = head_value(d0 + (size_t)p * 32, hw, hb[0], d);
+        uint4 v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = reinterpret_cast<const uint4 *>(d0 + (size_t)p * 32)[q];
+        const float y = head_value(v, hw, hb[0], d);
         if (y_out) y_out[p] = y;
         const float diff = cls[p] == TWG_CELL_FREE ? y - target[p] : 0.f;
         const unsigned int nf = cnt[b];
@@ -584,8 +420,7 @@ __global__ __launch_bounds__(256) void k_head_loss(const uint16_t *__restrict__ 
 // Hp x Wp frame; only the grid's nx x ny cells are written.
 // A non-finite output at a FREE cell sets *bad (the whole field then falls
 // back to the plain start, k_net_fallback).
-__global__ __launch_bounds__(256) void k_head_psi(const uint16_t *__restrict__ d0, const float *__restrict__ hw,
-                                                  const float *__restrict__ hb, const uint8_t *__restrict__ cls,
+__global__ __launch_bounds__(256) void k_head_psi(const float *__restrict__ yv, const uint8_t *__restrict__ cls,
                                                   float *__restrict__ psi, int nx, int ny, int pitch, int Wp,
                                                   unsigned int *bad)
 {
@@ -595,8 +430,7 @@ __global__ __launch_bounds__(256) void k_head_psi(const uint16_t *__restrict__ d
     const size_t i = (size_t)y * pitch + x;
     const uint8_t c = cls[i];
     if (c == TWG_CELL_FREE) {
-        float d[32];
-        const float v = head_value(d0 + ((size_t)y * Wp + x) * 32, hw, hb[0], d);
+        const float v = yv[(size_t)y * Wp + x];
         if (!isfinite(v)) atomicOr(bad, 1u);
         psi[i] = fminf(fmaxf(v, 0.f), 1.f);
     } else if (c == TWG_CELL_OBST || c == TWG_CELL_WALL) {
@@ -629,16 +463,6 @@ __global__ __launch_bounds__(256) void k_net_fallback(const uint8_t *__restrict_
 __global__ void k_zero_words(unsigned int *w, int n)
 {
     if (blockIdx.x == 0 && (int)threadIdx.x < n) w[threadIdx.x] = 0u;
-}
-
-// Plain head output y[p] (no field semantics).
-__global__ __launch_bounds__(256) void k_head_plain(const uint16_t *__restrict__ d0, const float *__restrict__ hw,
-                                                    const float *__restrict__ hb, float *__restrict__ y, int total)
-{
-    const int p = blockIdx.x * 256 + threadIdx.x;
-    if (p >= total) return;
-    float d[32];
-    y[p] = head_value(d0 + (size_t)p * 32, hw, hb[0], d);
 }
 
 // Gradient through up() into a low-resolution activation:
@@ -922,7 +746,7 @@ __device__ __forceinline__ ParamPos locate(const NetLayout &L, int i)
 __device__ __forceinline__ void store_copies(const NetLayout &L, const ParamPos &pp, float v,
                                              uint16_t *__restrict__ wt, uint16_t *__restrict__ wf, int i)
 {
-    const uint16_t h = (uint16_t)f2bf(v);
+    const uint16_t h = (uint16_t)(pack2(v, 0.f) & 0xffffu);
     wt[i] = h;
     if (L.k[pp.layer] == 3)
         wf[L.offw[pp.layer] + ((size_t)pp.c * 9 + (8 - pp.tap)) * L.cout[pp.layer] + pp.o] = h;
@@ -1029,15 +853,6 @@ __global__ __launch_bounds__(256) void k_sum_loss(const float *__restrict__ part
 }
 
 // ---- launch helpers -----------------------------------------------------------
-template <int CIN, int COUT, int MODE, int CA, bool F32>
-int conv(const uint16_t *A, const uint16_t *Bs, const uint16_t *wt, const float *bias, void *out, int nb, int H,
-         int W, hipStream_t st)
-{
-    const dim3 grid((W + kTS - 1) / kTS, (H + kTS - 1) / kTS, nb * (COUT > 128 ? COUT / 128 : 1));
-    hipLaunchKernelGGL((k_conv3<CIN, COUT, MODE, CA, F32>), grid, dim3(256), 0, st, A, Bs, wt, bias, out, H, W);
-    return last_status();
-}
-
 int choose_split(int nchunk, int ntile)
 {
     int s = std::max(1, 256 / nchunk);
@@ -1107,26 +922,30 @@ NetLayout net_layout()
     return L;
 }
 
-int net_forward(twg_unet *n, int nb, int H, int W, hipStream_t st)
+int net_forward(twg_unet *n, int nb, int H, int W, float *y, hipStream_t st)
 {
     const NetLayout &L = n->L;
-    const uint16_t *wt = n->wt;
-    const float *mb = n->master;
-    auto W_ = [&](int l) { return wt + L.offw[l]; };
-    auto B_ = [&](int l) { return mb + L.offb[l]; };
+    const int cu = n->ctx->num_cu;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
+    auto args = [&](int l, const uint16_t *A, const uint16_t *Bs, uint16_t *out, uint16_t *pool, int h, int w) {
+        return ConvArgs{A, Bs, n->wt + L.offw[l], n->master + L.offb[l], out, pool, n->master + L.offw[7],
+                        n->master + L.offb[7], y, nb, h, w};
+    };
     {
         const long long ntile = (long long)nb * ((W + kTS - 1) / kTS) * ((H + kTS - 1) / kTS);
         const int grid = (int)std::max<long long>(1, std::min<long long>(ntile, 2048));
-        hipLaunchKernelGGL(k_conv3_in, dim3(grid), dim3(256), 0, st, n->xp, W_(0), B_(0), n->e0, nb, H, W);
+        hipLaunchKernelGGL(k_conv3_in, dim3(grid), dim3(256), 0, st, n->xp, n->wt + L.offw[0], n->master + L.offb[0],
+                           n->e0, n->p0, nb, H, W);
     }
     int rc = last_status();
-    if (!rc) rc = conv<32, 64, kPool, 0, false>(n->e0, nullptr, W_(1), B_(1), n->e1, nb, H1, W1, st);
-    if (!rc) rc = conv<64, 128, kPool, 0, false>(n->e1, nullptr, W_(2), B_(2), n->e2, nb, H2, W2, st);
-    if (!rc) rc = conv<128, 128, kPool, 0, false>(n->e2, nullptr, W_(3), B_(3), n->e3, nb, H3, W3, st);
-    if (!rc) rc = conv<256, 64, kUpCat, 128, false>(n->e3, n->e2, W_(4), B_(4), n->d2, nb, H2, W2, st);
-    if (!rc) rc = conv<128, 32, kUpCat, 64, false>(n->d2, n->e1, W_(5), B_(5), n->d1, nb, H1, W1, st);
-    if (!rc) rc = conv<64, 32, kUpCat, 32, false>(n->d1, n->e0, W_(6), B_(6), n->d0, nb, H, W, st);
+    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutPool>(args(1, n->p0, nullptr, n->e1, n->p1, H1, W1), cu, st);
+    if (!rc) rc = launch_conv3<64, 128, kPlain, 0, kOutPool>(args(2, n->p1, nullptr, n->e2, n->p2, H2, W2), cu, st);
+    if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutAct>(args(3, n->p2, nullptr, n->e3, nullptr, H3, W3), cu, st);
+    if (!rc) rc = launch_conv3<256, 64, kUpCat, 128, kOutAct>(args(4, n->e3, n->e2, n->d2, nullptr, H2, W2), cu, st);
+    if (!rc) rc = launch_conv3<128, 32, kUpCat, 64, kOutAct>(args(5, n->d2, n->e1, n->d1, nullptr, H1, W1), cu, st);
+    const ConvArgs last = args(6, n->d1, n->e0, n->d0, nullptr, H, W);
+    if (!rc) rc = y ? launch_conv3<64, 32, kUpCat, 32, kOutHead>(last, cu, st)
+                    : launch_conv3<64, 32, kUpCat, 32, kOutAct>(last, cu, st);
     return rc;
 }
 
@@ -1135,7 +954,9 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
 {
     const NetLayout &L = n->L;
     const uint16_t *wf = n->wf;
-    auto F_ = [&](int l) { return wf + L.offw[l]; };
+    auto grad_args = [&](const uint16_t *g, int l, float *out, int h, int w) {
+        return ConvArgs{g, nullptr, wf + L.offw[l], nullptr, out, nullptr, nullptr, nullptr, nullptr, nb, h, w};
+    };
     auto GW = [&](int l) { return n->grad + L.offw[l]; };
     auto GB = [&](int l) { return n->grad + L.offb[l]; };
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
@@ -1152,27 +973,27 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     int rc = last_status();
     // d0: input cat(up(d1), e0) at H
     if (!rc) rc = wgrad<64, 32, kUpCat, 32>(n->d1, n->e0, n->g_d0, n->part, n->bpart, GW(6), GB(6), nb, H, W, st);
-    if (!rc) rc = conv<32, 64, kPlain, 0, true>(n->g_d0, nullptr, F_(6), nullptr, n->f_c0, nb, H, W, st);
+    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutF32>(grad_args(n->g_d0, 6, n->f_c0, H, W), n->ctx->num_cu, st);
     if (!rc) rc = route_up<32, 64>(n->f_c0, n->d1, n->g_d1, nb, H1, W1, st);
     // d1: input cat(up(d2), e1) at H/2
     if (!rc) rc = wgrad<128, 32, kUpCat, 64>(n->d2, n->e1, n->g_d1, n->part, n->bpart, GW(5), GB(5), nb, H1, W1, st);
-    if (!rc) rc = conv<32, 128, kPlain, 0, true>(n->g_d1, nullptr, F_(5), nullptr, n->f_c1, nb, H1, W1, st);
+    if (!rc) rc = launch_conv3<32, 128, kPlain, 0, kOutF32>(grad_args(n->g_d1, 5, n->f_c1, H1, W1), n->ctx->num_cu, st);
     if (!rc) rc = route_up<64, 128>(n->f_c1, n->d2, n->g_d2, nb, H2, W2, st);
     // d2: input cat(up(e3), e2) at H/4
     if (!rc) rc = wgrad<256, 64, kUpCat, 128>(n->e3, n->e2, n->g_d2, n->part, n->bpart, GW(4), GB(4), nb, H2, W2, st);
-    if (!rc) rc = conv<64, 256, kPlain, 0, true>(n->g_d2, nullptr, F_(4), nullptr, n->f_c2, nb, H2, W2, st);
+    if (!rc) rc = launch_conv3<64, 256, kPlain, 0, kOutF32>(grad_args(n->g_d2, 4, n->f_c2, H2, W2), n->ctx->num_cu, st);
     if (!rc) rc = route_up<128, 256>(n->f_c2, n->e3, n->g_e3, nb, H3, W3, st);
     // e3: input pool(e2) at H/8
-    if (!rc) rc = wgrad<128, 128, kPool, 0>(n->e2, nullptr, n->g_e3, n->part, n->bpart, GW(3), GB(3), nb, H3, W3, st);
-    if (!rc) rc = conv<128, 128, kPlain, 0, true>(n->g_e3, nullptr, F_(3), nullptr, n->f_p2, nb, H3, W3, st);
+    if (!rc) rc = wgrad<128, 128, kPlain, 0>(n->p2, nullptr, n->g_e3, n->part, n->bpart, GW(3), GB(3), nb, H3, W3, st);
+    if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutF32>(grad_args(n->g_e3, 3, n->f_p2, H3, W3), n->ctx->num_cu, st);
     if (!rc) rc = route_pool<128, 128, 256>(n->f_c2, n->f_p2, n->e2, n->g_e2, nb, H2, W2, st);
     // e2: input pool(e1) at H/4
-    if (!rc) rc = wgrad<64, 128, kPool, 0>(n->e1, nullptr, n->g_e2, n->part, n->bpart, GW(2), GB(2), nb, H2, W2, st);
-    if (!rc) rc = conv<128, 64, kPlain, 0, true>(n->g_e2, nullptr, F_(2), nullptr, n->f_p1, nb, H2, W2, st);
+    if (!rc) rc = wgrad<64, 128, kPlain, 0>(n->p1, nullptr, n->g_e2, n->part, n->bpart, GW(2), GB(2), nb, H2, W2, st);
+    if (!rc) rc = launch_conv3<128, 64, kPlain, 0, kOutF32>(grad_args(n->g_e2, 2, n->f_p1, H2, W2), n->ctx->num_cu, st);
     if (!rc) rc = route_pool<64, 64, 128>(n->f_c1, n->f_p1, n->e1, n->g_e1, nb, H1, W1, st);
     // e1: input pool(e0) at H/2
-    if (!rc) rc = wgrad<32, 64, kPool, 0>(n->e0, nullptr, n->g_e1, n->part, n->bpart, GW(1), GB(1), nb, H1, W1, st);
-    if (!rc) rc = conv<64, 32, kPlain, 0, true>(n->g_e1, nullptr, F_(1), nullptr, n->f_p0, nb, H1, W1, st);
+    if (!rc) rc = wgrad<32, 64, kPlain, 0>(n->p0, nullptr, n->g_e1, n->part, n->bpart, GW(1), GB(1), nb, H1, W1, st);
+    if (!rc) rc = launch_conv3<64, 32, kPlain, 0, kOutF32>(grad_args(n->g_e1, 1, n->f_p0, H1, W1), n->ctx->num_cu, st);
     if (!rc) rc = route_pool<32, 32, 64>(n->f_c0, n->f_p0, n->e0, n->g_e0, nb, H, W, st);
     // e0: input x (padded to 32 channels)
     if (!rc) rc = wgrad<32, 32, kIn4, 0>(n->xp, nullptr, n->g_e0, n->part, n->bpart, GW(0), GB(0), nb, H, W, st);
@@ -1215,19 +1036,11 @@ int net_pack_input(twg_unet *n, const float *x, long long total, hipStream_t st)
     return last_status();
 }
 
-int net_head_plain(twg_unet *n, float *y, int total, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_head_plain, dim3((total + 255) / 256), dim3(256), 0, st, n->d0, n->master + n->L.offw[7],
-                       n->master + n->L.offb[7], y, total);
-    return last_status();
-}
-
 int net_head_psi(twg_unet *n, const uint8_t *cls, float *psi, int nx, int ny, int pitch, int Wp, int32_t *status,
                  hipStream_t st)
 {
     const dim3 grid((nx + 63) / 64, (ny + 3) / 4);
-    hipLaunchKernelGGL(k_head_psi, grid, dim3(256), 0, st, n->d0, n->master + n->L.offw[7],
-                       n->master + n->L.offb[7], cls, psi, nx, ny, pitch, Wp, n->words + 1);
+    hipLaunchKernelGGL(k_head_psi, grid, dim3(256), 0, st, n->y, cls, psi, nx, ny, pitch, Wp, n->words + 1);
     hipLaunchKernelGGL(k_net_fallback, grid, dim3(256), 0, st, cls, psi, nx, ny, pitch, n->words + 1, status);
     return last_status();
 }

@@ -26,8 +26,9 @@ int ensure_fwd(twg_unet *n, long long P)
         n->fwd_pixels = 0;
     }
     const size_t s32 = al((size_t)P * 32 * 2), s4 = al((size_t)P * 4 * 2), s1 = al((size_t)P / 4 * 2),
-                 s2 = al((size_t)P / 16 * 2), s3 = al((size_t)P / 64 * 2);
-    const size_t bytes = s4 + 2 * s32 + 64 * s1 + 32 * s1 + 128 * s2 + 64 * s2 + 128 * s3;
+                 s2 = al((size_t)P / 16 * 2), s3 = al((size_t)P / 64 * 2), sy = al((size_t)P * 4);
+    const size_t bytes = s4 + 2 * s32 + 64 * s1 + 32 * s1 + 128 * s2 + 64 * s2 + 128 * s3 + 32 * s1 + 64 * s2 +
+                         128 * s3 + sy;
     if (hipMalloc(&n->fblock, bytes) != hipSuccess) {
         n->fblock = nullptr;
         return set_err(n->ctx, TWG_ENOMEM, "network activation allocation failed");
@@ -42,6 +43,10 @@ int ensure_fwd(twg_unet *n, long long P)
     n->e2 = take(128 * s2);
     n->d2 = take(64 * s2);
     n->e3 = take(128 * s3);
+    n->p0 = take(32 * s1);
+    n->p1 = take(64 * s2);
+    n->p2 = take(128 * s3);
+    n->y = reinterpret_cast<float *>(take(sy));
     n->fwd_pixels = P;
     return TWG_OK;
 }
@@ -148,7 +153,6 @@ int32_t twg_unet_destroy(twg_unet *n)
     if (n->pblock) hipFree(n->pblock);
     if (n->fblock) hipFree(n->fblock);
     if (n->bblock) hipFree(n->bblock);
-    if (n->yc) hipFree(n->yc);
     delete n;
     return TWG_OK;
 }
@@ -193,8 +197,7 @@ int32_t twg_unet_forward(twg_unet *n, int32_t batch, int32_t H, int32_t W, const
     const long long P = (long long)batch * H * W;
     rc = ensure_fwd(n, P);
     if (!rc) rc = net_pack_input(n, x, P, st);
-    if (!rc) rc = net_forward(n, batch, H, W, st);
-    if (!rc) rc = net_head_plain(n, y, (int)P, st);
+    if (!rc) rc = net_forward(n, batch, H, W, y, st);
     return rc ? set_err(n->ctx, rc, n->ctx->err.empty() ? "network forward failed" : n->ctx->err) : TWG_OK;
 }
 
@@ -213,7 +216,7 @@ int32_t twg_unet_loss_grad(twg_unet *n, int32_t batch, int32_t H, int32_t W, con
     rc = ensure_fwd(n, P);
     if (!rc) rc = ensure_bwd(n, P);
     if (!rc) rc = net_pack_input(n, x, P, st);
-    if (!rc) rc = net_forward(n, batch, H, W, st);
+    if (!rc) rc = net_forward(n, batch, H, W, nullptr, st);
     if (!rc) rc = net_backward(n, batch, H, W, target, cls, loss, st);
     if (!rc && grads) rc = net_grads_out(n, grads, st);
     return rc ? set_err(n->ctx, rc, n->ctx->err.empty() ? "network backward failed" : n->ctx->err) : TWG_OK;
@@ -265,7 +268,7 @@ int32_t twg_unet_warm_start(twg_unet *n, twg_grid g, const uint8_t *cls, const u
     rc = net_zero_words(n, 2, st);
     if (!rc && ring) rc = net_ring_max(ring, g.nx, g.ny, g.pitch, n->words, st);
     if (!rc) rc = net_features(cls, ring, g.nx, g.ny, g.pitch, H, W, goal_x, goal_y, n->words, nullptr, n->xp, st);
-    if (!rc) rc = net_forward(n, 1, H, W, st);
+    if (!rc) rc = net_forward(n, 1, H, W, n->y, st);
     if (!rc) rc = net_head_psi(n, cls, psi, g.nx, g.ny, g.pitch, W, status, st);
     return rc ? set_err(n->ctx, rc, "warm start failed") : TWG_OK;
 }
@@ -348,26 +351,12 @@ int32_t twg_unet_warm_start_coarse(twg_unet *n, twg_grid g, const uint8_t *cls, 
     const long long P = (long long)Hc * Wc;
     rc = ensure_fwd(n, P);
     if (rc) return rc;
-    if (P > n->yc_pixels) {
-        if (n->yc) {
-            hipDeviceSynchronize();
-            hipFree(n->yc);
-            n->yc = nullptr;
-            n->yc_pixels = 0;
-        }
-        if (hipMalloc(&n->yc, (size_t)P * sizeof(float)) != hipSuccess) {
-            n->yc = nullptr;
-            return set_err(n->ctx, TWG_ENOMEM, "coarse output allocation failed");
-        }
-        n->yc_pixels = P;
-    }
     rc = net_zero_words(n, 2, st);
     if (!rc && ring) rc = net_ring_max(ring, g.nx, g.ny, g.pitch, n->words, st);
     if (!rc) rc = net_features_coarse(cls, ring, g.nx, g.ny, g.pitch, factor, Hc, Wc, goal_x, goal_y, n->words,
                                       nullptr, n->xp, nullptr, st);
-    if (!rc) rc = net_forward(n, 1, Hc, Wc, st);
-    if (!rc) rc = net_head_plain(n, n->yc, (int)P, st);
-    if (!rc) rc = net_up_psi(n, n->yc, Hc, Wc, factor, cls, psi, g.nx, g.ny, g.pitch, status, st);
+    if (!rc) rc = net_forward(n, 1, Hc, Wc, n->y, st);
+    if (!rc) rc = net_up_psi(n, n->y, Hc, Wc, factor, cls, psi, g.nx, g.ny, g.pitch, status, st);
     return rc ? set_err(n->ctx, rc, "coarse warm start failed") : TWG_OK;
 }
 
