@@ -28,16 +28,12 @@
 // first layer, with its three input channels, is here.  The layers that are
 // pooled write their 2x2 means next to their output.
 //
-// Weight gradient: dW[cout][tap][c] = sum_pixels dOut[p][cout] * In[p + tap][c]
-// with the reduction over pixels on the matrix cores: the output-gradient tile
-// is staged transposed ([cout][pixel]) and the input halo as three copies
-// shifted by dx, so every operand is one aligned 16-byte LDS read.  The pixel
-// reduction is split over workgroups; partial sums are added in a fixed order
-// by a second kernel, so gradients are deterministic.
+// Weight gradients are in wgrad3.hip.
 #include "twg_internal.h"
 #include "conv3.h"
 #include "unet.h"
 #include "unet_dev.h"
+#include "wgrad3.h"
 
 #include <cmath>
 #include <cstring>
@@ -51,60 +47,8 @@ using namespace ndev;
 
 int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE; }
 
-constexpr int kIn4 = 2;  // (kPlain, kUpCat: conv3.h)
-
-constexpr int kTS = 16;       // output tile side
+constexpr int kTS = 16;       // tile side of the first layer
 constexpr int kHS = 18;       // halo side
-constexpr int kCK = 32;       // input channels per chunk
-constexpr int kPS = kCK + 8;  // LDS pixel stride (bf16), padded against bank conflicts
-constexpr int kNV = kHS * kHS * (kCK / 8);
-constexpr int kVPT = (kNV + 255) / 256;
-
-// 8 channels [c, c + 8) of the conv input at pixel (yy, xx) of image b, at
-// the conv's own resolution H x W (in bounds).
-//   kPlain: A is [B][H][W][CIN].
-//   kUpCat: channels < CA from A = [B][H/2][W/2][CA] (nearest), the rest
-//           from Bs = [B][H][W][CIN - CA].
-//   kIn4:   A is the network input [B][H][W][4] (3 channels and a zero);
-//           channels from 4 on read as zero.
-template <int MODE, int CIN, int CA>
-__device__ __forceinline__ uint4 gather8(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bs,
-                                         int b, int yy, int xx, int c, int H, int W)
-{
-    if (MODE == kIn4) {
-        if (c != 0) return make_uint4(0, 0, 0, 0);
-        const uint2 v = *reinterpret_cast<const uint2 *>(A + (((size_t)b * H + yy) * W + xx) * 4);
-        return make_uint4(v.x, v.y, 0, 0);
-    } else if (MODE == kPlain) {
-        return *reinterpret_cast<const uint4 *>(A + (((size_t)b * H + yy) * W + xx) * CIN + c);
-    } else {
-        // one load from whichever tensor holds channel c (no branch: the
-        // channel group differs between lanes)
-        const uint16_t *p = c < CA ? A + (((size_t)b * (H / 2) + yy / 2) * (W / 2) + xx / 2) * CA + c
-                                   : Bs + (((size_t)b * H + yy) * W + xx) * (CIN - CA) + (c - CA);
-        return *reinterpret_cast<const uint4 *>(p);
-    }
-}
-
-// Halo element v (pixel v / 4 of the 18 x 18 halo of the tile at (x0, y0),
-// channel group v % 4) of input chunk ch.  The load is unconditional: an
-// element outside the halo or the image reads a clamped in-bounds pixel and
-// is replaced by zero, so a wave issues all its halo loads back to back
-// instead of waiting for each one inside a divergent branch.
-template <int MODE, int CIN, int CA>
-__device__ __forceinline__ uint4 halo8(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bs, int b,
-                                       int v, int x0, int y0, int ch, int H, int W)
-{
-    const int vc = v < kNV ? v : 0;
-    const int hp = vc >> 2, cg = vc & 3;
-    const int hy = hp / kHS, hx = hp - hy * kHS;
-    const int yy = y0 + hy - 1, xx = x0 + hx - 1;
-    const bool in = v < kNV && yy >= 0 && yy < H && xx >= 0 && xx < W;
-    const uint4 val = gather8<MODE, CIN, CA>(A, Bs, b, min(max(yy, 0), H - 1), min(max(xx, 0), W - 1),
-                                             ch * kCK + cg * 8, H, W);
-    return in ? val : make_uint4(0, 0, 0, 0);
-}
-
 
 // ---- first layer ---------------------------------------------------------
 // The input has 3 real channels, so one K = 32 slice of the implicit GEMM
@@ -226,126 +170,6 @@ __global__ __launch_bounds__(256) void k_conv3_in(const uint16_t *__restrict__ x
         // (its products precede the barrier), and its staging follows the
         // next barrier
     }
-}
-
-// ---- weight gradient -----------------------------------------------------
-constexpr int kOS = 256 + 8;              // LDS stride of one output channel's pixel row
-constexpr int kIS = kHS * kTS + 8;        // LDS stride of one input channel (18 rows x 16)
-
-// grid (CIN / 32, nsplit), 256 threads.  Workgroup (chunk, split) adds up
-// the pixel tiles split, split + nsplit, ... of all images and writes
-// part[split][cout][tap][chunk * 32 + c]; chunk 0 also writes the bias
-// gradient's partial sums bpart[split][cout].
-template <int CIN, int COUT, int MODE, int CA>
-__global__ __launch_bounds__(256) void k_wgrad3(const uint16_t *__restrict__ A, const uint16_t *__restrict__ Bs,
-                                                const uint16_t *__restrict__ dout, float *__restrict__ part,
-                                                float *__restrict__ bpart, int nb, int H, int W, int nsplit)
-{
-    constexpr int NPAIR = (COUT / 16) * 2, PPW = NPAIR / 4;
-    static_assert(NPAIR % 4 == 0, "pairs must split over 4 waves");
-    __shared__ __align__(16) uint16_t ldo[COUT * kOS];
-    __shared__ __align__(16) uint16_t ldi[3 * kCK * kIS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int j = lane & 15, g = lane >> 4;
-    const int ch = blockIdx.x, split = blockIdx.y;
-    const int tx = (W + kTS - 1) / kTS, ty = (H + kTS - 1) / kTS, per = tx * ty, ntile = nb * per;
-
-    f32x4 acc[PPW][9];
-#pragma unroll
-    for (int q = 0; q < PPW; ++q)
-#pragma unroll
-        for (int t = 0; t < 9; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bsum = 0.f;
-
-    for (int t = split; t < ntile; t += nsplit) {
-        const int b = t / per, r = t - b * per;
-        const int y0 = (r / tx) * kTS, x0 = (r % tx) * kTS;
-        // output gradient tile, transposed to [cout][pixel]
-        for (int v = tid; v < 256 * (COUT / 8); v += 256) {
-            const int p = v & 255, cg = v >> 8;
-            const int y = y0 + (p >> 4), x = x0 + (p & 15);
-            const uint4 ld = *reinterpret_cast<const uint4 *>(
-                dout + (((size_t)b * H + min(y, H - 1)) * W + min(x, W - 1)) * COUT + cg * 8);
-            const uint4 val = y < H && x < W ? ld : make_uint4(0, 0, 0, 0);
-            const uint32_t w4[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                ldo[(cg * 8 + 2 * e) * kOS + p] = (uint16_t)(w4[e] & 0xffffu);
-                ldo[(cg * 8 + 2 * e + 1) * kOS + p] = (uint16_t)(w4[e] >> 16);
-            }
-        }
-        // input halo of this channel chunk as three copies shifted by dx:
-        // ldi[dx][c][hy][px] = In(y0 + hy - 1, x0 + px + dx - 1, c)
-        for (int v = tid; v < kNV; v += 256) {
-            const int hp = v >> 2, cg = v & 3;
-            const int hy = hp / kHS, hx = hp - hy * kHS;
-            const uint4 val = halo8<MODE, CIN, CA>(A, Bs, b, v, x0, y0, ch, H, W);
-            const uint32_t w4[4] = {val.x, val.y, val.z, val.w};
-#pragma unroll
-            for (int dx = 0; dx < 3; ++dx) {
-                const int px = hx - dx;
-                if (px < 0 || px >= kTS) continue;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ldi[(dx * kCK + cg * 8 + 2 * e) * kIS + hy * kTS + px] = (uint16_t)(w4[e] & 0xffffu);
-                    ldi[(dx * kCK + cg * 8 + 2 * e + 1) * kIS + hy * kTS + px] = (uint16_t)(w4[e] >> 16);
-                }
-            }
-        }
-        __syncthreads();
-        if (ch == 0 && tid < COUT) {
-            const uint16_t *row = ldo + tid * kOS;
-            for (int p = 0; p < 256; ++p) bsum += __uint_as_float((uint32_t)row[p] << 16);
-        }
-#pragma unroll
-        for (int kb = 0; kb < 8; ++kb) {
-            const int row = 2 * kb + (g >> 1), col = (g & 1) * 8;
-#pragma unroll
-            for (int q = 0; q < PPW; ++q) {
-                const int pair = wave * PPW + q, ot = pair >> 1, cti = pair & 1;
-                const uint4 av = *reinterpret_cast<const uint4 *>(&ldo[(ot * 16 + j) * kOS + row * kTS + col]);
-#pragma unroll
-                for (int tap = 0; tap < 9; ++tap) {
-                    const int dy = tap / 3, dx = tap % 3;
-                    const uint4 bv = *reinterpret_cast<const uint4 *>(
-                        &ldi[(dx * kCK + cti * 16 + j) * kIS + (row + dy) * kTS + col]);
-                    acc[q][tap] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf8(av), as_bf8(bv), acc[q][tap], 0, 0, 0);
-                }
-            }
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int q = 0; q < PPW; ++q) {
-        const int pair = wave * PPW + q, ot = pair >> 1, cti = pair & 1;
-        const int c = ch * kCK + cti * 16 + j;
-#pragma unroll
-        for (int tap = 0; tap < 9; ++tap)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int o = ot * 16 + g * 4 + v;
-                part[(((size_t)split * COUT + o) * 9 + tap) * CIN + c] = acc[q][tap][v];
-            }
-    }
-    if (ch == 0 && tid < COUT) bpart[(size_t)split * COUT + tid] = bsum;
-}
-
-// out[i] = sum over s < n of part[s * stride + i].  A block covers 64
-// consecutive i with 4 lanes each; lane q adds s = q, q + 4, ... in order and
-// the four lane sums are combined in a fixed order, so the result does not
-// depend on scheduling.
-__global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ part, float *__restrict__ out,
-                                                   int count, int n, size_t stride)
-{
-    __shared__ float red[4][64];
-    const int q = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int i = blockIdx.x * 64 + l;
-    float s = 0.f;
-    if (i < count)
-        for (int k = q; k < n; k += 4) s += part[(size_t)k * stride + i];
-    red[q][l] = s;
-    __syncthreads();
-    if (q == 0 && i < count) out[i] = (red[0][l] + red[1][l]) + (red[2][l] + red[3][l]);
 }
 
 // ---- head, loss, routing ---------------------------------------------------
@@ -853,26 +677,6 @@ __global__ __launch_bounds__(256) void k_sum_loss(const float *__restrict__ part
 }
 
 // ---- launch helpers -----------------------------------------------------------
-int choose_split(int nchunk, int ntile)
-{
-    int s = std::max(1, 256 / nchunk);
-    return std::min(s, ntile);
-}
-
-template <int CIN, int COUT, int MODE, int CA>
-int wgrad(const uint16_t *A, const uint16_t *Bs, const uint16_t *dout, float *part, float *bpart, float *gw,
-          float *gb, int nb, int H, int W, hipStream_t st)
-{
-    const int ntile = nb * ((H + kTS - 1) / kTS) * ((W + kTS - 1) / kTS);
-    const int ns = choose_split(CIN / kCK, ntile);
-    hipLaunchKernelGGL((k_wgrad3<CIN, COUT, MODE, CA>), dim3(CIN / kCK, ns), dim3(256), 0, st, A, Bs, dout, part,
-                       bpart, nb, H, W, ns);
-    const int nw = COUT * 9 * CIN;
-    hipLaunchKernelGGL(k_sum_parts, dim3((nw + 63) / 64), dim3(256), 0, st, part, gw, nw, ns, (size_t)nw);
-    hipLaunchKernelGGL(k_sum_parts, dim3((COUT + 63) / 64), dim3(256), 0, st, bpart, gb, COUT, ns, (size_t)COUT);
-    return last_status();
-}
-
 template <int CL, int CT>
 int route_up(const float *dc, const uint16_t *act, uint16_t *dlow, int nb, int Hl, int Wl, hipStream_t st)
 {
@@ -958,7 +762,7 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
         return ConvArgs{g, nullptr, wf + L.offw[l], nullptr, out, nullptr, nullptr, nullptr, nullptr, nb, h, w};
     };
     auto GW = [&](int l) { return n->grad + L.offw[l]; };
-    auto GB = [&](int l) { return n->grad + L.offb[l]; };
+    const int cu = n->ctx->num_cu;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
     const int hwp = H * W, total = nb * hwp;
     // head and loss
@@ -972,31 +776,31 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     hipLaunchKernelGGL(k_sum_loss, dim3(34), dim3(256), 0, st, n->part, nblk, loss, n->grad + L.offw[7]);
     int rc = last_status();
     // d0: input cat(up(d1), e0) at H
-    if (!rc) rc = wgrad<64, 32, kUpCat, 32>(n->d1, n->e0, n->g_d0, n->part, n->bpart, GW(6), GB(6), nb, H, W, st);
-    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutF32>(grad_args(n->g_d0, 6, n->f_c0, H, W), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<64, 32, kUpCat, 32>(n->d1, n->e0, n->g_d0, n->part, GW(6), nb, H, W, cu, st);
+    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutF32>(grad_args(n->g_d0, 6, n->f_c0, H, W), cu, st);
     if (!rc) rc = route_up<32, 64>(n->f_c0, n->d1, n->g_d1, nb, H1, W1, st);
     // d1: input cat(up(d2), e1) at H/2
-    if (!rc) rc = wgrad<128, 32, kUpCat, 64>(n->d2, n->e1, n->g_d1, n->part, n->bpart, GW(5), GB(5), nb, H1, W1, st);
-    if (!rc) rc = launch_conv3<32, 128, kPlain, 0, kOutF32>(grad_args(n->g_d1, 5, n->f_c1, H1, W1), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<128, 32, kUpCat, 64>(n->d2, n->e1, n->g_d1, n->part, GW(5), nb, H1, W1, cu, st);
+    if (!rc) rc = launch_conv3<32, 128, kPlain, 0, kOutF32>(grad_args(n->g_d1, 5, n->f_c1, H1, W1), cu, st);
     if (!rc) rc = route_up<64, 128>(n->f_c1, n->d2, n->g_d2, nb, H2, W2, st);
     // d2: input cat(up(e3), e2) at H/4
-    if (!rc) rc = wgrad<256, 64, kUpCat, 128>(n->e3, n->e2, n->g_d2, n->part, n->bpart, GW(4), GB(4), nb, H2, W2, st);
-    if (!rc) rc = launch_conv3<64, 256, kPlain, 0, kOutF32>(grad_args(n->g_d2, 4, n->f_c2, H2, W2), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<256, 64, kUpCat, 128>(n->e3, n->e2, n->g_d2, n->part, GW(4), nb, H2, W2, cu, st);
+    if (!rc) rc = launch_conv3<64, 256, kPlain, 0, kOutF32>(grad_args(n->g_d2, 4, n->f_c2, H2, W2), cu, st);
     if (!rc) rc = route_up<128, 256>(n->f_c2, n->e3, n->g_e3, nb, H3, W3, st);
     // e3: input pool(e2) at H/8
-    if (!rc) rc = wgrad<128, 128, kPlain, 0>(n->p2, nullptr, n->g_e3, n->part, n->bpart, GW(3), GB(3), nb, H3, W3, st);
-    if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutF32>(grad_args(n->g_e3, 3, n->f_p2, H3, W3), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<128, 128, kPlain, 0>(n->p2, nullptr, n->g_e3, n->part, GW(3), nb, H3, W3, cu, st);
+    if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutF32>(grad_args(n->g_e3, 3, n->f_p2, H3, W3), cu, st);
     if (!rc) rc = route_pool<128, 128, 256>(n->f_c2, n->f_p2, n->e2, n->g_e2, nb, H2, W2, st);
     // e2: input pool(e1) at H/4
-    if (!rc) rc = wgrad<64, 128, kPlain, 0>(n->p1, nullptr, n->g_e2, n->part, n->bpart, GW(2), GB(2), nb, H2, W2, st);
-    if (!rc) rc = launch_conv3<128, 64, kPlain, 0, kOutF32>(grad_args(n->g_e2, 2, n->f_p1, H2, W2), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<64, 128, kPlain, 0>(n->p1, nullptr, n->g_e2, n->part, GW(2), nb, H2, W2, cu, st);
+    if (!rc) rc = launch_conv3<128, 64, kPlain, 0, kOutF32>(grad_args(n->g_e2, 2, n->f_p1, H2, W2), cu, st);
     if (!rc) rc = route_pool<64, 64, 128>(n->f_c1, n->f_p1, n->e1, n->g_e1, nb, H1, W1, st);
     // e1: input pool(e0) at H/2
-    if (!rc) rc = wgrad<32, 64, kPlain, 0>(n->p0, nullptr, n->g_e1, n->part, n->bpart, GW(1), GB(1), nb, H1, W1, st);
-    if (!rc) rc = launch_conv3<64, 32, kPlain, 0, kOutF32>(grad_args(n->g_e1, 1, n->f_p0, H1, W1), n->ctx->num_cu, st);
+    if (!rc) rc = launch_wgrad3<32, 64, kPlain, 0>(n->p0, nullptr, n->g_e1, n->part, GW(1), nb, H1, W1, cu, st);
+    if (!rc) rc = launch_conv3<64, 32, kPlain, 0, kOutF32>(grad_args(n->g_e1, 1, n->f_p0, H1, W1), cu, st);
     if (!rc) rc = route_pool<32, 32, 64>(n->f_c0, n->f_p0, n->e0, n->g_e0, nb, H, W, st);
     // e0: input x (padded to 32 channels)
-    if (!rc) rc = wgrad<32, 32, kIn4, 0>(n->xp, nullptr, n->g_e0, n->part, n->bpart, GW(0), GB(0), nb, H, W, st);
+    if (!rc) rc = launch_wgrad_in(n->xp, n->g_e0, n->part, GW(0), nb, H, W, cu, st);
     return rc;
 }
 

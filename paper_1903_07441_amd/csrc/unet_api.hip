@@ -6,6 +6,7 @@
 
 #include "twg_internal.h"
 #include "unet.h"
+#include "wgrad3.h"
 
 using namespace twg;
 
@@ -63,11 +64,11 @@ int ensure_bwd(twg_unet *n, long long P)
     }
     const size_t P0 = (size_t)P, P1 = P0 / 4, P2 = P0 / 16, P3 = P0 / 64;
     // bf16 gradients, FP32 input gradients, split-K partial sums
-    const size_t parts = std::max<size_t>((size_t)16384 * 9 * 128, 34 * ((P0 + 255) / 256));
+    const size_t parts = std::max<size_t>(kPartFloats, 34 * ((P0 + 255) / 256));
     const size_t sizes[] = {al(P0 * 32 * 2), al(P1 * 32 * 2), al(P2 * 64 * 2), al(P3 * 128 * 2), al(P2 * 128 * 2),
                             al(P1 * 64 * 2), al(P0 * 32 * 2), al(P0 * 64 * 4), al(P1 * 128 * 4), al(P2 * 256 * 4),
                             al(P3 * 128 * 4), al(P2 * 64 * 4), al(P1 * 32 * 4), al(parts * 4),
-                            al((size_t)512 * 128 * 4), al((size_t)65536 * 4)};
+                            al((size_t)65536 * 4)};
     size_t bytes = 0;
     for (size_t s : sizes) bytes += s;
     if (hipMalloc(&n->bblock, bytes) != hipSuccess) {
@@ -91,7 +92,6 @@ int ensure_bwd(twg_unet *n, long long P)
     n->f_p1 = reinterpret_cast<float *>(take());
     n->f_p0 = reinterpret_cast<float *>(take());
     n->part = reinterpret_cast<float *>(take());
-    n->bpart = reinterpret_cast<float *>(take());
     n->counts = reinterpret_cast<unsigned int *>(take());
     n->bwd_pixels = P;
     return TWG_OK;
