@@ -877,8 +877,7 @@ int32_t twg_ctx_create(twg_ctx **out, int32_t device)
         ctx->num_cu = prop.multiProcessorCount;
         ctx->lds_per_block = prop.sharedMemPerBlock;
     }
-    if (hipMalloc(&ctx->words, kWords * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc(&ctx->rpart, 2 * kResidBlocks * sizeof(unsigned long long)) != hipSuccess ||
+    if (hipMalloc(&ctx->rpart, 2 * kResidBlocks * sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc(&ctx->host_words, kWords * sizeof(unsigned long long), hipHostMallocDefault) !=
             hipSuccess) {
         twg_ctx_destroy(ctx);
@@ -907,8 +906,8 @@ int32_t twg_ctx_destroy(twg_ctx *ctx)
     for (auto &g : ctx->graphs) hipGraphExecDestroy(g.exec);
     ctx->graphs.clear();
     if (ctx->cap) hipStreamDestroy(ctx->cap);
-    void *bufs[] = {ctx->alt,   ctx->pol,   ctx->alt64,  ctx->fmask, ctx->pairs,   ctx->idxbuf,
-                    ctx->batch, ctx->words, ctx->jumpbuf, ctx->rpart, ctx->tunebuf, ctx->ctl};
+    void *bufs[] = {ctx->alt,   ctx->pol,   ctx->alt64,  ctx->fmask, ctx->idxbuf,
+                    ctx->batch, ctx->jumpbuf, ctx->rpart, ctx->tunebuf, ctx->ctl};
     for (void *b : bufs)
         if (b) hipFree(b);
     if (ctx->host_words) hipHostFree(ctx->host_words);

@@ -1,33 +1,40 @@
 // Map update on the time-warped grid (Algorithm 1, "Map Update"; sections
 // "Time-Warped Grid" and "Integration of Kalman Filter with Time-Warps").
 //
-//   k_raster_base  one thread per cell: ring number and the WALL / GOAL /
-//                  static-OBST / FREE class.
-//   k_pairs        one thread per (obstacle, ring): the constant-velocity
-//                  Kalman prediction of Eq. (9) to the ring's horizon, its Q.8
-//                  disc (optionally grown by the predicted position
-//                  covariance), and a conservative test of whether the disc can
-//                  touch the ring and the grid; survivors are appended to a
-//                  list.  With the per-object horizon of Algorithm 1, one
-//                  thread per obstacle, at the horizon of its own ring.
-//   k_scatter      one workgroup per listed pair: exact integer test of every
-//                  cell of the disc's bounding box (ring match + inside the
-//                  disc); FREE cells become OBST.  Every writer stores the same
-//                  byte, so the result does not depend on the order.
+//   k_map    ring number and the WALL / GOAL / static-OBST / FREE class, eight
+//            cells a thread.
+//   k_discs  per (obstacle, ring), one lane makes the constant-velocity
+//            Kalman prediction of Eq. (9) to the ring's horizon, its Q.8 disc (optionally grown by the
+//            predicted position covariance), and a conservative test of
+//            whether the disc can touch the ring and the grid; the survivors
+//            are marked by the whole wave: an exact integer test of every
+//            cell of the disc's bounding box (ring match + inside the disc).
+//            A marked cell that is not a border wall or the goal becomes
+//            OBST: nothing is read back, and every writer stores the same
+//            byte, so the result does not depend on the order.  With the
+//            per-object horizon of Algorithm 1 the obstacle has one disc, at
+//            the horizon of its own ring.
+//
+// Bound by launches and latency (500 discs on 2048 x 2048: 12.6 MB, 2.5 us at
+// the copy rate): two launches instead of four (a counter cleared, cells, a
+// list of (obstacle, ring) pairs built with atomics, and its scatter), squares
+// and ring numbers in 32 bits instead of FP64 square roots and 64-bit
+// divisions.
 //
 // Exactness: the horizon, the product and the sum of the prediction are each
 // rounded once (contraction is off for this file), 256*mu is exact, and the
 // Q.8 rounding is round-half-to-even; the inside test is in 64-bit integers.
 #include "twg_internal.h"
 
+#include <algorithm>
+
 namespace twg {
 
 namespace {
 
-struct Pair {
+struct Disc {
     long long cx, cy, R;  // Q.8 centre and radius
-    int j;                // ring
-    int pad;
+    int j;                // ring, or -1: all its cells
 };
 
 __device__ __forceinline__ int dev_isqrt(long long n)
@@ -73,9 +80,16 @@ struct WarpMode {
     double hc, hs;  // heading
 };
 
-__device__ __forceinline__ int ring_any(long long dx, long long dy, int W, const WarpMode &m)
+// floor(sqrt(n)) / W for the squared distance of two cells (n < 2^31, so the
+// root is below 46341): the hardware square root is within 0.02 of it and the
+// product with 1 / W within 0.01, so one step up or down makes each exact
+__device__ __forceinline__ int ring_of_cells(int dx, int dy, int W, float inv_w)
 {
-    return m.ring_mode == 1 ? ring_ellipse(dx, dy, m.hc, m.hs, W) : ring_of(dx, dy, W);
+    const uint32_t n = (uint32_t)(dx * dx) + (uint32_t)dy * (uint32_t)dy;
+    uint32_t s = (uint32_t)__builtin_amdgcn_sqrtf((float)n);
+    s = s * s > n ? s - 1u : (s + 1u) * (s + 1u) <= n ? s + 1u : s;
+    uint32_t j = (uint32_t)((float)s * inv_w);
+    return (int)(j * (uint32_t)W > s ? j - 1u : (j + 1u) * (uint32_t)W <= s ? j + 1u : j);
 }
 
 // Disc radius with covariance inflation: r + min(W, kappa sqrt(lambda_max)),
@@ -101,56 +115,33 @@ __device__ __forceinline__ long long floor_div256(long long a)
     return a >= 0 ? a / 256 : -((-a + 255) / 256);
 }
 
-__global__ void k_raster_base(int nx, int ny, int pitch, int xr, int yr, int xg, int yg, int W,
-                              int border, WarpMode wm, const uint8_t *__restrict__ static_occ,
-                              uint8_t *__restrict__ cls, uint16_t *__restrict__ ring)
+// The obstacle's disc at ring j's horizon, to be marked on the cells of ring
+// j; with the per-object horizon (Algorithm 1), its disc at the horizon of
+// the ring of the cell nearest its current centre, to be marked whole (j is
+// then -1).  False if it cannot touch a cell.
+template <bool ELL>
+__device__ __forceinline__ bool disc_at(int j, bool per_object, double px, double py, double vx, double vy, double r,
+                                        const double *cov, double kappa, const WarpMode &wm, int W, double vr, int nx,
+                                        int ny, int xr, int yr, Disc *out)
 {
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= nx || y >= ny) return;
-    const size_t i = (size_t)y * pitch + x;
-    uint8_t c = TWG_CELL_FREE;
-    if (border && (x == 0 || y == 0 || x == nx - 1 || y == ny - 1)) c = TWG_CELL_WALL;
-    else if (x == xg && y == yg) c = TWG_CELL_GOAL;
-    else if (static_occ && static_occ[i]) c = TWG_CELL_OBST;
-    cls[i] = c;
-    if (ring) ring[i] = (uint16_t)ring_any(x - xr, y - yr, W, wm);
-}
-
-// Per-cell horizon: one thread per (obstacle, ring) pair j < J; the disc
-// predicted to ring j's horizon is listed with ring j (its cells of ring j are
-// marked).  Per-object horizon (Algorithm 1): one thread per obstacle; the
-// disc predicted to the horizon of the ring of the cell nearest the
-// obstacle's current centre is listed with ring -1 (all its cells marked).
-__global__ void k_pairs(int n_obs, int J, int per_object, const double *__restrict__ pos,
-                        const double *__restrict__ vel, const double *__restrict__ rad,
-                        const double *__restrict__ cov, double kappa, WarpMode wm, int W, double vr, int nx,
-                        int ny, int xr, int yr, Pair *__restrict__ list, unsigned int *count)
-{
-    const long long id = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (long long)n_obs * (per_object ? 1 : J)) return;
-    const int i = per_object ? (int)id : (int)(id / J);
-    const double r = rad[i];
-    if (!(r >= 0.0 && r <= 1e6)) return;
-    int j;
+    if (!(r >= 0.0 && r <= 1e6)) return false;
     if (per_object) {
-        const double px = rint(pos[2 * i]), py = rint(pos[2 * i + 1]);
-        if (!(fabs(px) < 1e9) || !(fabs(py) < 1e9)) return;
-        j = ring_any((long long)px - xr, (long long)py - yr, W, wm);
-    } else {
-        j = (int)(id % J);
+        const double cx = rint(px), cy = rint(py);
+        if (!(fabs(cx) < 1e9) || !(fabs(cy) < 1e9)) return false;
+        const long long ox = (long long)cx - xr, oy = (long long)cy - yr;
+        j = ELL ? ring_ellipse(ox, oy, wm.hc, wm.hs, W) : ring_of(ox, oy, W);
     }
     // Eq. (9) with A(t): position p + t v, each operation rounded once
     const double t = ((double)j * (double)W) / vr;
-    const double tvx = t * vel[2 * i], tvy = t * vel[2 * i + 1];
-    const double mx = pos[2 * i] + tvx, my = pos[2 * i + 1] + tvy;
+    const double tvx = t * vx, tvy = t * vy;
+    const double mx = px + tvx, my = py + tvy;
     const double sx = 256.0 * mx, sy = 256.0 * my;
-    if (!(fabs(sx) < 1099511627776.0) || !(fabs(sy) < 1099511627776.0)) return;
+    if (!(fabs(sx) < 1099511627776.0) || !(fabs(sy) < 1099511627776.0)) return false;
     const long long cx = (long long)rint(sx), cy = (long long)rint(sy);
-    const double re = inflated_radius(r, cov ? cov + 16 * (size_t)i : nullptr, t, kappa, W);
+    const double re = inflated_radius(r, cov, t, kappa, W);
     const long long R = (long long)rint(256.0 * re);
     // disc must reach the grid
-    if (cx + R < 0 || cx - R > 256LL * (nx - 1) || cy + R < 0 || cy - R > 256LL * (ny - 1)) return;
+    if (cx + R < 0 || cx - R > 256LL * (nx - 1) || cy + R < 0 || cy - R > 256LL * (ny - 1)) return false;
     if (!per_object) {
         // ...and ring j: cells of the disc lie within R of its centre; ring j
         // holds Euclidean distances [jW, (j+1)W) (circular) or, since the
@@ -158,46 +149,132 @@ __global__ void k_pairs(int n_obs, int J, int per_object, const double *__restri
         // (elliptical); two cells of margin absorb rounding
         const double dx = (double)cx / 256.0 - xr, dy = (double)cy / 256.0 - yr;
         const double D = sqrt(dx * dx + dy * dy), Rc = (double)R / 256.0;
-        const double lo = wm.ring_mode == 1 ? (double)j * W / 10.0 : (double)j * W;
-        const double hi = wm.ring_mode == 1 ? 1.9 * (double)(j + 1) * W : (double)(j + 1) * W;
-        if (D - Rc - 2.0 >= hi) return;
-        if (D + Rc + 2.0 < lo) return;
+        const double lo = ELL ? (double)j * W / 10.0 : (double)j * W;
+        const double hi = ELL ? 1.9 * (double)(j + 1) * W : (double)(j + 1) * W;
+        if (D - Rc - 2.0 >= hi) return false;
+        if (D + Rc + 2.0 < lo) return false;
     }
-    const unsigned slot = atomicAdd(count, 1u);
-    Pair p;
-    p.cx = cx; p.cy = cy; p.R = R; p.j = per_object ? -1 : j; p.pad = 0;
-    list[slot] = p;
+    *out = Disc{cx, cy, R, per_object ? -1 : j};
+    return true;
 }
 
-__global__ __launch_bounds__(256) void k_scatter(const Pair *__restrict__ list,
-                                                 const unsigned int *__restrict__ count, int nx,
-                                                 int ny, int pitch, int xr, int yr, int W, WarpMode wm,
-                                                 uint8_t *cls)
+// 32 x 8 threads of 8 cells.  VEC: pitch and bases allow 8-byte class and
+// 16-byte ring stores.  ELL: the elliptical metric (its FP64 code is kept out
+// of the other kernels).
+template <bool VEC, bool ELL>
+__global__ __launch_bounds__(256) void k_map(int nx, int ny, int pitch, int xr, int yr, int xg, int yg, int W,
+                                             float inv_w, int border, WarpMode wm,
+                                             const uint8_t *__restrict__ static_occ, uint8_t *__restrict__ cls,
+                                             uint16_t *__restrict__ ring)
 {
-    const unsigned n = *count;
-    for (unsigned e = blockIdx.x; e < n; e += gridDim.x) {
-        const Pair p = list[e];
-        long long x0 = -floor_div256(-(p.cx - p.R)), x1 = floor_div256(p.cx + p.R);
-        long long y0 = -floor_div256(-(p.cy - p.R)), y1 = floor_div256(p.cy + p.R);
-        if (x0 < 0) x0 = 0;
-        if (y0 < 0) y0 = 0;
-        if (x1 > nx - 1) x1 = nx - 1;
-        if (y1 > ny - 1) y1 = ny - 1;
-        if (x1 < x0 || y1 < y0) continue;
-        const long long w = x1 - x0 + 1, total = w * (y1 - y0 + 1);
-        for (long long k = threadIdx.x; k < total; k += blockDim.x) {
-            const int x = (int)(x0 + k % w), y = (int)(y0 + k / w);
-            if (p.j >= 0 && ring_any(x - xr, y - yr, W, wm) != p.j) continue;
-            const long long dx = 256LL * x - p.cx, dy = 256LL * y - p.cy;
-            if (dx * dx + dy * dy <= p.R * p.R) {
-                const size_t i = (size_t)y * pitch + x;
-                if (cls[i] == TWG_CELL_FREE) cls[i] = TWG_CELL_OBST;
+    const int x0 = (blockIdx.x * 32 + (threadIdx.x & 31)) * 8, y = blockIdx.y * 8 + (threadIdx.x >> 5);
+    if (x0 >= nx || y >= ny) return;
+    const size_t i = (size_t)y * pitch + x0;
+    const bool whole = VEC && x0 + 8 <= nx;
+    uint8_t occ[8] = {};
+    if (static_occ) {
+        if (whole) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(static_occ + i);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) occ[k] = (uint8_t)((k < 4 ? v.x >> (8 * k) : v.y >> (8 * (k - 4))) & 0xffu);
+        } else {
+            for (int k = 0; k < 8; ++k)
+                if (x0 + k < nx) occ[k] = static_occ[i + k];
+        }
+    }
+    uint32_t c[8], r[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const int x = x0 + k;
+        c[k] = occ[k] ? TWG_CELL_OBST : TWG_CELL_FREE;
+        if (x == xg && y == yg) c[k] = TWG_CELL_GOAL;
+        if (border && (x == 0 || y == 0 || x == nx - 1 || y == ny - 1)) c[k] = TWG_CELL_WALL;
+        r[k] = 0u;
+        if (ring)
+            r[k] = (uint32_t)(ELL ? ring_ellipse(x - xr, y - yr, wm.hc, wm.hs, W)
+                                  : ring_of_cells(x - xr, y - yr, W, inv_w));
+    }
+    if (whole) {
+        *reinterpret_cast<uint2 *>(cls + i) = make_uint2(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24,
+                                                         c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24);
+        if (ring)
+            *reinterpret_cast<uint4 *>(ring + i) = make_uint4(r[0] | r[1] << 16, r[2] | r[3] << 16, r[4] | r[5] << 16,
+                                                              r[6] | r[7] << 16);
+    } else {
+        for (int k = 0; k < 8; ++k)
+            if (x0 + k < nx) {
+                cls[i + k] = (uint8_t)c[k];
+                if (ring) ring[i + k] = (uint16_t)r[k];
+            }
+    }
+}
+
+// Wave w of n_waves takes the (obstacle, ring) pairs w, w + n_waves, ..., one
+// a lane, so that the rings of one obstacle (a disc that moves with the rings
+// meets a hundred of them) go to different waves, then marks the discs that
+// survive one after another.
+template <bool ELL>
+__global__ __launch_bounds__(256) void k_discs(long long n_pairs, long long n_waves, int J, int per_object,
+                                               const double *__restrict__ pos, const double *__restrict__ vel,
+                                               const double *__restrict__ rad, const double *__restrict__ cov,
+                                               double kappa, WarpMode wm, int W, float inv_w, double vr, int nx, int ny,
+                                               int pitch, int xr, int yr, int xg, int yg, int border,
+                                               uint8_t *__restrict__ cls)
+{
+    const int lane = threadIdx.x & 63;
+    const long long w = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (w >= n_waves) return;
+    // cells a disc may mark: not the border walls
+    const int xa = border ? 1 : 0, xb = border ? nx - 2 : nx - 1, ya = border ? 1 : 0, yb = border ? ny - 2 : ny - 1;
+    const long long id = w + lane * n_waves;
+    Disc d{};
+    bool hit = false;
+    if (id < n_pairs) {
+        const long long i = per_object ? id : id >> 32 ? id / J : (long long)((uint32_t)id / (uint32_t)J);
+        const int j = per_object ? 0 : (int)(id - i * J);
+        hit = disc_at<ELL>(j, per_object, pos[2 * i], pos[2 * i + 1], vel[2 * i], vel[2 * i + 1], rad[i],
+                      cov ? cov + 16 * i : nullptr, kappa, wm, W, vr, nx, ny, xr, yr, &d);
+    }
+    {
+        for (unsigned long long todo = __ballot(hit); todo; todo &= todo - 1) {
+            const int l = __builtin_ctzll(todo);
+            const Disc p{__shfl(d.cx, l), __shfl(d.cy, l), __shfl(d.R, l), __shfl(d.j, l)};
+            const int x0 = (int)max(-floor_div256(-(p.cx - p.R)), (long long)xa);
+            const int x1 = (int)min(floor_div256(p.cx + p.R), (long long)xb);
+            const int y0 = (int)max(-floor_div256(-(p.cy - p.R)), (long long)ya);
+            const int y1 = (int)min(floor_div256(p.cy + p.R), (long long)yb);
+            auto mark = [&](int x, int y) {
+                if (p.j >= 0 && (ELL ? ring_ellipse(x - xr, y - yr, wm.hc, wm.hs, W)
+                                     : ring_of_cells(x - xr, y - yr, W, inv_w)) != p.j)
+                    return;
+                if (x != xg || y != yg) cls[(size_t)y * pitch + x] = TWG_CELL_OBST;
+            };
+            // 8 x 8 cells at a time
+            if (p.R < 65000) {  // squares within the box fit 32 bits
+                const uint32_t R2 = (uint32_t)p.R * (uint32_t)p.R;
+                for (int y = y0 + (lane >> 3); y <= y1; y += 8) {
+                    const int dy = (int)(256LL * y - p.cy);
+                    const uint32_t dy2 = (uint32_t)dy * (uint32_t)dy;
+                    if (dy2 > R2) continue;
+                    for (int x = x0 + (lane & 7); x <= x1; x += 8) {
+                        const int dx = (int)(256LL * x - p.cx);
+                        if ((uint32_t)dx * (uint32_t)dx <= R2 - dy2) mark(x, y);
+                    }
+                }
+            } else {
+                const long long R2 = p.R * p.R;
+                for (int y = y0 + (lane >> 3); y <= y1; y += 8) {
+                    const long long dy = 256LL * y - p.cy, in2 = R2 - dy * dy;
+                    if (in2 < 0) continue;
+                    for (int x = x0 + (lane & 7); x <= x1; x += 8) {
+                        const long long dx = 256LL * x - p.cx;
+                        if (dx * dx <= in2) mark(x, y);
+                    }
+                }
             }
         }
     }
 }
-
-__global__ void k_zero_u32(unsigned int *w) { *w = 0u; }
 
 int host_ring(long long dx, long long dy, int W)
 {
@@ -229,23 +306,29 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
         }
     if (J > 65535) return set_err(ctx, TWG_EUNSUPPORTED, "more than 65536 rings: increase ring_width");
     J += 1;
-    hipLaunchKernelGGL(k_raster_base, dim3((nx + 63) / 64, (ny + 3) / 4), dim3(256), 0, st, nx, ny,
-                       pitch, p.robot_x, p.robot_y, p.goal_x, p.goal_y, p.ring_width,
-                       p.border_walls, wm, static_occ, cls, ring);
-    if (hipGetLastError() != hipSuccess) return set_err(ctx, TWG_EDEVICE, "k_raster_base launch failed");
+    const float inv_w = 1.0f / (float)p.ring_width;
+    const auto al = [](const void *q, uintptr_t a) { return (reinterpret_cast<uintptr_t>(q) & (a - 1)) == 0; };
+    const bool vec = pitch % 8 == 0 && al(cls, 8) && al(ring, 16) && al(static_occ, 8);
+    auto map = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((nx + 255) / 256, (ny + 7) / 8), dim3(256), 0, st, nx, ny, pitch, p.robot_x,
+                           p.robot_y, p.goal_x, p.goal_y, p.ring_width, inv_w, p.border_walls, wm, static_occ, cls,
+                           ring);
+    };
+    const bool ell = p.ring_mode == 1;
+    if (vec) ell ? map(k_map<true, true>) : map(k_map<true, false>);
+    else ell ? map(k_map<false, true>) : map(k_map<false, false>);
+    if (hipGetLastError() != hipSuccess) return set_err(ctx, TWG_EDEVICE, "map launch failed");
     if (n_obs == 0) return TWG_OK;
+    // a full wave's worth of pairs each, but at least 2048 waves (or one pair
+    // each): a wave marks its discs one after another
     const long long pairs = (long long)n_obs * (p.per_object ? 1 : J);
-    const size_t need = (size_t)pairs * sizeof(Pair);
-    int rc = ensure(ctx, &ctx->pairs, &ctx->pairs_bytes, need);
-    if (rc) return rc;
-    unsigned int *count = reinterpret_cast<unsigned int *>(ctx->words + 32);
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, st, count);
-    hipLaunchKernelGGL(k_pairs, dim3((unsigned)((pairs + 255) / 256)), dim3(256), 0, st, n_obs, J,
-                       p.per_object, pos, vel, rad, p.cov, p.kappa, wm, p.ring_width, p.robot_speed, nx, ny,
-                       p.robot_x, p.robot_y, reinterpret_cast<Pair *>(ctx->pairs), count);
-    hipLaunchKernelGGL(k_scatter, dim3(1024), dim3(256), 0, st,
-                       reinterpret_cast<const Pair *>(ctx->pairs), count, nx, ny, pitch, p.robot_x,
-                       p.robot_y, p.ring_width, wm, cls);
+    const long long waves = std::max((pairs + 63) / 64, std::min(pairs, 2048LL));
+    auto discs = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, pairs, waves, J, p.per_object,
+                           pos, vel, rad, p.cov, p.kappa, wm, p.ring_width, inv_w, p.robot_speed, nx, ny, pitch,
+                           p.robot_x, p.robot_y, p.goal_x, p.goal_y, p.border_walls, cls);
+    };
+    ell ? discs(k_discs<true>) : discs(k_discs<false>);
     if (hipGetLastError() != hipSuccess) return set_err(ctx, TWG_EDEVICE, "rasterize launch failed");
     return TWG_OK;
 }

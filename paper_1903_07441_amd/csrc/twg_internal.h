@@ -54,9 +54,6 @@ struct twg_ctx {
     // free mask of the streamed sweeps, rebuilt by every call that sweeps
     void *fmask = nullptr;
     size_t fmask_bytes = 0;
-    // (obstacle, ring) work list of the rasteriser and its counter
-    void *pairs = nullptr;
-    size_t pairs_bytes = 0;
     // index matrix of hpf_descend
     void *idxbuf = nullptr;
     size_t idxbuf_bytes = 0;
@@ -70,8 +67,6 @@ struct twg_ctx {
     std::vector<char> batch_sig;
     // tiling of batched relaxations picked by hpf_autotune_batched (0: none)
     int batch_S = 0, batch_RH = 0;
-    // small device words: counters of the rasteriser
-    unsigned long long *words = nullptr;
     // per-block partial maxima of the residual kernels (2 kResidBlocks words)
     unsigned long long *rpart = nullptr;
     // pinned host words: residual maxima (uint64 bit patterns) of the last
