@@ -515,7 +515,7 @@ int32_t hpf_descend(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const float *p
  * FREE or GOAL cell, the number of moves its descent takes to reach a GOAL
  * cell (0 on GOAL cells), and -1 where the descent stops elsewhere (a cell
  * with no strictly better neighbour) or the cell is not walkable.  Computed
- * by pointer jumping over the index matrix (ceil(log2(nx ny)) rounds); on a
+ * tile by tile (pointer jumping over the index matrix); on a
  * converged field every FREE cell connected to the goal gets a length
  * (discrete maximum principle).  Asynchronous.  Errors: TWG_EINVAL. */
 int32_t hpf_descent_all(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const float *psi, const double *psi64,

@@ -907,7 +907,7 @@ int32_t twg_ctx_destroy(twg_ctx *ctx)
     ctx->graphs.clear();
     if (ctx->cap) hipStreamDestroy(ctx->cap);
     void *bufs[] = {ctx->alt,   ctx->pol,   ctx->alt64,  ctx->fmask, ctx->idxbuf,
-                    ctx->batch, ctx->jumpbuf, ctx->rpart, ctx->tunebuf, ctx->ctl};
+                    ctx->batch, ctx->hopbuf, ctx->jumpbuf, ctx->rpart, ctx->tunebuf, ctx->ctl};
     for (void *b : bufs)
         if (b) hipFree(b);
     if (ctx->host_words) hipHostFree(ctx->host_words);
@@ -1493,10 +1493,10 @@ int32_t hpf_descend(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const float *p
     hipStream_t st = as_stream(stream);
     rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, (size_t)g.pitch * g.ny);
     if (rc) return rc;
-    uint8_t *idx = reinterpret_cast<uint8_t *>(ctx->idxbuf);
-    rc = launch_index(cls, psi, psi64, idx, g.nx, g.ny, g.pitch, st, true);
-    if (!rc) rc = launch_walk(cls, idx, g.nx, g.ny, g.pitch, p->start_x, p->start_y, p->cap, path_xy,
-                              info, st);
+    rc = ensure(ctx, &ctx->hopbuf, &ctx->hopbuf_bytes, descend_bytes(g.nx, g.ny));
+    if (rc) return rc;
+    rc = launch_descend(cls, psi, psi64, reinterpret_cast<uint8_t *>(ctx->idxbuf), ctx->hopbuf, g.nx, g.ny, g.pitch,
+                        p->start_x, p->start_y, p->cap, path_xy, info, st);
     return rc ? set_err(ctx, rc, "descent launch failed") : TWG_OK;
 }
 
@@ -1589,15 +1589,9 @@ int32_t hpf_descent_all(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const floa
     if (steps_pitch < g.nx) return set_err(ctx, TWG_EINVAL, "steps_pitch must be >= nx");
     hipSetDevice(ctx->device);
     hipStream_t st = as_stream(stream);
-    const size_t cells = (size_t)g.nx * g.ny;
-    rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, (size_t)g.pitch * g.ny);
-    if (!rc) rc = ensure(ctx, &ctx->jumpbuf, &ctx->jumpbuf_bytes, 4 * cells * sizeof(int));
+    rc = ensure(ctx, &ctx->jumpbuf, &ctx->jumpbuf_bytes, descent_all_bytes(g.nx, g.ny));
     if (rc) return rc;
-    uint8_t *idx = reinterpret_cast<uint8_t *>(ctx->idxbuf);
-    rc = launch_index(cls, psi, psi64, idx, g.nx, g.ny, g.pitch, st);
-    if (!rc)
-        rc = launch_descent_all(cls, idx, g.nx, g.ny, g.pitch, reinterpret_cast<int *>(ctx->jumpbuf), steps,
-                                steps_pitch, st);
+    rc = launch_descent_all(cls, psi, psi64, ctx->jumpbuf, g.nx, g.ny, g.pitch, steps, steps_pitch, st);
     return rc ? set_err(ctx, rc, "descent launch failed") : TWG_OK;
 }
 

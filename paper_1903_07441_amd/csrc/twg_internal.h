@@ -54,10 +54,13 @@ struct twg_ctx {
     // free mask of the streamed sweeps, rebuilt by every call that sweeps
     void *fmask = nullptr;
     size_t fmask_bytes = 0;
-    // index matrix of hpf_descend
+    // walk codes of hpf_descend
     void *idxbuf = nullptr;
     size_t idxbuf_bytes = 0;
-    // pointer-jumping buffers of hpf_descent_all (4 int32 per cell)
+    // tile exits of hpf_descend (and the path's parts)
+    void *hopbuf = nullptr;
+    size_t hopbuf_bytes = 0;
+    // tile exits and in-tile descents of hpf_descent_all
     void *jumpbuf = nullptr;
     size_t jumpbuf_bytes = 0;
     // batched relaxation: descriptors, block list, control state and stats
@@ -265,14 +268,16 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
 int launch_kalman(int n, double *x, double *P, const double *z, double dt, const double *Q, const double *R,
                   double *pos, double *vel, hipStream_t st);
 
-// descend.hip.  walk: write the walk's codes (5 on GOAL cells, else the
-// index code) instead of the index matrix; launch_walk reads those.
-int launch_index(const uint8_t *cls, const float *psi, const double *psi64, uint8_t *idx, int nx,
-                 int ny, int pitch, hipStream_t st, bool walk = false);
-int launch_walk(const uint8_t *cls, const uint8_t *code, int nx, int ny, int pitch, int sx, int sy,
-                int cap, int32_t *path, int32_t *info, hipStream_t st);
-int launch_descent_all(const uint8_t *cls, const uint8_t *idx, int nx, int ny, int pitch, int *buf,
-                       int32_t *steps, int pitch_out, hipStream_t st);
+// descend.hip: the index matrix; one cell's path (code: pitch * ny bytes,
+// scratch: descend_bytes); every cell's descent length (descent_all_bytes)
+int launch_index(const uint8_t *cls, const float *psi, const double *psi64, uint8_t *idx, int nx, int ny, int pitch,
+                 hipStream_t st);
+size_t descend_bytes(int nx, int ny);
+int launch_descend(const uint8_t *cls, const float *psi, const double *psi64, uint8_t *code, void *scratch, int nx,
+                   int ny, int pitch, int sx, int sy, int cap, int32_t *path, int32_t *info, hipStream_t st);
+size_t descent_all_bytes(int nx, int ny);
+int launch_descent_all(const uint8_t *cls, const float *psi, const double *psi64, void *scratch, int nx, int ny,
+                       int pitch, int32_t *steps, int pitch_out, hipStream_t st);
 int launch_rubber(const uint8_t *cls, const float *psi, const double *psi64, int32_t *path, const int32_t *len,
                   int cap, int nx, int ny, int pitch, double k, int iters, hipStream_t st);
 
