@@ -24,6 +24,9 @@ ARCH = "gfx950"
 FLAGS = [
     f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    # a kernel's first arguments arrive in registers (k_relax_slot's control
+    # block and slot number)
+    "-mllvm", "-amdgpu-kernarg-preload-count=3",
     "-I", os.path.join(ROOT, "include"), "-I", CSRC,
 ]
 

@@ -553,6 +553,9 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
         a.tiling[l] = SlotTiling{gl.strips, gl.RH, gl.tiles};
     }
     a.fuse = fuse;
+    int most = 0;
+    for (const SlotTiling &t : a.tiling) most = std::max(most, t.tiles);
+    a.blocks = (most + 3) / 4;
     a.even = g.nx % 2 == 0;
     a.final_slot = 0;
     a.slot = 0;

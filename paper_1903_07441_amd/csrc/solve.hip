@@ -529,16 +529,25 @@ __device__ __forceinline__ double defect_at(const T *u, int nx, int ny, int pitc
 }
 
 // F: passes of S sweeps that one launch may do at once (1, 2 or 4)
+//
+// A pass of a small grid is mostly latency, so the kernel's scalar reads come
+// in two batches: the control block's hot words (ctl and slot, the first
+// arguments, arrive in registers with the wave) next to every other argument
+// a pass uses, then nothing more before the first rows (read where they are
+// used, they were four dependent batches; 0.3 us of a pass).
 template <int S, int F, bool EVEN>
-__global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
+__global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArgs a)
 {
-    RelaxCtl *c = static_cast<RelaxCtl *>(a.ctl);
+    RelaxCtl *c = static_cast<RelaxCtl *>(ctl);
     // the hot words in one load; everything below is wave-uniform
-    const RelaxHot h = *static_cast<const RelaxHot *>(a.ctl);
+    const RelaxHot h = *static_cast<const RelaxHot *>(ctl);
+    asm volatile("" ::"s"(a.mask), "s"(a.psi), "s"(a.alt), "s"(a.e), "s"(a.r32), "s"(a.cdc), "s"(a.clead), "s"(a.nx),
+                 "s"(a.ny), "s"(a.pitch), "s"(a.blocks), "s"(a.final_slot), "s"(a.tiling[0].strips),
+                 "s"(a.tiling[0].RH), "s"(a.tiling[0].tiles), "s"(a.omega), "s"(a.omega_dc), "s"(a.lead_passes));
     const int was = __builtin_amdgcn_readfirstlane(h.phase);
     // position in the current run of passes (solve phases), derived before
     // any branch so that the words above arrive in one load
-    const int k = __builtin_amdgcn_readfirstlane(a.slot - h.run_slot);
+    const int k = __builtin_amdgcn_readfirstlane(slot - h.run_slot);
     // slot k of a run: passes fused F (then F / 2, ...) at a time while that
     // many are left before the next check, which starts a slot of its own
     const int next_check = __builtin_amdgcn_readfirstlane(h.next_check);
@@ -553,8 +562,8 @@ __global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
     const int phase = forced ? (int)PH_FINISH : was;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gw = xcd_remap(blockIdx.x, gridDim.x) * 4 + wave;
-    const int nwaves = gridDim.x * 4;
+    const int gw = xcd_remap(blockIdx.x, a.blocks) * 4 + wave;
+    const int nwaves = a.blocks * 4;
     double m = 0.0;
     float mr = 0.0f;
     bool reduce = false;
@@ -699,7 +708,7 @@ __global__ __launch_bounds__(256) void k_relax_slot(SlotArgs a)
         }
         const unsigned int ticket =
             __hip_atomic_fetch_add(&c->ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        last = ticket == gridDim.x - 1;
+        last = ticket == (unsigned)a.blocks - 1u;
     }
     __syncthreads();
     if (!last) return;
@@ -768,19 +777,17 @@ template <int S>
 int launch_relax_slot_depth(const SlotArgs &a, hipStream_t st)
 {
     constexpr int F = slot_fuse_limit(S);
-    int tiles = a.tiling[0].tiles;
-    for (const SlotTiling &t : a.tiling) tiles = std::max(tiles, t.tiles);
-    const dim3 blocks((tiles + 3) / 4);
+    const dim3 blocks(a.blocks);
     if (F > 1 && a.fuse > 1) {
         if (a.even)
-            hipLaunchKernelGGL((k_relax_slot<S, F, true>), blocks, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_relax_slot<S, F, true>), blocks, dim3(256), 0, st, a.ctl, a.slot, a);
         else
-            hipLaunchKernelGGL((k_relax_slot<S, F, false>), blocks, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_relax_slot<S, F, false>), blocks, dim3(256), 0, st, a.ctl, a.slot, a);
     } else {
         if (a.even)
-            hipLaunchKernelGGL((k_relax_slot<S, 1, true>), blocks, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_relax_slot<S, 1, true>), blocks, dim3(256), 0, st, a.ctl, a.slot, a);
         else
-            hipLaunchKernelGGL((k_relax_slot<S, 1, false>), blocks, dim3(256), 0, st, a);
+            hipLaunchKernelGGL((k_relax_slot<S, 1, false>), blocks, dim3(256), 0, st, a.ctl, a.slot, a);
     }
     return last_status();
 }

@@ -209,6 +209,7 @@ struct SlotArgs {
     int nx, ny, pitch;
     SlotTiling tiling[kSlotLevels];  // SOR tiling of a pass (S sweeps), and of 2 and 4 passes fused
     int fuse;             // passes a launch may fuse (RelaxConfig::fuse)
+    int blocks;           // workgroups: a wave for each tile of the largest tiling
     int even;             // nx is even
     int final_slot;       // 1: finish what is left (the solve is then NOT_CONVERGED)
     int slot;             // this launch's number in the call's sequence (0, 1, ...)
