@@ -12,13 +12,13 @@
 // path, one FP64 maximum per grid), and its stop rules are those of the
 // single-grid solve (tolerance, sweep budget, a stall at the FP32 rounding
 // floor).  Checks happen only at "event" slots, multiples of a quantum, so
-// that many grids share them.  Each slot is followed by a one-workgroup
-// launch, k_batch_ctrl: at an event it runs the controller with one thread
-// per grid, then rebuilds the table of the active grids' tiles that the next
-// slots enumerate (one wave per entry); after any other slot it returns at
-// once.  When no grid is left, one finishing slot copies back every field
-// that ended in the partner buffer, and its control launch writes the
-// per-grid statistics.
+// that many grids share them.  A slot that can be an event is followed by a
+// one-workgroup launch, k_batch_ctrl: at an event it runs the controller with
+// one thread per grid, then rebuilds the table of the active grids' tiles
+// that the next slots enumerate (one wave per entry); after any other slot it
+// returns at once.  When no grid is left, the next slot copies back every
+// field that ended in the partner buffer, and the next control launch writes
+// the per-grid statistics.
 #include "stream_tile.h"
 
 #include <algorithm>
@@ -165,12 +165,14 @@ __device__ void grid_event(const BatchArgs &a, int k, int slot)
 
 // decision published for a blocking caller: the slot of the next event
 // (+1) in the low word, bit 63 when the solve is done
-__device__ void publish_b(unsigned long long *mirror, const BatchHdr *h, int slot_now)
+// (when the fields are only copied back: of the next control launch, at most
+// a quantum q on)
+__device__ void publish_b(unsigned long long *mirror, const BatchHdr *h, int slot_now, int q)
 {
     if (!mirror) return;
     unsigned long long w;
     if (h->phase == BP_DONE) w = 1ull << 63;
-    else if (h->phase == BP_FINISH) w = (unsigned long long)(slot_now + 2);
+    else if (h->phase == BP_FINISH) w = (unsigned long long)(slot_now + q + 1);
     else w = (unsigned long long)(h->next_event + 1);
     *reinterpret_cast<volatile unsigned long long *>(mirror) = w;
     __threadfence_system();
@@ -270,6 +272,8 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
     const int slot = a.slot;
     const bool forced = a.final_slot && phase == BP_RUN;
     const bool finish = phase == BP_FINISH || forced;
+    // the copy back is done once, by the slot after the last event
+    if (phase == BP_FINISH && slot != __builtin_amdgcn_readfirstlane(h.next_event)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int b = xcd_remap(blockIdx.x, gridDim.x);
@@ -356,7 +360,7 @@ __global__ __launch_bounds__(256) void k_batch_ctrl(BatchArgs a)
         __syncthreads();
         if (threadIdx.x == 0) {
             hp->phase = BP_DONE;
-            publish_b(a.mirror, hp, slot);
+            publish_b(a.mirror, hp, slot, a.quantum);
         }
         return;
     }
@@ -366,7 +370,7 @@ __global__ __launch_bounds__(256) void k_batch_ctrl(BatchArgs a)
     build_list(a, hp, slot);
     if (threadIdx.x == 0) {
         hp->events += 1;
-        publish_b(a.mirror, hp, slot);
+        publish_b(a.mirror, hp, slot, a.quantum);
     }
 }
 
@@ -617,6 +621,12 @@ int launch_batch_slot(const BatchArgs &a, int max_tiles, bool even, hipStream_t 
     default: return TWG_EUNSUPPORTED;
     }
     if (rc) return rc;
+    // Control launches only where an event can be: at multiples of the
+    // quantum, and from the last pass of the sweep budget on (a check is
+    // pulled forward to it).  A launch with nothing to do holds the next slot
+    // back by 5.2 us, and a slot of 64 grids of 64 to 1024 cells a side takes
+    // 50 us.
+    if (a.slot % a.quantum && a.slot < a.max_sweeps / a.S && !a.final_slot) return TWG_OK;
     hipLaunchKernelGGL(k_batch_ctrl, dim3(1), dim3(256), 0, st, a);
     return last_status_b();
 }

@@ -172,7 +172,12 @@ constexpr int kSrcNone = 0, kSrcF = 1, kSrcC = 2;
 // arrives, so the loaded values of the previous row are kept in two extra
 // registers.  rmax receives max |r| and rrel max |r| / |c| (|c| >= 1e-30,
 // evaluated with the hardware reciprocal: a diagnostic), both per lane; a
-// NaN residual propagates.
+// NaN residual propagates.  A check is VALU work next to the pass's own (at
+// S = 8 a checking row costs 43 instructions on top of 80, a third of them
+// FP64), so it takes the fewest: the maxima of all lanes, the halo's dropped
+// once at the end, and NaN seen by the integer maxima of the converted
+// residuals instead of a test per cell (64 before; with fewer control
+// launches a batch of 64 grids went from 8.47 to 8.00 ms).
 __device__ __forceinline__ double nan_max(double a, double b) { return (b > a || b != b) ? b : a; }
 
 // f(integral_constant<int, U>) for U = 0, 1, ..., one inlined copy each: the
@@ -298,9 +303,11 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
 
     // CHECK: loaded values of the row above the checked one (columns 2 lane
     // and 2 lane + 1), and the running maxima
-    T upa = T(0), upb = T(0);
-    double cmax = 0.0;
-    float crel = 0.0f;
+    // (of every lane; the halo lanes' are dropped at the end).  The floats'
+    // are kept as bit patterns, which order like non-negative floats with NaN
+    // above infinity; cmax takes no NaN, cnan does.
+    double upa = 0.0, upb = 0.0, cmax = 0.0;
+    uint32_t crel = 0u, cnan = 0u;
     // rows t - 1 checked at row step t: t - 1 in [ybeg - r0, yend - r0)
     const int tchk0 = ybeg - r0 + 1, tchk1 = yend - r0 + 1;
     // rows before the first streamed one are zeros with factor 0; the first
@@ -356,35 +363,40 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         }
         if constexpr (CHECK) {
             // residual of row t - 1 (slot um, not yet touched by any
-            // stage) from the kept row t - 2 and the new row t (slot u)
+            // stage) from the kept row t - 2 and the new row t (slot u).
+            // The sum of four is scaled by 1/4 and the centre subtracted (or
+            // f added) in one fma: a scaled sum is exact, so the bits are
+            // those of the separate operations.
             const int um = (u + NR - 1) % NR, uwm = (uw + NW - 1) % NW;
             const T ca = P0[um], cb = P1[um];
+            const double dca = (double)ca, dcb = (double)cb;
             // only the tile's own rows (a uniform branch: the halo and
             // pipeline rows, two fifths of the steps, skip the FP64 work)
             if (t >= tchk0 && t < tchk1) {
                 const bool ev = (um & 1) == 0;
                 const T wa = ev ? wR[uwm] : wB[uwm], wb = ev ? wB[uwm] : wR[uwm];
-                const T dna = P0[u], dnb = P1[u];
-                const double ea = (double)cb, wwa = (double)shr1(cb);
-                const double eb = (double)shl1(ca), wwb = (double)ca;
-                double ga = ((ea + wwa) + ((double)dna + (double)upa)) * 0.25;
-                double gb = ((eb + wwb) + ((double)dnb + (double)upb)) * 0.25;
+                const double sa = (dcb + (double)shr1(cb)) + ((double)P0[u] + upa);
+                const double sb = ((double)shl1(ca) + dca) + ((double)P1[u] + upb);
+                double ra, rb;
                 if constexpr (RHS == kSrcF) {
-                    ga = ga + (double)F0[um];
-                    gb = gb + (double)F1[um];
+                    ra = __builtin_fma(sa, 0.25, (double)F0[um]) - dca;
+                    rb = __builtin_fma(sb, 0.25, (double)F1[um]) - dcb;
+                } else {
+                    ra = __builtin_fma(sa, 0.25, -dca);
+                    rb = __builtin_fma(sb, 0.25, -dcb);
                 }
-                const double ra = ga - (double)ca, rb = gb - (double)cb;
-                const bool oka = writer && wa != T(0), okb = writer && wb != T(0);
-                cmax = nan_max(cmax, oka ? fabs(ra) : 0.0);
-                cmax = nan_max(cmax, okb ? fabs(rb) : 0.0);
+                ra = wa != T(0) ? ra : 0.0;
+                rb = wb != T(0) ? rb : 0.0;
+                cmax = fmax(cmax, fmax(fabs(ra), fabs(rb)));
+                const float fa = fabsf((float)ra), fb = fabsf((float)rb);
+                cnan = max(cnan, max(__float_as_uint(fa), __float_as_uint(fb)));
                 const float aa = fabsf((float)ca), ab = fabsf((float)cb);
-                const float qa = fabsf((float)ra) * __builtin_amdgcn_rcpf(aa);
-                const float qb = fabsf((float)rb) * __builtin_amdgcn_rcpf(ab);
-                crel = nan_maxf(crel, oka && aa >= 1e-30f ? qa : 0.0f);
-                crel = nan_maxf(crel, okb && ab >= 1e-30f ? qb : 0.0f);
+                const float qa = aa >= 1e-30f ? fa * __builtin_amdgcn_rcpf(aa) : 0.0f;
+                const float qb = ab >= 1e-30f ? fb * __builtin_amdgcn_rcpf(ab) : 0.0f;
+                crel = max(crel, max(__float_as_uint(fabsf(qa)), __float_as_uint(fabsf(qb))));
             }
-            upa = ca;
-            upb = cb;
+            upa = dca;
+            upb = dcb;
         }
         // row t + NW goes to the slot row t - NW left at the last step
         __builtin_amdgcn_sched_barrier(0);
@@ -492,8 +504,9 @@ __device__ __forceinline__ void stream_tile(const T *__restrict__ src, T *__rest
         }
     }
     if constexpr (CHECK) {
-        *rmax = nan_max(*rmax, cmax);
-        *rrel = nan_maxf(*rrel, crel);
+        if (cnan > 0x7f800000u) cmax = __longlong_as_double(0x7ff8000000000000ll);
+        *rmax = nan_max(*rmax, writer ? cmax : 0.0);
+        *rrel = nan_maxf(*rrel, writer ? __uint_as_float(crel) : 0.0f);
     }
 }
 
