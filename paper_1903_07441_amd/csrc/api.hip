@@ -584,6 +584,7 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     *word = 0ull;
     std::atomic_thread_fence(std::memory_order_seq_cst);
     a.mirror = ctx->host_words_dev + kMirrorWord;
+    const bool resident = relax_resident(g.nx, g.ny);
     int64_t queued = 0, target = 1 + kSlotMargin;
     unsigned long long seen = 0;
     int idle = 0;
@@ -597,7 +598,8 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
         }
         if (queued < target) {
             a.slot = (int)queued;
-            if ((rc = launch_relax_slot(a, pl.S, st))) return set_err(ctx, rc, "relaxation slot launch failed");
+            rc = resident ? launch_relax_resident(a, st) : launch_relax_slot(a, pl.S, st);
+            if (rc) return set_err(ctx, rc, "relaxation slot launch failed");
             ++queued;
             continue;
         }

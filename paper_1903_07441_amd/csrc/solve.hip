@@ -352,10 +352,9 @@ __device__ void publish(const RelaxCtl *c, unsigned long long *mirror, int32_t s
 // buffer parity par), a defect, an update, or the finish (`forced`: the
 // final slot ends a solve whose phase was `was`, at pass p on parity par
 // if that phase was a solve).
-__device__ void controller_on(RelaxCtl *c, const SlotArgs &a, int phase, int was, bool forced, int32_t p,
-                              int32_t par, double r, double rel)
+__device__ void controller_on(RelaxCtl *c, const SlotArgs &a, int32_t slot_now, unsigned long long *mirror, int phase,
+                              int was, bool forced, int32_t p, int32_t par, double r, double rel)
 {
-    const int32_t slot_now = a.slot;
     switch (phase) {
     case PH_PLAIN:
     case PH_CORR: {
@@ -398,7 +397,7 @@ __device__ void controller_on(RelaxCtl *c, const SlotArgs &a, int phase, int was
         c->h.phase = PH_DONE;
         break;
     }
-    publish(c, a.mirror, slot_now);
+    publish(c, mirror, slot_now);
 }
 
 // The controller works on a copy of the control block in registers: read in
@@ -410,7 +409,7 @@ __device__ void controller(RelaxCtl *cg, const SlotArgs &a, int phase, int was, 
                            double r, double rel)
 {
     RelaxCtl c = *cg;
-    controller_on(&c, a, phase, was, forced, p, par, r, rel);
+    controller_on(&c, a, a.slot, a.mirror, phase, was, forced, p, par, r, rel);
     cg->h = c.h;
     cg->last_check = c.last_check;
     cg->lead_check = c.lead_check;
@@ -435,26 +434,9 @@ __device__ void controller(RelaxCtl *cg, const SlotArgs &a, int phase, int was, 
 
 // ---- element-wise and stencil phases ----------------------------------------
 
-// the cells of a slot's elementwise phases: work items are (row, run of 256
+// The cells of a slot's elementwise phases: work items are (row, run of 256
 // columns), spread over all waves of the launch; each lane takes four
-// columns 64 apart
-template <typename F>
-__device__ __forceinline__ void for_cells(const SlotArgs &a, int gw, int nwaves, F fn)
-{
-    const int lane = threadIdx.x & 63;
-    const int runs = (a.nx + 255) / 256;
-    const int items = a.ny * runs;
-    for (int it = gw; it < items; it += nwaves) {
-        const int y = it / runs, x0 = (it - y * runs) * 256 + lane;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int x = x0 + 64 * j;
-            if (x < a.nx) fn(x, y);
-        }
-    }
-}
-
-// The same cells, K work items at a time, each cell split into `load`
+// columns 64 apart.  K work items at a time, each cell split into `load`
 // (reads and arithmetic, returning a value) and `store` (writes): every load
 // of the 4K cells is issued before the first store, so a wave has that many
 // cells' loads in flight instead of one cell's (the stores could alias the
@@ -526,6 +508,79 @@ __device__ __forceinline__ double defect_at(const T *u, int nx, int ny, int pitc
     const double n = y > 0 ? un : 0.0;
     *c_out = c;
     return ((e + w) + (s + n)) * 0.25 - c;
+}
+
+// A phase that is no pass, on the cells that `cells` goes over (a callable
+// taking `load` and `store`); fpar, cpar: the buffers of the FP32 field and
+// of the correction.  The maxima of a defect go to m and mr.
+template <typename Cells>
+__device__ __forceinline__ void element_phase(const SlotArgs &a, int phase, int fpar, int cpar, int fresh, int wide,
+                                              double &m, float &mr, Cells cells)
+{
+    if (phase == PH_DEFECT32 || phase == PH_DEFECT64) {
+        const bool first = phase == PH_DEFECT32;
+        const float *u32 = fpar ? a.alt : a.psi;
+        // the defect's maxima, and its outputs written through L2 (as the
+        // passes' field rows are, so the kernel's end has nothing to write
+        // back): the widened field and a cleared correction the first time
+        auto store = [&](int x, int y, const DefectCell &d) {
+            const size_t i = (size_t)y * a.pitch + x;
+            if (first) {
+                st_through(a.psi64 + i, d.c);
+                st_through(a.e + i, 0.0f);
+            }
+            // the correction solves' source, and its products with their
+            // two factors, formed here once instead of in every pass
+            const float f = d.fr ? (float)d.r : 0.0f;
+            st_through(a.r32 + i, f);
+            st_through(a.cdc + i, a.omega_dc * f);
+            if (a.lead_passes > 0) st_through(a.clead + i, a.omega_lead * f);
+            m = nan_max(m, d.fr ? fabs(d.r) : 0.0);
+            const float ac = fabsf((float)d.c);
+            mr = nan_maxf(mr, d.fr && ac >= 1e-30f ? fabsf((float)d.r) * __builtin_amdgcn_rcpf(ac) : 0.0f);
+        };
+        auto load = [&](const auto *u, int x, int y) {
+            DefectCell d;
+            d.r = defect_at(u, a.nx, a.ny, a.pitch, x, y, &d.c);
+            d.fr = a.mask[(size_t)y * a.pitch + x] != 0;
+            return d;
+        };
+        if (first)
+            cells([&](int x, int y) { return load(u32, x, y); }, store);
+        else
+            cells([&](int x, int y) { return load(a.psi64, x, y); }, store);
+    } else if (phase == PH_UPDATE) {
+        const float *ecur = cpar ? a.alt : a.e;
+        // ecur may be e itself: every cell's correction is read before any
+        // cell's is cleared
+        cells(
+            [&](int x, int y) {
+                const size_t i = (size_t)y * a.pitch + x;
+                return UpdateCell{a.psi64[i], ecur[i], a.mask[i] != 0};
+            },
+            [&](int x, int y, const UpdateCell &u) {
+                const size_t i = (size_t)y * a.pitch + x;
+                double v = u.v;
+                if (u.fr) {
+                    v = v + (double)u.e;
+                    st_through(a.psi64 + i, v);
+                }
+                st_through(a.psi + i, (float)v);
+                st_through(a.e + i, 0.0f);
+            });
+    } else {  // PH_FINISH
+        const bool copy = !fresh && fpar;
+        const bool widen = a.psi64 && a.polish && !wide;
+        if (copy || widen) {
+            const float *u = copy ? a.alt : a.psi;
+            cells([&](int x, int y) { return u[(size_t)y * a.pitch + x]; },
+                  [&](int x, int y, float v) {
+                      const size_t i = (size_t)y * a.pitch + x;
+                      if (copy) a.psi[i] = v;
+                      if (widen) a.psi64[i] = (double)v;
+                  });
+        }
+    }
 }
 
 // F: passes of S sweeps that one launch may do at once (1, 2 or 4)
@@ -610,75 +665,13 @@ __global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArg
         // a pass that does not check decides nothing: the next slot derives
         // its pass and buffers from its own slot number
         if (!check) return;
-    } else if (phase == PH_DEFECT32 || phase == PH_DEFECT64) {
-        reduce = true;
-        const bool first = phase == PH_DEFECT32;
-        const int fpar = hpar;
-        const float *u32 = fpar ? a.alt : a.psi;
-        // the defect's maxima, and its outputs written through L2 (as the
-        // passes' field rows are, so the kernel's end has nothing to write
-        // back): the widened field and a cleared correction the first time
-        auto store = [&](int x, int y, const DefectCell &d) {
-            const size_t i = (size_t)y * a.pitch + x;
-            if (first) {
-                st_through(a.psi64 + i, d.c);
-                st_through(a.e + i, 0.0f);
-            }
-            // the correction solves' source, and its products with their
-            // two factors, formed here once instead of in every pass
-            const float f = d.fr ? (float)d.r : 0.0f;
-            st_through(a.r32 + i, f);
-            st_through(a.cdc + i, a.omega_dc * f);
-            if (a.lead_passes > 0) st_through(a.clead + i, a.omega_lead * f);
-            m = nan_max(m, d.fr ? fabs(d.r) : 0.0);
-            const float ac = fabsf((float)d.c);
-            mr = nan_maxf(mr, d.fr && ac >= 1e-30f ? fabsf((float)d.r) * __builtin_amdgcn_rcpf(ac) : 0.0f);
-        };
-        auto load = [&](const auto *u, int x, int y) {
-            DefectCell d;
-            d.r = defect_at(u, a.nx, a.ny, a.pitch, x, y, &d.c);
-            d.fr = a.mask[(size_t)y * a.pitch + x] != 0;
-            return d;
-        };
-        if (first)
-            for_cells_batched<2>(a, gw, nwaves, [&](int x, int y) { return load(u32, x, y); }, store);
-        else
-            for_cells_batched<2>(a, gw, nwaves, [&](int x, int y) { return load(a.psi64, x, y); }, store);
-    } else if (phase == PH_UPDATE) {
-        const int cpar = hcpar;
-        const float *ecur = cpar ? a.alt : a.e;
-        // ecur may be e itself: every cell's correction is read before any
-        // cell's is cleared
-        for_cells_batched<2>(
-            a, gw, nwaves,
-            [&](int x, int y) {
-                const size_t i = (size_t)y * a.pitch + x;
-                return UpdateCell{a.psi64[i], ecur[i], a.mask[i] != 0};
-            },
-            [&](int x, int y, const UpdateCell &u) {
-                const size_t i = (size_t)y * a.pitch + x;
-                double v = u.v;
-                if (u.fr) {
-                    v = v + (double)u.e;
-                    st_through(a.psi64 + i, v);
-                }
-                st_through(a.psi + i, (float)v);
-                st_through(a.e + i, 0.0f);
-            });
-    } else {  // PH_FINISH
+    } else {
+        reduce = phase != PH_UPDATE && phase != PH_FINISH;
         // the FP32 field's buffer: a solve cut short between checks left it
         // where its last pass wrote
-        const int fpar = was == PH_PLAIN ? par : hpar;
-        const bool copy = !hfresh && fpar;
-        const bool widen = a.psi64 && a.polish && !hwide;
-        if (copy || widen) {
-            for_cells(a, gw, nwaves, [&](int x, int y) {
-                const size_t i = (size_t)y * a.pitch + x;
-                const float v = copy ? a.alt[i] : a.psi[i];
-                if (copy) a.psi[i] = v;
-                if (widen) a.psi64[i] = (double)v;
-            });
-        }
+        const int fpar = phase == PH_FINISH && was == PH_PLAIN ? par : hpar;
+        element_phase(a, phase, fpar, hcpar, hfresh, hwide, m, mr,
+                      [&](auto load, auto store) { for_cells_batched<2>(a, gw, nwaves, load, store); });
     }
 
     // maxima, then the ticket, one per workgroup: the block's maxima are
@@ -737,6 +730,288 @@ __global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArg
     __hip_atomic_exchange(&c->ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     controller(c, a, phase, was, forced, pass, par, bitsd(pr), bitsd(pq));
 }
+
+#ifndef TWG_DEPTH
+// ---- small grids: the whole solve in one workgroup's registers ---------------
+// A grid of at most 128 x 96 (or 64 x 128) cells is too small for the passes:
+// a launch of eight sweeps takes 6 us there, half of it the launch and the
+// first load, and every sweep of it is redone in the tiles' halos.  Here one
+// workgroup keeps the field in registers for a whole solve: a lane holds two
+// columns of a block of R rows, 64 lanes a row of up to 128 cells (NARROW: 32
+// lanes a row of up to 64, two blocks a wave), a half-sweep updates one of a
+// lane's two cells in every row, and the blocks' first and last rows go
+// through LDS, one barrier a half-sweep.  A half-sweep is bound by VALU issue
+// of the four waves (5 operations a row, 6 where the shift must stop between
+// two blocks: 84 of 140 ns at R = 8) and by what the inner rows do not hide
+// of the rows' way through LDS and the barrier.  The updates, the checks, the
+// control (on an LDS copy of the control block) and the elementwise phases
+// are those of the slots, so a field after N sweeps has the same bits.  A
+// launch ends after kResidentWork sweeps, so none runs long; the field is then
+// in psi (or e) and the next launch goes on.  4000 sweeps of 64 x 64 cells:
+// 3.32 to 1.12 ms; certified to 1e-9 (1068 sweeps, 64 x 32): 1.01 to 0.38 ms.
+constexpr int kResidentWork = 4096;
+constexpr int kCheckWork = 16;  // a check's share of that
+
+template <bool NARROW, int R>
+__global__ __launch_bounds__(256) void k_relax_resident(void *ctl, int slot, SlotArgs a)
+{
+    constexpr int LW = NARROW ? 32 : 64;  // lanes of a row
+    constexpr int B = 4 * (64 / LW);      // blocks of rows
+    RelaxCtl *cg = static_cast<RelaxCtl *>(ctl);
+    __shared__ RelaxCtl sc;
+    // boundary rows by colour (a checked field's two columns use both):
+    // block b's first and last row at [.][b + 1]; zeros above and below all
+    __shared__ float halo[2][B + 2][2][LW];
+    __shared__ double bm[4];
+    __shared__ float br[4];
+    const int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (static_cast<const RelaxHot *>(ctl)->phase == PH_DONE) return;
+    for (int i = tid; i < (int)(sizeof(RelaxCtl) / 4); i += 256)
+        reinterpret_cast<uint32_t *>(&sc)[i] = reinterpret_cast<const uint32_t *>(cg)[i];
+    for (int i = tid; i < (int)(sizeof(halo) / 4); i += 256) (&halo[0][0][0][0])[i] = 0.0f;
+
+    const int li = lane & (LW - 1), blk = NARROW ? 2 * wave + (lane >> 5) : wave;
+    const int x = 2 * li, y0 = blk * R;
+    // a neighbour across the two blocks of a wave is outside the grid
+    int32_t lm = li == 0 ? 0 : -1, rm = li == LW - 1 ? 0 : -1;
+    asm volatile("" : "+v"(lm), "+v"(rm));  // masks, not conditions: the shift folds into the AND
+    auto from_left = [&](float v) { return NARROW ? keep(shr1(v), lm) : shr1(v); };
+    auto from_right = [&](float v) { return NARROW ? keep(shl1(v), rm) : shl1(v); };
+    // A lane's cells in memory.  Each use forms its own (the empty asm): kept
+    // across the solve, the addresses and conditions of every cell would
+    // spill.
+    struct Cells {
+        int x, y, nx, ny, pitch;
+        __device__ bool in(int r, int j) const { return x + j < nx && y + r < ny; }
+        __device__ size_t at(int r, int j) const { return (size_t)(y + r) * pitch + x + j; }
+    };
+    auto cells_now = [&] {
+        Cells q{x, y0, a.nx, a.ny, a.pitch};
+        asm volatile("" : "+v"(q.x), "+v"(q.y));
+        return q;
+    };
+
+    uint32_t free0 = 0u, free1 = 0u;  // bit r: row r's cell is FREE
+    {
+        const Cells q = cells_now();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (q.in(r, 0) && a.mask[q.at(r, 0)]) free0 |= 1u << r;
+            if (q.in(r, 1) && a.mask[q.at(r, 1)]) free1 |= 1u << r;
+        }
+    }
+    float P0[R], P1[R];
+    auto load_cells = [&](const float *u, float (&v0)[R], float (&v1)[R]) {
+        const Cells q = cells_now();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v0[r] = q.in(r, 0) ? u[q.at(r, 0)] : 0.0f;
+            v1[r] = q.in(r, 1) ? u[q.at(r, 1)] : 0.0f;
+        }
+    };
+    auto store_cells = [&](float *u) {
+        const Cells q = cells_now();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (q.in(r, 0)) u[q.at(r, 0)] = P0[r];
+            if (q.in(r, 1)) u[q.at(r, 1)] = P1[r];
+        }
+    };
+    // n sweeps; upd_cell(r, j, ewn, s) updates the cell of column j in row r
+    auto sweeps = [&](int n, auto upd_cell) {
+        // the black cells of the boundary rows, then one barrier a half-sweep
+        halo[1][blk + 1][0][li] = P1[0];
+        halo[1][blk + 1][1][li] = P0[R - 1];
+        __syncthreads();
+        auto half = [&](auto C) __attribute__((always_inline)) {
+            constexpr int c = decltype(C)::value;
+            const float up = halo[1 - c][blk][1][li], dn = halo[1 - c][blk + 2][0][li];
+            auto row = [&](auto Rr) __attribute__((always_inline)) {
+                constexpr int r = decltype(Rr)::value;
+                constexpr int rn = r > 0 ? r - 1 : 0, rs = r + 1 < R ? r + 1 : R - 1;
+                if constexpr (((r + c) & 1) == 0) {
+                    const float ewn = (from_left(P1[r]) + P1[r]) + (r > 0 ? P0[rn] : up);
+                    upd_cell(std::integral_constant<int, r>{}, std::integral_constant<int, 0>{}, ewn,
+                             r + 1 < R ? P0[rs] : dn);
+                } else {
+                    const float ewn = (from_right(P0[r]) + P0[r]) + (r > 0 ? P1[rn] : up);
+                    upd_cell(std::integral_constant<int, r>{}, std::integral_constant<int, 1>{}, ewn,
+                             r + 1 < R ? P1[rs] : dn);
+                }
+            };
+            // half of the inner rows while the neighbours' rows arrive, the
+            // boundary rows, and the rest while those go out
+            static_for(std::make_integer_sequence<int, R / 2 - 1>{},
+                       [&](auto U) { row(std::integral_constant<int, decltype(U)::value + 1>{}); });
+            row(std::integral_constant<int, 0>{});
+            row(std::integral_constant<int, R - 1>{});
+            halo[c][blk + 1][0][li] = c == 0 ? P0[0] : P1[0];
+            halo[c][blk + 1][1][li] = c == 0 ? P1[R - 1] : P0[R - 1];
+            __builtin_amdgcn_sched_barrier(0);
+            static_for(std::make_integer_sequence<int, R / 2 - 1>{},
+                       [&](auto U) { row(std::integral_constant<int, decltype(U)::value + R / 2>{}); });
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+        };
+        for (int k = 0; k < n; ++k) {
+            half(std::integral_constant<int, 0>{});
+            half(std::integral_constant<int, 1>{});
+        }
+    };
+    // the workgroup's maxima to thread 0, which decides
+    auto decide = [&](int phase, int pass, double m, float mr) {
+        m = wave_max(m);
+        mr = wave_maxf(mr);
+        __syncthreads();
+        if (lane == 0) {
+            bm[wave] = m;
+            br[wave] = mr;
+        }
+        __syncthreads();
+        if (tid == 0) {
+            m = nan_max(nan_max(bm[0], bm[1]), nan_max(bm[2], bm[3]));
+            mr = nan_maxf(nan_maxf(br[0], br[1]), nan_maxf(br[2], br[3]));
+            // decisions are not published: the host queues launches, not slots
+            controller_on(&sc, a, slot, nullptr, phase, phase, false, pass, 0, m, (double)mr);
+            // fields stay in psi and e, and the checked pass is still to run
+            sc.h.parity = sc.h.cparity = 0;
+            if (sc.h.phase == phase && (phase == PH_PLAIN || phase == PH_CORR)) sc.h.pass = pass;
+        }
+        __syncthreads();
+    };
+    const int S = __builtin_amdgcn_readfirstlane(cg->c.S);
+    int left = kResidentWork;
+    __syncthreads();
+    for (;;) {
+        const int phase = __builtin_amdgcn_readfirstlane(sc.h.phase);
+        if (phase == PH_DONE || left <= 0) break;
+        if (phase != PH_PLAIN && phase != PH_CORR) {
+            double m = 0.0;
+            float mr = 0.0f;
+            element_phase(a, phase, 0, 0, __builtin_amdgcn_readfirstlane(sc.h.fresh),
+                          __builtin_amdgcn_readfirstlane(sc.h.wide), m, mr, [&](auto load, auto store) {
+                              using V = decltype(load(0, 0));
+                              constexpr int K = 4;  // rows at a time
+                              Cells c = cells_now();
+#pragma unroll 1
+                              for (int q = 0; q < R; q += K, c.y += K) {
+                                  V v[K][2];
+#pragma unroll
+                                  for (int r = 0; r < K; ++r)
+#pragma unroll
+                                      for (int j = 0; j < 2; ++j)
+                                          v[r][j] = load(c.in(r, j) ? c.x + j : 0, c.in(r, j) ? c.y + r : 0);
+#pragma unroll
+                                  for (int r = 0; r < K; ++r)
+#pragma unroll
+                                      for (int j = 0; j < 2; ++j)
+                                          if (c.in(r, j)) store(c.x + j, c.y + r, v[r][j]);
+                              }
+                          });
+            left -= kCheckWork;
+            decide(phase, 0, m, mr);  // its barriers also order the phases' stores and loads
+            continue;
+        }
+        const bool corr = phase == PH_CORR;
+        float *field = corr ? a.e : a.psi;
+        load_cells(field, P0, P1);
+        for (;;) {
+            const int pass = __builtin_amdgcn_readfirstlane(sc.h.pass);
+            const int next_check = __builtin_amdgcn_readfirstlane(sc.h.next_check);
+            // passes of one factor, within this launch's work
+            const bool lead = corr && pass < a.lead_passes;
+            int n = lead ? min(next_check, a.lead_passes) - pass : next_check - pass;
+            n = min(max(n, 0), (max(left, 0) + S - 1) / S);
+            if (n > 0) {
+                if (corr) {
+                    const float om = lead ? a.omega_lead : a.omega_dc, quarter = om * 0.25f;
+                    SrcConst<float> k0[R], k1[R];
+                    float c0[R], c1[R];
+                    load_cells(lead ? a.clead : a.cdc, c0, c1);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        const float a0 = free0 >> r & 1u ? quarter : 0.0f, a1 = free1 >> r & 1u ? quarter : 0.0f;
+                        k0[r] = {a0, fused(a0, -4.0f, 1.0f), c0[r]};
+                        k1[r] = {a1, fused(a1, -4.0f, 1.0f), c1[r]};
+                    }
+                    sweeps(n * S, [&](auto Rr, auto J, float ewn, float s) __attribute__((always_inline)) {
+                        constexpr int r = decltype(Rr)::value;
+                        float &p = decltype(J)::value ? P1[r] : P0[r];
+                        p = upd_src(p, ewn, s, decltype(J)::value ? k1[r] : k0[r]);
+                    });
+                } else {
+                    float w0[R], w1[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        w0[r] = free0 >> r & 1u ? a.omega : 0.0f;
+                        w1[r] = free1 >> r & 1u ? a.omega : 0.0f;
+                    }
+                    sweeps(n * S, [&](auto Rr, auto J, float ewn, float s) __attribute__((always_inline)) {
+                        constexpr int r = decltype(Rr)::value;
+                        float &p = decltype(J)::value ? P1[r] : P0[r];
+                        p = upd(p, ewn, s, decltype(J)::value ? w1[r] : w0[r]);
+                    });
+                }
+                left -= n * S;
+            }
+            if (pass + n < next_check) {
+                __syncthreads();
+                if (tid == 0) sc.h.pass = pass + n;
+                __syncthreads();
+                if (left <= 0) break;
+                continue;
+            }
+            // the residual of the field at this check, in FP64, the
+            // expression of the passes' checks (its source: the FP32 defect)
+            halo[0][blk + 1][0][li] = P0[0];
+            halo[1][blk + 1][0][li] = P1[0];
+            halo[0][blk + 1][1][li] = P0[R - 1];
+            halo[1][blk + 1][1][li] = P1[R - 1];
+            __syncthreads();
+            double m = 0.0;
+            float mr = 0.0f;
+            {
+                const float up0 = halo[0][blk][1][li], up1 = halo[1][blk][1][li];
+                const float dn0 = halo[0][blk + 2][0][li], dn1 = halo[1][blk + 2][0][li];
+                float f0[R], f1[R];
+                if (corr) load_cells(a.r32, f0, f1);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const float n0 = r > 0 ? P0[r > 0 ? r - 1 : 0] : up0, n1 = r > 0 ? P1[r > 0 ? r - 1 : 0] : up1;
+                    const float s0 = r + 1 < R ? P0[r + 1 < R ? r + 1 : 0] : dn0;
+                    const float s1 = r + 1 < R ? P1[r + 1 < R ? r + 1 : 0] : dn1;
+                    auto cell = [&](bool fr, float c, float e, float w, float nn, float ss, float f) {
+                        double g = (((double)e + (double)w) + ((double)ss + (double)nn)) * 0.25;
+                        if (corr) g = g + (double)f;
+                        const double d = g - (double)c;
+                        const float ac = fabsf(c);
+                        m = nan_max(m, fr ? fabs(d) : 0.0);
+                        mr = nan_maxf(mr, fr && ac >= 1e-30f ? fabsf((float)d) * __builtin_amdgcn_rcpf(ac) : 0.0f);
+                    };
+                    const float w = from_left(P1[r]), e = from_right(P0[r]);
+                    cell(free0 >> r & 1u, P0[r], P1[r], w, n0, s0, corr ? f0[r] : 0.0f);
+                    cell(free1 >> r & 1u, P1[r], e, P0[r], n1, s1, corr ? f1[r] : 0.0f);
+                }
+            }
+            left -= kCheckWork;
+            decide(phase, next_check, m, mr);
+            if (__builtin_amdgcn_readfirstlane(sc.h.phase) != phase) break;
+        }
+        store_cells(field);
+        __syncthreads();
+    }
+    // the control block (its maxima and ticket are not in use here), then the
+    // word a blocking caller waits for
+    for (int i = tid; i < (int)(offsetof(RelaxCtl, part) / 4); i += 256)
+        reinterpret_cast<uint32_t *>(cg)[i] = reinterpret_cast<const uint32_t *>(&sc)[i];
+    if (tid == 0) {
+        const bool done = sc.h.phase == PH_DONE;
+        *reinterpret_cast<volatile unsigned long long *>(a.mirror) = done ? 1ull << 63 : (unsigned long long)(slot + 2);
+        __threadfence_system();
+    }
+}
+#endif
 
 __global__ void k_relax_begin(RelaxCtl *c, RelaxConfig cfg)
 {
@@ -801,6 +1076,29 @@ TWG_SLOT_DEPTH(5) TWG_SLOT_DEPTH(6) TWG_SLOT_DEPTH(7) TWG_SLOT_DEPTH(8)
 #undef TWG_SLOT_DEPTH
 
 size_t relax_ctl_bytes() { return (sizeof(RelaxCtl) + 255) & ~size_t(255); }
+
+// Blocks of 8, 16 and 24 rows take 0.28 (0.26 with 64 lanes a row), 0.45
+// (0.40) and 0.60 us a sweep where the passes take 0.82 to 0.85; at 32 rows a
+// block (128 x 128) it is 0.76, and certified solves gain nothing.
+bool relax_resident(int nx, int ny) { return (nx <= 128 && ny <= 96) || (nx <= 64 && ny <= 128); }
+
+int launch_relax_resident(const SlotArgs &a, hipStream_t st)
+{
+    if (!relax_resident(a.nx, a.ny)) return TWG_EUNSUPPORTED;
+    // the fewest rows a block that hold the grid
+    const auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(1), dim3(256), 0, st, a.ctl, a.slot, a); };
+    if (a.nx <= 64) {
+        if (a.ny <= 64) go(k_relax_resident<true, 8>);
+        else go(k_relax_resident<true, 16>);
+    } else if (a.ny <= 32) {
+        go(k_relax_resident<false, 8>);
+    } else if (a.ny <= 64) {
+        go(k_relax_resident<false, 16>);
+    } else {
+        go(k_relax_resident<false, 24>);
+    }
+    return last_status();
+}
 
 int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st)
 {

@@ -220,6 +220,10 @@ struct SlotArgs {
 size_t relax_ctl_bytes();
 int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st);
 int launch_relax_slot(const SlotArgs &a, int S, hipStream_t st);
+// a solve whose grid one workgroup can keep (relax_resident): one such launch
+// goes on until the solve ends or it has done its share of sweeps
+bool relax_resident(int nx, int ny);
+int launch_relax_resident(const SlotArgs &a, hipStream_t st);
 // passes a slot may fuse at S sweeps per pass (their kernels exist)
 constexpr int slot_fuse_limit(int S) { return S == 2 ? 4 : S == 4 ? 2 : 1; }
 
