@@ -357,7 +357,9 @@ typedef struct {
  * from pinned memory).  Sweeps per tile load and rows per tile come from
  * hpf_autotune_batched if it ran on this context, else from the
  * autotuned entry of the largest grid (or params->sweeps_per_pass /
- * rows_per_tile); each grid's SOR factor is params->omega, else its size's
+ * rows_per_tile); the rows are the most a tile takes: as grids end, lower
+ * tiles keep the device's SIMDs evenly loaded (no result depends on them).
+ * Each grid's SOR factor is params->omega, else its size's
  * autotuned factor, else its open-rectangle optimum.  init: HPF_INIT_KEEP,
  * HALF or ZERO; polish must be 0.  stats: host array of n entries, or NULL.
  * Blocking.  Returns TWG_OK when every grid converged, else

@@ -683,18 +683,9 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     }
     if (p.sweeps_per_pass) S = p.sweeps_per_pass;
     const int VW = 128 - 4 * S;
-    if (ctx->batch_S <= 0 && !ctx->tuned.count({grids[big].nx, grids[big].ny})) {
-        // an untuned batch: the lowest tiles that fit the kernel's three
-        // waves per SIMD, at most 128 rows (lower tiles spend more row steps
-        // on their halo, taller ones leave SIMDs idle)
-        const long long waves = 3LL * 4 * std::max(1, ctx->num_cu);
-        for (RH = 8; RH < 128; RH *= 2) {
-            long long tiles = 0;
-            for (int k = 0; k < n; ++k)
-                tiles += (long long)((grids[k].nx + VW - 1) / VW) * ((grids[k].ny + RH - 1) / RH);
-            if (tiles <= waves) break;
-        }
-    }
+    // an untuned batch: any height up to 128 rows, as the device chooses (higher
+    // tiles gain under 10 % of a row step and leave less to choose from)
+    if (ctx->batch_S <= 0 && !ctx->tuned.count({grids[big].nx, grids[big].ny})) RH = 128;
     if (p.rows_per_tile) RH = p.rows_per_tile;
     bool even = true;
     int max_pitch = 1;
@@ -729,6 +720,8 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         }
         for (int bx = 0; bx < (grids[k].nx + 63) / 64; ++bx) bl.push_back(make_int2(k, bx));
     }
+    // lower tiles (chosen at the events) may be as many as three waves a SIMD
+    if (lds.size() < (size_t)n) max_tiles = std::max(max_tiles, 3LL * 4 * std::max(1, ctx->num_cu));
     if (max_tiles > INT_MAX / 2 || (long long)bl.size() * 32 > INT_MAX / 2)
         return set_err(ctx, TWG_EUNSUPPORTED, "batch too large");
     // device layout: grids | blocks | LDS list | hdr | run | ctl | tile table | rmax | rrel | stats
@@ -781,6 +774,8 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     a.n = n;
     a.S = S;
     a.RH = RH;
+    a.max_tiles = (int)max_tiles;
+    a.simds = 4 * std::max(1, ctx->num_cu);
     a.slot = 0;
     a.final_slot = 0;
     a.quantum = p.check_passes > 0 ? 1 : kBatchQuantum;
@@ -803,16 +798,15 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     rc = launch_batch_begin(a, st);
     if (!rc) rc = launch_batch_lds(a, lds_bytes, &ctx->lds_attr, st);
     if (rc) return set_err(ctx, rc, "batch begin launch failed");
-    const int mt = (int)max_tiles;
 
     if (slots > 0) {
         for (int64_t k = 0; k < slots; ++k) {
             a.slot = (int)k;
-            if ((rc = launch_batch_slot(a, mt, even, st))) return set_err(ctx, rc, "batch slot launch failed");
+            if ((rc = launch_batch_slot(a, even, st))) return set_err(ctx, rc, "batch slot launch failed");
         }
         a.final_slot = 1;
         a.slot = (int)slots;
-        rc = launch_batch_slot(a, mt, even, st);
+        rc = launch_batch_slot(a, even, st);
         return rc ? set_err(ctx, rc, "batch slot launch failed") : TWG_OK;
     }
 
@@ -836,7 +830,7 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         if (queued < target) {
             if (queued >= INT_MAX - 8) return set_err(ctx, TWG_EDEVICE, "batch slot count overflow");
             a.slot = (int)queued;
-            if ((rc = launch_batch_slot(a, mt, even, st))) return set_err(ctx, rc, "batch slot launch failed");
+            if ((rc = launch_batch_slot(a, even, st))) return set_err(ctx, rc, "batch slot launch failed");
             ++queued;
             continue;
         }

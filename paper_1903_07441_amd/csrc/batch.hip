@@ -32,7 +32,7 @@ namespace twg {
 // grid's parity0 is the buffer its result ended in
 struct GridRun {
     int32_t pass0, run_slot, next_check, parity0;
-    int32_t strips, tiles, mode, status;
+    int32_t strips, ny, mode, status;
 };
 // per grid, controller only
 struct GridCtl {
@@ -54,7 +54,8 @@ struct alignas(32) BatchHdr {
     int32_t total_tiles;  // tiles of the active grids
     int32_t next_event;   // slot of the next event (a check of some grid)
     int32_t events;
-    int32_t pad[3];
+    int32_t rows;         // rows per tile of the next slots
+    int32_t pad[2];
 };
 enum : int32_t { BP_RUN = 0, BP_FINISH = 1, BP_DONE = 2 };
 enum : int32_t { BG_ACTIVE = 0, BG_DONE = 1 };
@@ -178,21 +179,87 @@ __device__ void publish_b(unsigned long long *mirror, const BatchHdr *h, int slo
     __threadfence_system();
 }
 
-// the active list (every thread of one workgroup): the tiles of the grids
+// Tile heights a batch chooses from at each event: a.RH rows, the most, and
+// lower ones that fill whole pipeline windows (2S + 2 row steps of h + 4S, so
+// that none pads).
+constexpr int kHeights = 16;
+__device__ __forceinline__ int tile_height(const BatchArgs &a, int j)
+{
+    const int NW = 2 * a.S + 2;
+    const int kmax = (a.RH + 4 * a.S - 1) / NW;  // windows of the highest below a.RH
+    const int stride = max(kmax - 2, 0) / kHeights + 1;
+    const int k = kmax - (j - 1) * stride;
+    return j == 0 ? a.RH : k >= 3 ? k * NW - 4 * a.S : 0;
+}
+// Row steps the slowest SIMD spends on a slot of `tiles` tiles of h rows: the
+// tiles share the SIMDs' issue slots (up to three waves each), so what counts
+// is the most any SIMD has, and past three each a tail of one more.  The
+// first turn of a tile's ring (two windows) runs half the stages.
+__device__ __forceinline__ int slot_cost(const BatchArgs &a, int h, int tiles)
+{
+    const int NW = 2 * a.S + 2;
+    const int steps = (h + 4 * a.S + NW - 1) / NW * NW - NW;
+    const long long rounds16 = tiles <= 3 * a.simds ? 16ll * ((tiles + a.simds - 1) / a.simds)
+                                                    : 16ll * tiles / a.simds + 16;
+    return (int)min(rounds16 * steps, (long long)INT_MAX);
+}
+
+// The active list (every thread of one workgroup): the tiles of the grids
 // still active, in grid order, and the slot of the next check of any of
-// them; no grid left ends the run
+// them; no grid left ends the run.  The tiles' height is the one that loads
+// the SIMDs most evenly: 64 grids of 64 to 1024 cells a side start with 1573
+// tiles of 128 rows on 1024 SIMDs (two on half of them, one on the rest; with
+// 112 rows 2002, two on nearly all) and end with a few dozen.  With the tiles
+// that are left spread over all XCDs (a fixed mapping of the first launch's
+// blocks left most XCDs idle in the end), a late slot went from 28 to 10 us,
+// a first one from 51 to 45, and the batch from 8.0 to 5.5 ms.
 __device__ void build_list(const BatchArgs &a, BatchHdr *h, int slot)
 {
     __shared__ int gsum[256], tsum[256], smin[256];
+    __shared__ int total[kHeights], height[kHeights];
+    __shared__ int rows_s;
     const int tid = threadIdx.x;
     const int per = (a.n + 255) / 256;
     const int k0 = min(tid * per, a.n), k1 = min(k0 + per, a.n);
+    if (tid < kHeights) {
+        total[tid] = 0;
+        height[tid] = tile_height(a, tid);
+    }
+    __syncthreads();
+    // tiles of each height: a thread takes one height and every 16th grid
+    {
+        const int j = tid % kHeights, hj = height[j];
+        int mine = 0;
+#pragma unroll 4
+        for (int k = tid / kHeights; k < a.n; k += 256 / kHeights) {
+            const GridRun gr = a.run[k];
+            const int nt = gr.strips * ((gr.ny + max(hj, 1) - 1) / max(hj, 1));
+            mine += gr.mode == BG_ACTIVE ? nt : 0;
+        }
+        if (hj > 0 && mine) atomicAdd(&total[j], mine);
+    }
+    __syncthreads();
+    if (tid < 64) {
+        // the cheapest height; of equals the highest
+        const int j = min(tid, kHeights - 1), rows = height[j];
+        int cost = rows > 0 && (j == 0 || total[j] <= a.max_tiles) ? slot_cost(a, rows, total[j]) : INT_MAX, best = j;
+        for (int o = 1; o < kHeights; o <<= 1) {
+            const int c = __shfl_xor(cost, o), q = __shfl_xor(best, o);
+            if (c < cost || (c == cost && q < best)) {
+                cost = c;
+                best = q;
+            }
+        }
+        if (tid == 0) rows_s = height[best];
+    }
+    __syncthreads();
+    const int rows = rows_s;
     int cnt = 0, tiles = 0, nxt = INT_MAX;
     for (int k = k0; k < k1; ++k) {
         const GridRun gr = a.run[k];
         if (gr.mode != BG_ACTIVE) continue;
         ++cnt;
-        tiles += gr.tiles;
+        tiles += gr.strips * ((gr.ny + rows - 1) / rows);
         nxt = min(nxt, gr.run_slot + (gr.next_check - gr.pass0));
     }
     gsum[tid] = cnt;
@@ -210,19 +277,30 @@ __device__ void build_list(const BatchArgs &a, BatchHdr *h, int slot)
         smin[tid] = min(smin[tid], v3);
         __syncthreads();
     }
-    // the tile table of the next slots: entry i = (grid, tile of the grid)
+    // the tile table of the next slots: entry i = (grid, tile of the grid);
+    // a wave writes its lanes' grids one after the other, all lanes at once
     int tpos = tsum[tid] - tiles;
-    for (int k = k0; k < k1; ++k) {
-        const GridRun gr = a.run[k];
-        if (gr.mode != BG_ACTIVE) continue;
-        for (int t = 0; t < gr.tiles; ++t) a.tiles[tpos + t] = make_int2(k, t);
-        tpos += gr.tiles;
+    for (int i = 0; i < per; ++i) {
+        const int k = k0 + i;
+        int nt = 0;
+        if (k < k1) {
+            const GridRun gr = a.run[k];
+            if (gr.mode == BG_ACTIVE) nt = gr.strips * ((gr.ny + rows - 1) / rows);
+        }
+        for (unsigned long long left = __ballot(nt > 0); left; left &= left - 1) {
+            const int l = __builtin_amdgcn_readfirstlane(__ffsll((long long)left) - 1);
+            const int nl = __builtin_amdgcn_readlane(nt, l), pl = __builtin_amdgcn_readlane(tpos, l);
+            const int kl = __builtin_amdgcn_readlane(k, l);
+            for (int t = tid & 63; t < nl; t += 64) a.tiles[pl + t] = make_int2(kl, t);
+        }
+        tpos += nt;
     }
     __syncthreads();
     if (tid == 0) {
         const int n_act = gsum[255];
         h->n_active = n_act;
         h->total_tiles = tsum[255];
+        h->rows = rows;
         if (n_act == 0) {
             h->phase = BP_FINISH;
             h->next_event = slot + 1;
@@ -268,6 +346,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
     const BatchHdr h = *hp;
     const int phase = __builtin_amdgcn_readfirstlane(h.phase);
     const int total = __builtin_amdgcn_readfirstlane(h.total_tiles);
+    const int rows = __builtin_amdgcn_readfirstlane(h.rows);
     if (phase == BP_DONE) return;
     const int slot = a.slot;
     const bool forced = a.final_slot && phase == BP_RUN;
@@ -276,8 +355,10 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
     if (phase == BP_FINISH && slot != __builtin_amdgcn_readfirstlane(h.next_event)) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = xcd_remap(blockIdx.x, gridDim.x);
-    const int gw = b * 4 + wave;
+    // the blocks that have tiles (the launch is sized for the most) are spread
+    // over all XCDs
+    const int used = (total + 3) / 4;
+    const int gw = (finish ? (int)blockIdx.x : (int)blockIdx.x < used ? xcd_remap(blockIdx.x, used) : used) * 4 + wave;
 
     if (!finish) {
         if (gw < total) {
@@ -296,7 +377,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
             float *src = par ? x1 : x0, *dst = par ? x0 : x1;
             const uint8_t *m = a.mask + g.off;
             constexpr int VW = 128 - 4 * S;
-            const int ybeg = seg * a.RH, yend = min(ybeg + a.RH, g.ny);
+            const int ybeg = seg * rows, yend = min(ybeg + rows, g.ny);
             const int xs = strip * VW - 2 * S;
             if (check) {
                 double rm = 0.0;
@@ -332,7 +413,7 @@ __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
             if (!par) continue;
             const BatchGrid g = a.grids[bk.x];
             const int x = bk.y * 64 + lane;
-            const int rows = (g.ny + 31) / 32, y0 = c * rows, y1 = min(y0 + rows, g.ny);
+            const int chunk = (g.ny + 31) / 32, y0 = c * chunk, y1 = min(y0 + chunk, g.ny);
             if (x < g.nx)
                 for (int y = y0; y < y1; ++y) {
                     const size_t i = (size_t)g.off + (size_t)y * g.pitch + x;
@@ -525,7 +606,7 @@ __global__ __launch_bounds__(256) void k_batch_begin(BatchArgs a)
         const BatchGrid g = a.grids[k];
         GridRun gr;
         gr.strips = (g.nx + VW - 1) / VW;
-        gr.tiles = g.lds ? 0 : gr.strips * ((g.ny + a.RH - 1) / a.RH);
+        gr.ny = g.ny;
         gr.pass0 = 0;
         gr.run_slot = 0;
         gr.next_check = 0;
@@ -603,11 +684,11 @@ int launch_batch_lds(const BatchArgs &a, size_t lds_bytes, size_t *lds_attr, hip
     return last_status_b();
 }
 
-int launch_batch_slot(const BatchArgs &a, int max_tiles, bool even, hipStream_t st)
+int launch_batch_slot(const BatchArgs &a, bool even, hipStream_t st)
 {
     // one wave per tile of the whole batch (the finishing slot's copy loops
     // over its items with the same waves)
-    const int blocks = std::max(1, (max_tiles + 3) / 4);
+    const int blocks = std::max(1, (a.max_tiles + 3) / 4);
     int rc;
     switch (a.S) {
     case 1: rc = launch_batch_slot_depth<1>(a, blocks, even, st); break;

@@ -236,7 +236,9 @@ struct BatchArgs {
     const BatchGrid *grids;  // n descriptors
     const int2 *blocks;      // static (grid, 64-column block) list of every grid
     int n_blocks, n;
-    int S, RH;               // sweeps per pass, output rows per tile
+    int S, RH;               // sweeps per pass, output rows per tile (at most)
+    int max_tiles;           // entries of the tile table, and a slot's waves
+    int simds;               // SIMDs of the device
     int slot, final_slot;    // this launch's number; 1: finish what is left
     int quantum;             // checks only at slots that are multiples of this
     int check_passes;        // > 0: a check every this many passes
@@ -258,7 +260,7 @@ size_t batch_hdr_bytes();
 size_t batch_run_bytes();
 size_t batch_ctl_bytes();
 int launch_batch_begin(const BatchArgs &a, hipStream_t st);
-int launch_batch_slot(const BatchArgs &a, int max_tiles, bool even, hipStream_t st);
+int launch_batch_slot(const BatchArgs &a, bool even, hipStream_t st);
 // LDS bytes k_batch_lds needs for a grid of `cells` cells; the solve of the
 // LDS grids (one workgroup each), launched after launch_batch_begin
 size_t batch_lds_bytes(long long cells);

@@ -1,6 +1,7 @@
 """The batch's control launches (only where a check can be): solves that end
 at every distance from the checks' quantum, at a sweep budget or at a fixed
-number of slots, and the residual a check reports."""
+number of slots, and the residual a check reports; and the heights the device
+chooses for the tiles."""
 import numpy as np
 import pytest
 
@@ -64,6 +65,30 @@ def test_budget_ends_between_events(ctx, passes, asynchronous):
         assert np.array_equal(u, one.cpu().numpy()), passes
         # every operation of the check is the reference's: the same bits
         assert st["residual"] == _residual(c, u), (passes, st)
+
+
+# the least height, below and at the first and second heights of whole windows
+# (2 (S + 1) k - 4 S rows), and more rows than any grid has
+@pytest.mark.parametrize("S,rows", [(8, 2), (8, 20), (8, 22), (8, 24), (8, 40), (8, 42), (8, 128), (8, 2000), (1, 2),
+                                    (1, 8), (1, 10), (1, 500), (3, 12), (3, 14), (3, 128), (4, 0), (7, 0)])
+def test_chosen_tile_heights_give_the_same_bits(ctx, S, rows):
+    rng = np.random.default_rng(S * 1000 + rows)
+    descs, flat, at = [], [], 0
+    for nx, ny in [(64, 64), (33, 201), (300, 7), (130, 257), (128, 1)] * 3:
+        c = np.zeros((ny, nx), np.uint8)
+        c[rng.random(c.shape) < 0.05] = 1
+        c[ny // 2, nx // 2] = 3
+        descs.append((nx, ny, nx, at))
+        flat.append(c)
+        at += c.size
+    dc = torch.as_tensor(np.concatenate([c.ravel() for c in flat])).cuda()
+    psi = torch.zeros(at, dtype=torch.float32, device="cuda")
+    stats = ctx.relax_batched(dc, psi, descs, tol=1e-6, omega=1.5, sweeps_per_pass=S, rows_per_tile=rows)
+    for (nx, ny, _, o), c, st in zip(descs, flat, stats):
+        dcl = torch.as_tensor(c).cuda()
+        one = torch.where(dcl == 3, 1.0, torch.where(dcl == 0, 0.5, 0.0)).float()
+        ctx.sweeps(dcl, one, 1.5, st["sweeps"], tiled=False)
+        assert st["status"] == 0 and torch.equal(one.view(-1), psi[o:o + nx * ny]), (nx, ny, st)
 
 
 @pytest.mark.parametrize("bad", [float("nan"), float("inf")])
