@@ -617,7 +617,6 @@ __global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArg
     const int phase = forced ? (int)PH_FINISH : was;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int gw = xcd_remap(blockIdx.x, a.blocks) * 4 + wave;
     const int nwaves = a.blocks * 4;
     double m = 0.0;
     float mr = 0.0f;
@@ -631,6 +630,9 @@ __global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArg
         float *src = par ? a.alt : x0, *dst = par ? x0 : a.alt;
         const float om = corr ? (pass < a.lead_passes ? a.omega_lead : a.omega_dc) : a.omega;
         const SlotTiling t = a.tiling[F > 1 ? level : 0];
+        // this tiling's blocks, spread over all XCDs
+        const int used = (t.tiles + 3) / 4;
+        const int gw = ((int)blockIdx.x < used ? xcd_remap(blockIdx.x, used) : used) * 4 + wave;
         if (gw < t.tiles) {
             const int strip = gw % t.strips, seg = gw / t.strips;
             const int ybeg = seg * t.RH, yend = min(ybeg + t.RH, a.ny);
@@ -671,7 +673,10 @@ __global__ __launch_bounds__(256) void k_relax_slot(void *ctl, int slot, SlotArg
         // where its last pass wrote
         const int fpar = phase == PH_FINISH && was == PH_PLAIN ? par : hpar;
         element_phase(a, phase, fpar, hcpar, hfresh, hwide, m, mr,
-                      [&](auto load, auto store) { for_cells_batched<2>(a, gw, nwaves, load, store); });
+                      [&](auto load, auto store) {
+                          const int gw = xcd_remap(blockIdx.x, a.blocks) * 4 + wave;
+                          for_cells_batched<2>(a, gw, nwaves, load, store);
+                      });
     }
 
     // maxima, then the ticket, one per workgroup: the block's maxima are
