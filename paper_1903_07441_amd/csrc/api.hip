@@ -9,6 +9,7 @@
 #include <mutex>
 #include <vector>
 
+#include "cell_setup.h"
 #include "twg_internal.h"
 
 // Scratch of hpf_relax_async_noalloc, for callers that cannot allocate: one
@@ -507,9 +508,6 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     // an asynchronous call's slots are its caller's budget of passes: one each
     const int fuse = slots > 0 ? 1 : pl.fuse;
 
-    rc = launch_field_init(cls, psi, g.nx, g.ny, g.pitch, p.init, p.goal_x, p.goal_y, st);
-    if (!rc) rc = launch_fmask(cls, bufs.fmask, g.nx, g.ny, g.pitch, st);
-    if (rc) return set_err(ctx, rc, "relaxation set-up launch failed");
     RelaxConfig cfg;
     cfg.tol = p.tol;
     cfg.need = p.polish ? (p.tol_cert > 0.0 ? std::min(p.tol, p.tol_cert / wb) : p.tol) : 0.0;
@@ -525,7 +523,8 @@ int relax_device(twg_ctx *ctx, const twg_grid &g, const uint8_t *cls, float *psi
     cfg.max_rounds = kMaxRounds;
     cfg.fuse = fuse;
     cfg.kept = cfg.polish && p.init == HPF_INIT_KEEP ? 1 : 0;
-    rc = launch_relax_begin(ctl, cfg, st);
+    rc = launch_relax_begin(ctl, cfg, CellSetup{cls, psi, bufs.fmask, g.nx, g.ny, g.pitch, p.init, p.goal_x, p.goal_y},
+                            st);
     if (rc) return set_err(ctx, rc, "relaxation begin launch failed");
 
     SlotArgs a;
@@ -763,10 +762,6 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
         ctx->batch_sig = std::move(sig);
     }
     uint8_t *const fmask = static_cast<uint8_t *>(ctx->fmask);
-    rc = launch_field_init_batch(cls, psi, d_grids, d_blocks, (int)bl.size(), p.init, st);
-    if (!rc) rc = launch_fmask_batch(cls, fmask, d_grids, d_blocks, (int)bl.size(), st);
-    if (rc) return set_err(ctx, TWG_EDEVICE, "batch set-up failed");
-
     BatchArgs a;
     a.grids = d_grids;
     a.blocks = d_blocks;
@@ -795,7 +790,9 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     a.mirror = nullptr;
     a.lds_list = d_lds;
     a.n_lds = (int)lds.size();
-    rc = launch_batch_begin(a, st);
+    int most_rows = 1;
+    for (int k = 0; k < n; ++k) most_rows = std::max(most_rows, (int)grids[k].ny);
+    rc = launch_batch_begin(a, cls, p.init, most_rows, st);
     if (!rc) rc = launch_batch_lds(a, lds_bytes, &ctx->lds_attr, st);
     if (rc) return set_err(ctx, rc, "batch begin launch failed");
 

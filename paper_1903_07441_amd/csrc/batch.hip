@@ -19,6 +19,7 @@
 // returns at once.  When no grid is left, the next slot copies back every
 // field that ended in the partner buffer, and the next control launch writes
 // the per-grid statistics.
+#include "cell_setup.h"
 #include "stream_tile.h"
 
 #include <algorithm>
@@ -596,10 +597,24 @@ __global__ __launch_bounds__(kLdsThreads) void k_batch_lds(BatchArgs a)
     }
 }
 
-// set-up of a batch solve (one workgroup): every grid active, checking its
-// initial field in slot 0
-__global__ __launch_bounds__(256) void k_batch_begin(BatchArgs a)
+// Set-up of a batch solve: the cells of every grid (block (b, c): rows 32 c to
+// 32 c + 31 of the 64 columns of list entry b; 64 grids of 64 to 1024 cells a
+// side took 110 us for the fields and 30 for the masks with a block per
+// column list entry), and in the last row of blocks one that makes every grid
+// active, checking its initial field in slot 0.
+__global__ __launch_bounds__(256) void k_batch_begin(BatchArgs a, const uint8_t *cls, int mode)
 {
+    if (blockIdx.y + 1 < gridDim.y) {
+        const int2 bk = a.blocks[blockIdx.x];
+        const BatchGrid g = a.grids[bk.x];
+        const CellSetup s{cls + g.off, a.psi + g.off, a.mask + g.off, g.nx, g.ny, g.pitch, mode, 0, 0};
+        const int x = bk.y * 64 + 4 * (threadIdx.x & 15);
+        const bool quads = setup_quads(s);
+        const int y1 = min(32 * (int)blockIdx.y + 32, g.ny);
+        for (int y = 32 * (int)blockIdx.y + (threadIdx.x >> 4); y < y1; y += 16) setup_four(s, x, y, quads);
+        return;
+    }
+    if (blockIdx.x != 0) return;
     BatchHdr *h = static_cast<BatchHdr *>(a.hdr);
     const int VW = 128 - 4 * a.S;
     for (int k = threadIdx.x; k < a.n; k += 256) {
@@ -658,9 +673,9 @@ size_t batch_hdr_bytes() { return (sizeof(BatchHdr) + 255) & ~size_t(255); }
 size_t batch_run_bytes() { return sizeof(GridRun); }
 size_t batch_ctl_bytes() { return sizeof(GridCtl); }
 
-int launch_batch_begin(const BatchArgs &a, hipStream_t st)
+int launch_batch_begin(const BatchArgs &a, const uint8_t *cls, int mode, int most_rows, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_batch_begin, dim3(1), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_batch_begin, dim3(a.n_blocks, (most_rows + 31) / 32 + 1), dim3(256), 0, st, a, cls, mode);
     return last_status_b();
 }
 

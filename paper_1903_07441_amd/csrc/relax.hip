@@ -6,6 +6,7 @@
 //
 // Field layout: row-major, x fastest, pitch in elements; psi = 1 - phi.
 // Red cells are (x + y) even.
+#include "cell_setup.h"
 #include "twg_internal.h"
 #include "update.h"
 
@@ -128,29 +129,6 @@ __global__ __launch_bounds__(256) void k_resid_reduce(const unsigned long long *
     }
 }
 
-__global__ void k_field_init_batch(const uint8_t *__restrict__ cls, float *psi,
-                                   const BatchGrid *__restrict__ grids,
-                                   const int2 *__restrict__ blocks, int mode)
-{
-    const int2 bk = blocks[blockIdx.x];
-    const BatchGrid g = grids[bk.x];
-    const int x = bk.y * 64 + (threadIdx.x & 63);
-    if (x >= g.nx) return;
-    for (int y = threadIdx.x >> 6; y < g.ny; y += 4) {
-        const size_t i = g.off + (size_t)y * g.pitch + x;
-        switch (cls[i]) {
-        case TWG_CELL_OBST:
-        case TWG_CELL_WALL: psi[i] = 0.0f; break;
-        case TWG_CELL_GOAL: psi[i] = 1.0f; break;
-        case TWG_CELL_FREE:
-            if (mode == HPF_INIT_HALF) psi[i] = 0.5f;
-            else if (mode == HPF_INIT_ZERO) psi[i] = 0.0f;
-            break;
-        default: break;
-        }
-    }
-}
-
 // Warm start from a previous field: FREE cells that were FREE in the
 // previous step take the previous value; every other cell keeps psi.
 __global__ void k_merge_prev(const uint8_t *__restrict__ cls, const uint8_t *__restrict__ cls_prev,
@@ -166,35 +144,8 @@ __global__ void k_merge_prev(const uint8_t *__restrict__ cls, const uint8_t *__r
 }
 
 // ---- element-wise helpers --------------------------------------------------
-// Field initialisation: OBST and WALL 0, GOAL 1, FIXED unchanged; FREE cells
-// by mode: HALF 0.5, ZERO 0, LINEAR the ramp 1 - d / (max(nx, ny) sqrt 2)
-// of the Euclidean distance d to the goal cell (gx, gy), evaluated in FP64
-// and rounded once; KEEP leaves them.
-__global__ void k_field_init(const uint8_t *__restrict__ cls, float *psi, int nx, int ny, int pitch,
-                             int mode, int gx, int gy)
-{
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= nx || y >= ny) return;
-    const size_t i = (size_t)y * pitch + x;
-    switch (cls[i]) {
-    case TWG_CELL_OBST:
-    case TWG_CELL_WALL: psi[i] = 0.0f; break;
-    case TWG_CELL_GOAL: psi[i] = 1.0f; break;
-    case TWG_CELL_FREE:
-        if (mode == HPF_INIT_HALF) {
-            psi[i] = 0.5f;
-        } else if (mode == HPF_INIT_ZERO) {
-            psi[i] = 0.0f;
-        } else if (mode == HPF_INIT_LINEAR) {
-            const double dx = (double)(x - gx), dy = (double)(y - gy);
-            const double d = sqrt(dx * dx + dy * dy);
-            psi[i] = (float)(1.0 - d / ((double)max(nx, ny) * sqrt(2.0)));
-        }
-        break;
-    default: break;
-    }
-}
+// field and mask set-up of one grid, either left out
+__global__ __launch_bounds__(256) void k_setup(CellSetup s) { setup_grid(s); }
 
 __global__ void k_update64(const uint8_t *__restrict__ cls, double *u, const float *__restrict__ e,
                            float *psi, int nx, int ny, int pitch)
@@ -248,30 +199,6 @@ __global__ void k_copy(const float *__restrict__ s, float *__restrict__ d, int n
 
 dim3 cell_grid(int nx, int ny) { return dim3((nx + 63) / 64, (ny + 3) / 4); }
 
-// free mask of the streamed sweeps: 0xFF on FREE cells, 0 on the others
-template <typename T>
-__global__ void k_wmap(const uint8_t *__restrict__ cls, T *__restrict__ w, T omega, int nx, int ny, int pitch)
-{
-    const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= nx || y >= ny) return;
-    const size_t i = (size_t)y * pitch + x;
-    w[i] = cls[i] == TWG_CELL_FREE ? omega : T(0);
-}
-
-__global__ void k_fmask_batch(const uint8_t *__restrict__ cls, uint8_t *__restrict__ m,
-                              const BatchGrid *__restrict__ grids, const int2 *__restrict__ blocks)
-{
-    const int2 bk = blocks[blockIdx.x];
-    const BatchGrid g = grids[bk.x];
-    const int x = bk.y * 64 + (threadIdx.x & 63);
-    if (x >= g.nx) return;
-    for (int y = threadIdx.x >> 6; y < g.ny; y += 4) {
-        const size_t i = g.off + (size_t)y * g.pitch + x;
-        m[i] = cls[i] == TWG_CELL_FREE ? 0xff : 0;
-    }
-}
-
 int last_status()
 {
     return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE;
@@ -279,35 +206,18 @@ int last_status()
 
 }  // namespace
 
-int launch_field_init_batch(const uint8_t *cls, float *psi, const BatchGrid *grids,
-                            const int2 *blocks, int n_blocks, int mode, hipStream_t st)
-{
-    if (n_blocks > 0)
-        hipLaunchKernelGGL(k_field_init_batch, dim3(n_blocks), dim3(256), 0, st, cls, psi, grids,
-                           blocks, mode);
-    return last_status();
-}
-
-
 int launch_fmask(const uint8_t *cls, uint8_t *fmask, int nx, int ny, int pitch, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_wmap<uint8_t>, cell_grid(nx, ny), dim3(256), 0, st, cls, fmask, (uint8_t)0xff, nx, ny,
-                       pitch);
-    return last_status();
-}
-
-int launch_fmask_batch(const uint8_t *cls, uint8_t *fmask, const BatchGrid *grids, const int2 *blocks,
-                       int n_blocks, hipStream_t st)
-{
-    if (n_blocks > 0)
-        hipLaunchKernelGGL(k_fmask_batch, dim3(n_blocks), dim3(256), 0, st, cls, fmask, grids, blocks);
+    hipLaunchKernelGGL(k_setup, dim3(setup_blocks(nx, ny)), dim3(256), 0, st,
+                       CellSetup{cls, nullptr, fmask, nx, ny, pitch, HPF_INIT_KEEP, 0, 0});
     return last_status();
 }
 
 int launch_field_init(const uint8_t *cls, float *psi, int nx, int ny, int pitch, int mode, int gx, int gy,
                       hipStream_t st)
 {
-    hipLaunchKernelGGL(k_field_init, cell_grid(nx, ny), dim3(256), 0, st, cls, psi, nx, ny, pitch, mode, gx, gy);
+    hipLaunchKernelGGL(k_setup, dim3(setup_blocks(nx, ny)), dim3(256), 0, st,
+                       CellSetup{cls, psi, nullptr, nx, ny, pitch, mode, gx, gy});
     return last_status();
 }
 

@@ -28,6 +28,7 @@
 // host-mapped word, which lets a blocking caller keep just enough slots
 // queued; an asynchronous caller enqueues a fixed number of slots and one
 // final slot that finishes whatever is left.
+#include "cell_setup.h"
 #include "stream_tile.h"
 
 #include <algorithm>
@@ -1018,8 +1019,11 @@ __global__ __launch_bounds__(256) void k_relax_resident(void *ctl, int slot, Slo
 }
 #endif
 
-__global__ void k_relax_begin(RelaxCtl *c, RelaxConfig cfg)
+// Set-up of a solve: the cells (boundary and initial values, free mask), and
+// in the first block the control block.
+__global__ __launch_bounds__(256) void k_relax_begin(RelaxCtl *c, RelaxConfig cfg, CellSetup cells)
 {
+    setup_grid(cells);
     if (blockIdx.x != 0) return;
     for (int i = threadIdx.x; i < kParts; i += blockDim.x) {
         __hip_atomic_store(&c->part[i][0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1105,9 +1109,10 @@ int launch_relax_resident(const SlotArgs &a, hipStream_t st)
     return last_status();
 }
 
-int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st)
+int launch_relax_begin(void *ctl, const RelaxConfig &cfg, const CellSetup &cells, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_relax_begin, dim3(1), dim3(64), 0, st, static_cast<RelaxCtl *>(ctl), cfg);
+    hipLaunchKernelGGL(k_relax_begin, dim3(setup_blocks(cells.nx, cells.ny)), dim3(256), 0, st,
+                       static_cast<RelaxCtl *>(ctl), cfg, cells);
     return last_status();
 }
 

@@ -113,9 +113,6 @@ struct BatchGrid {
     int lds;  // 1: solved whole in one workgroup's LDS (k_batch_lds), not by tiles
     int pad_;
 };
-int launch_field_init_batch(const uint8_t *cls, float *psi, const BatchGrid *grids,
-                            const int2 *blocks, int n_blocks, int mode, hipStream_t st);
-
 int set_err(twg_ctx *ctx, int code, const std::string &msg);
 int ensure(twg_ctx *ctx, void **buf, size_t *have, size_t need);
 int check_grid(twg_ctx *ctx, const twg_grid &g);
@@ -147,9 +144,6 @@ int launch_stream_f32(const float *src, float *dst, const uint8_t *fmask, float 
 int launch_stream_f64(const double *src, double *dst, const uint8_t *fmask, double omega, int nx, int ny,
                       int pitch, const Geometry &geo, hipStream_t st);
 int launch_fmask(const uint8_t *cls, uint8_t *fmask, int nx, int ny, int pitch, hipStream_t st);
-// the batch's free mask, over the batch's column blocks
-int launch_fmask_batch(const uint8_t *cls, uint8_t *fmask, const BatchGrid *grids, const int2 *blocks,
-                       int n_blocks, hipStream_t st);
 // residual reductions: part = the context's block partials (2 kResidBlocks
 // words), out = 3 words receiving max |r| and max |r| / |u|, then seq (after
 // a system-scope fence, so a host that sees seq in out[2] reads final
@@ -218,7 +212,9 @@ struct SlotArgs {
     int lead_passes;      // RelaxConfig::lead_passes
 };
 size_t relax_ctl_bytes();
-int launch_relax_begin(void *ctl, const RelaxConfig &cfg, hipStream_t st);
+struct CellSetup;
+// the control block, and the cells' set-up in the same launch
+int launch_relax_begin(void *ctl, const RelaxConfig &cfg, const CellSetup &cells, hipStream_t st);
 int launch_relax_slot(const SlotArgs &a, int S, hipStream_t st);
 // a solve whose grid one workgroup can keep (relax_resident): one such launch
 // goes on until the solve ends or it has done its share of sweeps
@@ -245,7 +241,7 @@ struct BatchArgs {
     double tol;
     int64_t max_sweeps;      // per grid
     float *psi, *alt;        // batch fields and their ping-pong partner
-    const uint8_t *mask;     // free masks, laid out as the fields
+    uint8_t *mask;           // free masks, laid out as the fields
     void *hdr;               // batch_hdr_bytes()
     GridRun *run;            // n
     GridCtl *ctl;            // n
@@ -259,7 +255,8 @@ struct BatchArgs {
 size_t batch_hdr_bytes();
 size_t batch_run_bytes();
 size_t batch_ctl_bytes();
-int launch_batch_begin(const BatchArgs &a, hipStream_t st);
+// cls: the batch's class maps; mode: HPF_INIT_*; most_rows: of any grid
+int launch_batch_begin(const BatchArgs &a, const uint8_t *cls, int mode, int most_rows, hipStream_t st);
 int launch_batch_slot(const BatchArgs &a, bool even, hipStream_t st);
 // LDS bytes k_batch_lds needs for a grid of `cells` cells; the solve of the
 // LDS grids (one workgroup each), launched after launch_batch_begin
