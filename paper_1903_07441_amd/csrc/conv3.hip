@@ -22,7 +22,10 @@
 // layers that the encoder pools write the 2x2 means as well (their consumers
 // then read a quarter of the bytes, once, instead of pooling while staging),
 // and the last layer's head is evaluated from LDS instead of from a stored
-// activation.
+// activation.  The input gradient of a concatenation leaves as what its two
+// halves are used for: the upsampled half as 2x2 sums in bf16 (an eighth of
+// the FP32 bytes, and no launch that reads them back), the skip half in FP32
+// (loss and gradients of 16 x 256 x 256: 841 -> 777 us).
 //
 // Measured (whole calls, against 16 x 16 tiles that staged through registers,
 // pooled while staging and loaded every wave's weights from global memory one
@@ -52,6 +55,12 @@ typedef __attribute__((address_space(3))) void lds_void;
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t bytes)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p), 0, (int)bytes, 0x00020000);
+}
+
+// the value of the lane at the right of an even one
+__device__ __forceinline__ float lane_right(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
 }
 
 template <int CIN, int COUT, int MODE, int CA, int OUT, int R>
@@ -168,13 +177,39 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
         if (ch + 1 < NCH) load(ch + 1);
     }
 
-    if constexpr (OUT == kOutF32) {
-        const int x = x0 + j;
+    if (OUT == kOutCatGrad && co0 < COUT / 2) {
+        // 2x2 sums, left to right and top to bottom: rows in this lane's
+        // registers, the column at its right in the next lane; H and W are
+        // even, so a pair lies inside whole
+        constexpr int CL = COUT / 2;
+        const int W2 = W / 2, H2 = H / 2, x = x0 + j;
+#pragma unroll
+        for (int ct = 0; ct + 1 < R; ct += 2) {
+            const int y = y0 + wave * R + ct;
+            const bool in = !(j & 1) && y < H && x < W;
+            const size_t at = (((size_t)b * H2 + y / 2) * W2 + x / 2) * CL + co0 + g * 4;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) {
+                float s[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    s[i] = (((0.f + acc[ct][rt][i]) + lane_right(acc[ct][rt][i])) + acc[ct + 1][rt][i]) +
+                           lane_right(acc[ct + 1][rt][i]);
+                if (!in) continue;
+                const uint2 av = *reinterpret_cast<const uint2 *>(a.act + at + rt * 16);
+                *reinterpret_cast<uint2 *>(a.pool + at + rt * 16) =
+                    make_uint2(pack2(bf_pos(av.x & 0xffffu) ? s[0] : 0.f, bf_pos(av.x >> 16) ? s[1] : 0.f),
+                               pack2(bf_pos(av.y & 0xffffu) ? s[2] : 0.f, bf_pos(av.y >> 16) ? s[3] : 0.f));
+            }
+        }
+    } else if constexpr (OUT == kOutF32 || OUT == kOutCatGrad) {
+        constexpr int CT = OUT == kOutF32 ? COUT : COUT / 2;  // channels stored
+        const int x = x0 + j, c0 = co0 - (COUT - CT);
 #pragma unroll
         for (int ct = 0; ct < R; ++ct) {
             const int y = y0 + wave * R + ct;
             if (y >= H || x >= W) continue;
-            float *o = static_cast<float *>(a.out) + (((size_t)b * H + y) * W + x) * COUT + co0 + g * 4;
+            float *o = static_cast<float *>(a.out) + (((size_t)b * H + y) * W + x) * CT + c0 + g * 4;
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
                 const f32x4 v = acc[ct][rt];
@@ -253,8 +288,9 @@ int launch_conv3(const ConvArgs &a, int num_cu, hipStream_t st)
     const long long want = 2LL * std::max(1, num_cu);
     if (groups(8) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 8>(a, st);
     if (groups(4) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 4>(a, st);
-    if (groups(2) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 2>(a, st);
-    return launch_r<CIN, COUT, MODE, CA, OUT, 1>(a, st);
+    // (2x2 sums take a wave's rows in pairs)
+    if (OUT == kOutCatGrad || groups(2) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 2>(a, st);
+    if constexpr (OUT != kOutCatGrad) return launch_r<CIN, COUT, MODE, CA, OUT, 1>(a, st);
 }
 
 // forward
@@ -266,9 +302,9 @@ template int launch_conv3<128, 32, kUpCat, 64, kOutAct>(const ConvArgs &, int, h
 template int launch_conv3<64, 32, kUpCat, 32, kOutAct>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<64, 32, kUpCat, 32, kOutHead>(const ConvArgs &, int, hipStream_t);
 // input gradients
-template int launch_conv3<32, 64, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
-template int launch_conv3<32, 128, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
-template int launch_conv3<64, 256, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 64, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 128, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 256, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<128, 128, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<128, 64, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<64, 32, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);

@@ -289,51 +289,11 @@ __global__ void k_zero_words(unsigned int *w, int n)
     if (blockIdx.x == 0 && (int)threadIdx.x < n) w[threadIdx.x] = 0u;
 }
 
-// Gradient through up() into a low-resolution activation:
-// dlow[b][Y][X][c] = bf16((sum_{2x2} dc[b][2Y+a][2X+e][c]) * [act > 0]) for
-// c < CL, where dc is the FP32 input gradient of a concatenating conv with
-// CT channels.  One thread per (low pixel, 8 channels).
-template <int CL, int CT>
-__global__ __launch_bounds__(256) void k_route_up(const float *__restrict__ dc, const uint16_t *__restrict__ act,
-                                                  uint16_t *__restrict__ dlow, int nb, int Hl, int Wl)
-{
-    const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = (long long)nb * Hl * Wl * (CL / 8);
-    if (v >= total) return;
-    const int cg = (int)(v % (CL / 8));
-    const long long lp = v / (CL / 8);
-    const int X = (int)(lp % Wl);
-    const long long t = lp / Wl;
-    const int Y = (int)(t % Hl);
-    const int b = (int)(t / Hl);
-    const int Hh = 2 * Hl, Wh = 2 * Wl;
-    float s[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = 0.f;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-            const float *p = dc + (((size_t)b * Hh + 2 * Y + a) * Wh + 2 * X + e) * CT + cg * 8;
-            const float4 u = reinterpret_cast<const float4 *>(p)[0], w = reinterpret_cast<const float4 *>(p)[1];
-            s[0] += u.x; s[1] += u.y; s[2] += u.z; s[3] += u.w;
-            s[4] += w.x; s[5] += w.y; s[6] += w.z; s[7] += w.w;
-        }
-    const uint4 av = *reinterpret_cast<const uint4 *>(act + (size_t)lp * CL + cg * 8);
-    const uint32_t aw[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (!bf_pos(aw[i] & 0xffffu)) s[2 * i] = 0.f;
-        if (!bf_pos(aw[i] >> 16)) s[2 * i + 1] = 0.f;
-    }
-    *reinterpret_cast<uint4 *>(dlow + (size_t)lp * CL + cg * 8) = pack8(s);
-}
-
 // Gradient of an encoder activation used by a skip connection and by pool():
-// de[b][y][x][c] = bf16((dskip[...][OFF + c] + dp[b][y/2][x/2][c] / 4) * [e > 0]),
-// dskip an FP32 input gradient with CT channels, dp the FP32 input gradient
-// of the next encoder conv (C channels at half resolution).
-template <int C, int OFF, int CT>
+// de[b][y][x][c] = bf16((dskip[...][c] + dp[b][y/2][x/2][c] / 4) * [e > 0]),
+// dskip the FP32 input gradient of the skip connection, dp that of the next
+// encoder conv (at half resolution).
+template <int C>
 __global__ __launch_bounds__(256) void k_route_pool(const float *__restrict__ dskip, const float *__restrict__ dp,
                                                     const uint16_t *__restrict__ e, uint16_t *__restrict__ de,
                                                     int nb, int H, int W)
@@ -347,7 +307,7 @@ __global__ __launch_bounds__(256) void k_route_pool(const float *__restrict__ ds
     const long long t = pix / W;
     const int y = (int)(t % H);
     const int b = (int)(t / H);
-    const float *ps = dskip + (size_t)pix * CT + OFF + cg * 8;
+    const float *ps = dskip + (size_t)pix * C + cg * 8;
     const float *pp = dp + (((size_t)b * (H / 2) + y / 2) * (W / 2) + x / 2) * C + cg * 8;
     float s[8];
 #pragma unroll
@@ -677,21 +637,12 @@ __global__ __launch_bounds__(256) void k_sum_loss(const float *__restrict__ part
 }
 
 // ---- launch helpers -----------------------------------------------------------
-template <int CL, int CT>
-int route_up(const float *dc, const uint16_t *act, uint16_t *dlow, int nb, int Hl, int Wl, hipStream_t st)
-{
-    const long long total = (long long)nb * Hl * Wl * (CL / 8);
-    hipLaunchKernelGGL((k_route_up<CL, CT>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, dc, act, dlow,
-                       nb, Hl, Wl);
-    return last_status();
-}
-
-template <int C, int OFF, int CT>
+template <int C>
 int route_pool(const float *dskip, const float *dp, const uint16_t *e, uint16_t *de, int nb, int H, int W,
                hipStream_t st)
 {
     const long long total = (long long)nb * H * W * (C / 8);
-    hipLaunchKernelGGL((k_route_pool<C, OFF, CT>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, dskip,
+    hipLaunchKernelGGL((k_route_pool<C>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, dskip,
                        dp, e, de, nb, H, W);
     return last_status();
 }
@@ -761,6 +712,13 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     auto grad_args = [&](const uint16_t *g, int l, float *out, int h, int w) {
         return ConvArgs{g, nullptr, wf + L.offw[l], nullptr, out, nullptr, nullptr, nullptr, nullptr, nb, h, w};
     };
+    // of a concatenation: the low activation's gradient, the skip's in FP32
+    auto cat_args = [&](const uint16_t *g, int l, float *skip, const uint16_t *low, uint16_t *dlow, int h, int w) {
+        ConvArgs c = grad_args(g, l, skip, h, w);
+        c.pool = dlow;
+        c.act = low;
+        return c;
+    };
     auto GW = [&](int l) { return n->grad + L.offw[l]; };
     const int cu = n->ctx->num_cu;
     const int H1 = H / 2, W1 = W / 2, H2 = H / 4, W2 = W / 4, H3 = H / 8, W3 = W / 8;
@@ -777,28 +735,28 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     int rc = last_status();
     // d0: input cat(up(d1), e0) at H
     if (!rc) rc = launch_wgrad3<64, 32, kUpCat, 32>(n->d1, n->e0, n->g_d0, n->part, GW(6), nb, H, W, cu, st);
-    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutF32>(grad_args(n->g_d0, 6, n->f_c0, H, W), cu, st);
-    if (!rc) rc = route_up<32, 64>(n->f_c0, n->d1, n->g_d1, nb, H1, W1, st);
+    if (!rc)
+        rc = launch_conv3<32, 64, kPlain, 0, kOutCatGrad>(cat_args(n->g_d0, 6, n->f_c0, n->d1, n->g_d1, H, W), cu, st);
     // d1: input cat(up(d2), e1) at H/2
     if (!rc) rc = launch_wgrad3<128, 32, kUpCat, 64>(n->d2, n->e1, n->g_d1, n->part, GW(5), nb, H1, W1, cu, st);
-    if (!rc) rc = launch_conv3<32, 128, kPlain, 0, kOutF32>(grad_args(n->g_d1, 5, n->f_c1, H1, W1), cu, st);
-    if (!rc) rc = route_up<64, 128>(n->f_c1, n->d2, n->g_d2, nb, H2, W2, st);
+    if (!rc)
+        rc = launch_conv3<32, 128, kPlain, 0, kOutCatGrad>(cat_args(n->g_d1, 5, n->f_c1, n->d2, n->g_d2, H1, W1), cu, st);
     // d2: input cat(up(e3), e2) at H/4
     if (!rc) rc = launch_wgrad3<256, 64, kUpCat, 128>(n->e3, n->e2, n->g_d2, n->part, GW(4), nb, H2, W2, cu, st);
-    if (!rc) rc = launch_conv3<64, 256, kPlain, 0, kOutF32>(grad_args(n->g_d2, 4, n->f_c2, H2, W2), cu, st);
-    if (!rc) rc = route_up<128, 256>(n->f_c2, n->e3, n->g_e3, nb, H3, W3, st);
+    if (!rc)
+        rc = launch_conv3<64, 256, kPlain, 0, kOutCatGrad>(cat_args(n->g_d2, 4, n->f_c2, n->e3, n->g_e3, H2, W2), cu, st);
     // e3: input pool(e2) at H/8
     if (!rc) rc = launch_wgrad3<128, 128, kPlain, 0>(n->p2, nullptr, n->g_e3, n->part, GW(3), nb, H3, W3, cu, st);
     if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutF32>(grad_args(n->g_e3, 3, n->f_p2, H3, W3), cu, st);
-    if (!rc) rc = route_pool<128, 128, 256>(n->f_c2, n->f_p2, n->e2, n->g_e2, nb, H2, W2, st);
+    if (!rc) rc = route_pool<128>(n->f_c2, n->f_p2, n->e2, n->g_e2, nb, H2, W2, st);
     // e2: input pool(e1) at H/4
     if (!rc) rc = launch_wgrad3<64, 128, kPlain, 0>(n->p1, nullptr, n->g_e2, n->part, GW(2), nb, H2, W2, cu, st);
     if (!rc) rc = launch_conv3<128, 64, kPlain, 0, kOutF32>(grad_args(n->g_e2, 2, n->f_p1, H2, W2), cu, st);
-    if (!rc) rc = route_pool<64, 64, 128>(n->f_c1, n->f_p1, n->e1, n->g_e1, nb, H1, W1, st);
+    if (!rc) rc = route_pool<64>(n->f_c1, n->f_p1, n->e1, n->g_e1, nb, H1, W1, st);
     // e1: input pool(e0) at H/2
     if (!rc) rc = launch_wgrad3<32, 64, kPlain, 0>(n->p0, nullptr, n->g_e1, n->part, GW(1), nb, H1, W1, cu, st);
     if (!rc) rc = launch_conv3<64, 32, kPlain, 0, kOutF32>(grad_args(n->g_e1, 1, n->f_p0, H1, W1), cu, st);
-    if (!rc) rc = route_pool<32, 32, 64>(n->f_c0, n->f_p0, n->e0, n->g_e0, nb, H, W, st);
+    if (!rc) rc = route_pool<32>(n->f_c0, n->f_p0, n->e0, n->g_e0, nb, H, W, st);
     // e0: input x (padded to 32 channels)
     if (!rc) rc = launch_wgrad_in(n->xp, n->g_e0, n->part, GW(0), nb, H, W, cu, st);
     return rc;

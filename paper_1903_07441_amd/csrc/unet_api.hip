@@ -66,7 +66,7 @@ int ensure_bwd(twg_unet *n, long long P)
     // bf16 gradients, FP32 input gradients, split-K partial sums
     const size_t parts = std::max<size_t>(kPartFloats, 34 * ((P0 + 255) / 256));
     const size_t sizes[] = {al(P0 * 32 * 2), al(P1 * 32 * 2), al(P2 * 64 * 2), al(P3 * 128 * 2), al(P2 * 128 * 2),
-                            al(P1 * 64 * 2), al(P0 * 32 * 2), al(P0 * 64 * 4), al(P1 * 128 * 4), al(P2 * 256 * 4),
+                            al(P1 * 64 * 2), al(P0 * 32 * 2), al(P0 * 32 * 4), al(P1 * 64 * 4), al(P2 * 128 * 4),
                             al(P3 * 128 * 4), al(P2 * 64 * 4), al(P1 * 32 * 4), al(parts * 4),
                             al((size_t)65536 * 4)};
     size_t bytes = 0;
