@@ -173,16 +173,44 @@ __global__ __launch_bounds__(256) void k_conv3_in(const uint16_t *__restrict__ x
 }
 
 // ---- head, loss, routing ---------------------------------------------------
-__device__ __forceinline__ float wave_sum(float v)
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+
+// v summed over the 16 lanes of a row, by halves (every lane gets the sum)
+__device__ __forceinline__ float row_sum(float v)
 {
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+    auto ror = [](float f, auto n) {
+        return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(f), 0x120 + decltype(n)::value, 0xf, 0xf, true));
+    };
+    v += ror(v, std::integral_constant<int, 8>{});
+    v += ror(v, std::integral_constant<int, 4>{});
+    v += ror(v, std::integral_constant<int, 2>{});
+    v += ror(v, std::integral_constant<int, 1>{});
     return v;
+}
+// lanes of the first half: a summed over both halves of the wave; of the
+// second: b (the halves change places between two registers)
+__device__ __forceinline__ float half_sums(float a, float b)
+{
+    const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    const uint32_t x = r[0], y = r[1];
+    return __uint_as_float(x) + __uint_as_float(y);
+}
+// the same for the rows of a pair: a in even rows of 16 lanes, b in odd ones
+__device__ __forceinline__ float pair_sums(float a, float b)
+{
+    const u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    const uint32_t x = r[0], y = r[1];
+    return __uint_as_float(x) + __uint_as_float(y);
 }
 
 // Training head: masked MSE over FREE cells.  Per pixel: y, diff = y - t
 // (0 outside the mask), loss += diff^2 / (n_b B), dy = 2 diff / (n_b B),
 // dd0 = bf16(dy * hw * [d0 > 0]); block partial sums of the head gradients
-// (hw: 32, hb: 1) and of the loss go to part[block][34].
+// (hw: 32, hb: 1) and of the loss go to part[block][34].  Bound by memory
+// (130 bytes a pixel) once the sums over a wave take few steps: 34 sums by
+// shuffles were 204 trips through LDS, and 52 us for 16 x 256 x 256; here
+// registers change halves, so that after two steps a lane sums 8 of them over
+// its row (the same pairs in the same order).
 __global__ __launch_bounds__(256) void k_head_loss(const uint16_t *__restrict__ d0, const float *__restrict__ hw,
                                                    const float *__restrict__ hb, const float *__restrict__ target,
                                                    const uint8_t *__restrict__ cls,
@@ -221,16 +249,19 @@ __global__ __launch_bounds__(256) void k_head_loss(const uint16_t *__restrict__ 
         for (int q = 0; q < 4; ++q) o[q] = pack8(dd + 8 * q);
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // channel c + 8 r ends in row r of 16 lanes
+    float s16[16];
 #pragma unroll
-    for (int c = 0; c < 32; ++c) {
-        const float s = wave_sum(gw[c]);
-        if (lane == 0) red[wave][c] = s;
+    for (int c = 0; c < 16; ++c) s16[c] = half_sums(gw[c], gw[c + 16]);
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float s = row_sum(pair_sums(s16[c], s16[c + 8]));
+        if ((lane & 15) == 0) red[wave][c + 8 * (lane >> 4)] = s;
     }
     {
-        const float s = wave_sum(gb);
-        if (lane == 0) red[wave][32] = s;
-        const float l = wave_sum(lp);
-        if (lane == 0) red[wave][33] = l;
+        const float h = half_sums(gb, lp);  // gb in the first half, lp in the second
+        const float s = row_sum(pair_sums(h, h));
+        if ((lane & 31) == 0) red[wave][32 + (lane >> 5)] = s;
     }
     __syncthreads();
     if (threadIdx.x < 34) {
@@ -602,17 +633,36 @@ __global__ void k_zero_u32n(unsigned int *__restrict__ w, int n)
     if (i < n) w[i] = 0u;
 }
 
-// per-image count of FREE cells, added into cnt[b] (integer additions are
-// exact in any order); grid (blocks per image, images)
+// Per-image count of FREE cells; grid (blocks per image, images).  One block
+// an image stores its count, several add theirs (integer additions are exact
+// in any order).  Sixteen cells a load where `cls` is aligned for that.
 __global__ __launch_bounds__(256) void k_count_free(const uint8_t *__restrict__ cls, int hw_pixels,
                                                     unsigned int *__restrict__ cnt)
 {
-    const int b = blockIdx.y;
+    static_assert(TWG_CELL_FREE == 0, "FREE cells are counted as zero bytes");
+    __shared__ unsigned int red[4];
+    const uint8_t *c = cls + (size_t)blockIdx.y * hw_pixels;
     unsigned int n = 0;
-    for (int p = blockIdx.x * 256 + threadIdx.x; p < hw_pixels; p += gridDim.x * 256)
-        n += cls[(size_t)b * hw_pixels + p] == TWG_CELL_FREE;
+    const int first = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
+    auto zeros = [](uint32_t w) {
+        return __popc(~(((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
+    };
+    if (!((uintptr_t)c & 15)) {  // images are multiples of 64 cells
+#pragma unroll 8
+        for (int p = first; p < hw_pixels / 16; p += step) {
+            const uint4 v = reinterpret_cast<const uint4 *>(c)[p];
+            n += (zeros(v.x) + zeros(v.y)) + (zeros(v.z) + zeros(v.w));
+        }
+    } else {
+        for (int p = first; p < hw_pixels; p += step) n += c[p] == TWG_CELL_FREE;
+    }
     for (int o = 32; o > 0; o >>= 1) n += (unsigned int)__shfl_xor((int)n, o);
-    if ((threadIdx.x & 63) == 0 && n) atomicAdd(cnt + b, n);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    n = (red[0] + red[1]) + (red[2] + red[3]);
+    if (gridDim.x == 1) cnt[blockIdx.y] = n;
+    else if (n) atomicAdd(cnt + blockIdx.y, n);
 }
 
 // column c < 34 of part[nblk][34] summed by block c: thread t adds rows t,
@@ -725,9 +775,11 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     const int hwp = H * W, total = nb * hwp;
     // head and loss
     unsigned int *cnt = n->counts;
-    hipLaunchKernelGGL(k_zero_u32n, dim3((nb + 255) / 256), dim3(256), 0, st, cnt, nb);
-    hipLaunchKernelGGL(k_count_free, dim3(std::max(1, std::min(64, hwp / 4096)), nb), dim3(256), 0, st, cls, hwp,
-                       cnt);
+    // one block counts an image of up to 65536 cells (16 loads a thread: 4 us,
+    // where zeroing and adding up 16 blocks' counts took 24)
+    const int count_blocks = std::min(64, (hwp + 65535) / 65536);
+    if (count_blocks > 1) hipLaunchKernelGGL(k_zero_u32n, dim3((nb + 255) / 256), dim3(256), 0, st, cnt, nb);
+    hipLaunchKernelGGL(k_count_free, dim3(count_blocks, nb), dim3(256), 0, st, cls, hwp, cnt);
     const int nblk = (total + 255) / 256;
     hipLaunchKernelGGL(k_head_loss, dim3(nblk), dim3(256), 0, st, n->d0, n->master + L.offw[7],
                        n->master + L.offb[7], target, cls, cnt, hwp, nb, n->g_d0, nullptr, n->part);
