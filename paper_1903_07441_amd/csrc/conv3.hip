@@ -22,10 +22,11 @@
 // layers that the encoder pools write the 2x2 means as well (their consumers
 // then read a quarter of the bytes, once, instead of pooling while staging),
 // and the last layer's head is evaluated from LDS instead of from a stored
-// activation.  The input gradient of a concatenation leaves as what its two
-// halves are used for: the upsampled half as 2x2 sums in bf16 (an eighth of
-// the FP32 bytes, and no launch that reads them back), the skip half in FP32
-// (loss and gradients of 16 x 256 x 256: 841 -> 777 us).
+// activation.  The input gradient of a concatenation is never stored: the
+// upsampled half leaves as 2x2 sums in bf16, and the skip half is computed
+// when the pooled tensor's gradient, which adds to it, is there (its input is
+// read once more; stored in FP32 in between, it was written and read twice).
+// Loss and gradients of 16 x 256 x 256: 841 -> 676 us.
 //
 // Measured (whole calls, against 16 x 16 tiles that staged through registers,
 // pooled while staging and loaded every wave's weights from global memory one
@@ -61,6 +62,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const void *p, uint32_t b
 __device__ __forceinline__ float lane_right(float v)
 {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xb1, 0xf, 0xf, true));
+}
+
+// eight bf16 values, zero where e's are not positive
+__device__ __forceinline__ uint4 where_positive(uint4 v, uint4 e)
+{
+    auto two = [](uint32_t a, uint32_t q) {
+        return (bf_pos(q & 0xffffu) ? a & 0xffffu : 0u) | (bf_pos(q >> 16) ? a & 0xffff0000u : 0u);
+    };
+    return make_uint4(two(v.x, e.x), two(v.y, e.y), two(v.z, e.z), two(v.w, e.w));
 }
 
 template <int CIN, int COUT, int MODE, int CA, int OUT, int R>
@@ -147,6 +157,44 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
     const uint16_t *wp = lds + HALO + lane * 8;
 
     load(0);
+    // What the epilogue of an activation's gradient adds and masks by is read
+    // ahead of the products, one memory latency less per tile (56 instead of
+    // 69 us for 32 channels of 16 x 256 x 256); dp: a row of the pooled grid
+    // serves two rows, with R = 1 every row its own.
+    constexpr int ND = OUT == kOutSkipGrad || OUT == kOutUpGrad ? (R + 1) / 2 : 1, NE = OUT == kOutSkipGrad ? R : 1;
+    float4 dp[ND][2];
+    uint4 ev[NE];
+    uint2 lv[ND][2];  // kOutUpGrad
+    if constexpr (OUT == kOutUpGrad) {
+        const int x = min(x0 + j, W - 1);
+#pragma unroll
+        for (int q = 0; q < R / 2; ++q) {
+            const int y = min(y0 + wave * R + 2 * q, H - 1);
+            const uint16_t *l = a.act + (((size_t)b * (H / 2) + y / 2) * (W / 2) + x / 2) * COUT + co0 + g * 4;
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt) lv[q][rt] = *reinterpret_cast<const uint2 *>(l + rt * 16);
+        }
+    }
+    auto read_mask = [&] {
+#pragma unroll
+        for (int q = 0; q < NE; ++q) {
+            const int p = (tid + 256 * q) >> 2;
+            const int y = min(y0 + p / kTW, H - 1), xe = min(x0 + p % kTW, W - 1);
+            ev[q] = *reinterpret_cast<const uint4 *>(a.act + (((size_t)b * H + y) * W + xe) * COUT + co0 + (tid & 3) * 8);
+        }
+    };
+    if constexpr (OUT == kOutSkipGrad) {
+        const int x = min(x0 + j, W - 1);
+        const float *d = a.dp + ((size_t)b * (H / 2) * (W / 2) + x / 2) * COUT + co0 + g * 4;
+#pragma unroll
+        for (int q = 0; q < ND; ++q) {
+            const int y = min(y0 + wave * R + 2 * q, H - 1);
+#pragma unroll
+            for (int rt = 0; rt < 2; ++rt)
+                dp[q][rt] = *reinterpret_cast<const float4 *>(d + (size_t)(y / 2) * (W / 2) * COUT + rt * 16);
+        }
+        if (NCH == 1) read_mask();  // with more chunks the registers do not reach
+    }
     for (int ch = 0; ch < NCH; ++ch) {
         // the copies of every wave have landed
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -176,18 +224,18 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
         __syncthreads();
         if (ch + 1 < NCH) load(ch + 1);
     }
+    if constexpr (OUT == kOutSkipGrad && NCH > 1) read_mask();
 
-    if (OUT == kOutCatGrad && co0 < COUT / 2) {
+    if constexpr (OUT == kOutUpGrad) {
         // 2x2 sums, left to right and top to bottom: rows in this lane's
         // registers, the column at its right in the next lane; H and W are
         // even, so a pair lies inside whole
-        constexpr int CL = COUT / 2;
         const int W2 = W / 2, H2 = H / 2, x = x0 + j;
 #pragma unroll
         for (int ct = 0; ct + 1 < R; ct += 2) {
             const int y = y0 + wave * R + ct;
             const bool in = !(j & 1) && y < H && x < W;
-            const size_t at = (((size_t)b * H2 + y / 2) * W2 + x / 2) * CL + co0 + g * 4;
+            const size_t at = (((size_t)b * H2 + y / 2) * W2 + x / 2) * COUT + co0 + g * 4;
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
                 float s[4];
@@ -196,20 +244,19 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
                     s[i] = (((0.f + acc[ct][rt][i]) + lane_right(acc[ct][rt][i])) + acc[ct + 1][rt][i]) +
                            lane_right(acc[ct + 1][rt][i]);
                 if (!in) continue;
-                const uint2 av = *reinterpret_cast<const uint2 *>(a.act + at + rt * 16);
+                const uint2 av = lv[ct / 2][rt];
                 *reinterpret_cast<uint2 *>(a.pool + at + rt * 16) =
                     make_uint2(pack2(bf_pos(av.x & 0xffffu) ? s[0] : 0.f, bf_pos(av.x >> 16) ? s[1] : 0.f),
                                pack2(bf_pos(av.y & 0xffffu) ? s[2] : 0.f, bf_pos(av.y >> 16) ? s[3] : 0.f));
             }
         }
-    } else if constexpr (OUT == kOutF32 || OUT == kOutCatGrad) {
-        constexpr int CT = OUT == kOutF32 ? COUT : COUT / 2;  // channels stored
-        const int x = x0 + j, c0 = co0 - (COUT - CT);
+    } else if constexpr (OUT == kOutF32) {
+        const int x = x0 + j;
 #pragma unroll
         for (int ct = 0; ct < R; ++ct) {
             const int y = y0 + wave * R + ct;
             if (y >= H || x >= W) continue;
-            float *o = static_cast<float *>(a.out) + (((size_t)b * H + y) * W + x) * CT + c0 + g * 4;
+            float *o = static_cast<float *>(a.out) + (((size_t)b * H + y) * W + x) * COUT + co0 + g * 4;
 #pragma unroll
             for (int rt = 0; rt < 2; ++rt) {
                 const f32x4 v = acc[ct][rt];
@@ -217,9 +264,21 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
             }
         }
     } else {
-        // the tile as bf16(relu(acc + bias)) in LDS, pixel by pixel
+        // the tile as bf16(relu(acc + bias)), or bf16(acc + dp / 4), in LDS,
+        // pixel by pixel
 #pragma unroll
         for (int rt = 0; rt < 2; ++rt) {
+            if constexpr (OUT == kOutSkipGrad) {
+#pragma unroll
+                for (int ct = 0; ct < R; ++ct) {
+                    const float4 d = dp[ct / 2][rt];
+                    const f32x4 v = acc[ct][rt];
+                    *reinterpret_cast<uint2 *>(lds + ((wave * R + ct) * kTW + j) * kSS + rt * 16 + g * 4) =
+                        make_uint2(pack2(v[0] + d.x * 0.25f, v[1] + d.y * 0.25f),
+                                   pack2(v[2] + d.z * 0.25f, v[3] + d.w * 0.25f));
+                }
+                continue;
+            }
             const float *bp = a.bias + co0 + rt * 16 + g * 4;
             const float b0 = bp[0], b1 = bp[1], b2 = bp[2], b3 = bp[3];
 #pragma unroll
@@ -243,12 +302,14 @@ __global__ __launch_bounds__(256, 2) void k_conv3(ConvArgs a, int tx, int ty)
         } else {
             uint16_t *out = static_cast<uint16_t *>(a.out);
 #pragma unroll
-            for (int q = tid; q < TH * kTW * 4; q += 256) {
-                const int p = q >> 2, c8 = q & 3;
+            for (int k = 0; k < R; ++k) {  // TH * kTW pixels, 4 groups each
+                const int q = tid + 256 * k, p = q >> 2, c8 = q & 3;
                 const int y = y0 + p / kTW, x = x0 + p % kTW;
-                const uint4 v = *reinterpret_cast<const uint4 *>(lds + p * kSS + c8 * 8);
-                if (y < H && x < W)
-                    *reinterpret_cast<uint4 *>(out + (((size_t)b * H + y) * W + x) * COUT + co0 + c8 * 8) = v;
+                uint4 v = *reinterpret_cast<const uint4 *>(lds + p * kSS + c8 * 8);
+                if (y >= H || x >= W) continue;
+                const size_t at = (((size_t)b * H + y) * W + x) * COUT + co0 + c8 * 8;
+                if constexpr (OUT == kOutSkipGrad) v = where_positive(v, ev[k]);
+                *reinterpret_cast<uint4 *>(out + at) = v;
             }
             if constexpr (OUT == kOutPool) {
                 const int H2 = H / 2, W2 = W / 2;
@@ -289,8 +350,8 @@ int launch_conv3(const ConvArgs &a, int num_cu, hipStream_t st)
     if (groups(8) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 8>(a, st);
     if (groups(4) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 4>(a, st);
     // (2x2 sums take a wave's rows in pairs)
-    if (OUT == kOutCatGrad || groups(2) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 2>(a, st);
-    if constexpr (OUT != kOutCatGrad) return launch_r<CIN, COUT, MODE, CA, OUT, 1>(a, st);
+    if (OUT == kOutUpGrad || groups(2) >= want) return launch_r<CIN, COUT, MODE, CA, OUT, 2>(a, st);
+    if constexpr (OUT != kOutUpGrad) return launch_r<CIN, COUT, MODE, CA, OUT, 1>(a, st);
 }
 
 // forward
@@ -302,9 +363,12 @@ template int launch_conv3<128, 32, kUpCat, 64, kOutAct>(const ConvArgs &, int, h
 template int launch_conv3<64, 32, kUpCat, 32, kOutAct>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<64, 32, kUpCat, 32, kOutHead>(const ConvArgs &, int, hipStream_t);
 // input gradients
-template int launch_conv3<32, 64, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
-template int launch_conv3<32, 128, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
-template int launch_conv3<64, 256, kPlain, 0, kOutCatGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 32, kPlain, 0, kOutUpGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 64, kPlain, 0, kOutUpGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 128, kPlain, 0, kOutUpGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 32, kPlain, 0, kOutSkipGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<32, 64, kPlain, 0, kOutSkipGrad>(const ConvArgs &, int, hipStream_t);
+template int launch_conv3<64, 128, kPlain, 0, kOutSkipGrad>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<128, 128, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<128, 64, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);
 template int launch_conv3<64, 32, kPlain, 0, kOutF32>(const ConvArgs &, int, hipStream_t);

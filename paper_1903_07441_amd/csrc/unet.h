@@ -42,7 +42,7 @@ struct twg_unet {
     long long bwd_pixels = 0;
     uint16_t *g_d0 = nullptr, *g_d1 = nullptr, *g_d2 = nullptr, *g_e3 = nullptr, *g_e2 = nullptr,
              *g_e1 = nullptr, *g_e0 = nullptr;
-    float *f_c0 = nullptr, *f_c1 = nullptr, *f_c2 = nullptr, *f_p2 = nullptr, *f_p1 = nullptr,
+    float *f_p2 = nullptr, *f_p1 = nullptr,
           *f_p0 = nullptr;
     float *part = nullptr;
     unsigned int *counts = nullptr;  // FREE cells per image

@@ -320,39 +320,6 @@ __global__ void k_zero_words(unsigned int *w, int n)
     if (blockIdx.x == 0 && (int)threadIdx.x < n) w[threadIdx.x] = 0u;
 }
 
-// Gradient of an encoder activation used by a skip connection and by pool():
-// de[b][y][x][c] = bf16((dskip[...][c] + dp[b][y/2][x/2][c] / 4) * [e > 0]),
-// dskip the FP32 input gradient of the skip connection, dp that of the next
-// encoder conv (at half resolution).
-template <int C>
-__global__ __launch_bounds__(256) void k_route_pool(const float *__restrict__ dskip, const float *__restrict__ dp,
-                                                    const uint16_t *__restrict__ e, uint16_t *__restrict__ de,
-                                                    int nb, int H, int W)
-{
-    const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
-    const long long total = (long long)nb * H * W * (C / 8);
-    if (v >= total) return;
-    const int cg = (int)(v % (C / 8));
-    const long long pix = v / (C / 8);
-    const int x = (int)(pix % W);
-    const long long t = pix / W;
-    const int y = (int)(t % H);
-    const int b = (int)(t / H);
-    const float *ps = dskip + (size_t)pix * C + cg * 8;
-    const float *pp = dp + (((size_t)b * (H / 2) + y / 2) * (W / 2) + x / 2) * C + cg * 8;
-    float s[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[i] = ps[i] + pp[i] * 0.25f;
-    const uint4 av = *reinterpret_cast<const uint4 *>(e + (size_t)pix * C + cg * 8);
-    const uint32_t aw[4] = {av.x, av.y, av.z, av.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        if (!bf_pos(aw[i] & 0xffffu)) s[2 * i] = 0.f;
-        if (!bf_pos(aw[i] >> 16)) s[2 * i + 1] = 0.f;
-    }
-    *reinterpret_cast<uint4 *>(de + (size_t)pix * C + cg * 8) = pack8(s);
-}
-
 // ---- input packing and features ------------------------------------------
 // x [P][3] FP32 -> xp [P][4] bf16 (channel 3 zero)
 __global__ __launch_bounds__(256) void k_pack_input(const float *__restrict__ x, uint16_t *__restrict__ xp,
@@ -687,16 +654,6 @@ __global__ __launch_bounds__(256) void k_sum_loss(const float *__restrict__ part
 }
 
 // ---- launch helpers -----------------------------------------------------------
-template <int C>
-int route_pool(const float *dskip, const float *dp, const uint16_t *e, uint16_t *de, int nb, int H, int W,
-               hipStream_t st)
-{
-    const long long total = (long long)nb * H * W * (C / 8);
-    hipLaunchKernelGGL((k_route_pool<C>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, dskip,
-                       dp, e, de, nb, H, W);
-    return last_status();
-}
-
 }  // namespace
 
 // ---- host side ----------------------------------------------------------------
@@ -762,11 +719,20 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     auto grad_args = [&](const uint16_t *g, int l, float *out, int h, int w) {
         return ConvArgs{g, nullptr, wf + L.offw[l], nullptr, out, nullptr, nullptr, nullptr, nullptr, nb, h, w};
     };
-    // of a concatenation: the low activation's gradient, the skip's in FP32
-    auto cat_args = [&](const uint16_t *g, int l, float *skip, const uint16_t *low, uint16_t *dlow, int h, int w) {
-        ConvArgs c = grad_args(g, l, skip, h, w);
+    // of a concatenation: the low activation's gradient (the first cin channels
+    // of layer l's input), then, of the others, that of the skip connection
+    auto up_args = [&](const uint16_t *g, int l, const uint16_t *low, uint16_t *dlow, int h, int w) {
+        ConvArgs c = grad_args(g, l, nullptr, h, w);
         c.pool = dlow;
         c.act = low;
+        return c;
+    };
+    auto skip_args = [&](const uint16_t *g, int l, const float *dp, const uint16_t *e, uint16_t *de, int h, int w) {
+        ConvArgs c = grad_args(g, l, nullptr, h, w);
+        c.wt += (size_t)(L.cin[l] / 2) * 9 * L.cout[l];
+        c.out = de;
+        c.act = e;
+        c.dp = dp;
         return c;
     };
     auto GW = [&](int l) { return n->grad + L.offw[l]; };
@@ -787,28 +753,28 @@ int net_backward(twg_unet *n, int nb, int H, int W, const float *target, const u
     int rc = last_status();
     // d0: input cat(up(d1), e0) at H
     if (!rc) rc = launch_wgrad3<64, 32, kUpCat, 32>(n->d1, n->e0, n->g_d0, n->part, GW(6), nb, H, W, cu, st);
-    if (!rc)
-        rc = launch_conv3<32, 64, kPlain, 0, kOutCatGrad>(cat_args(n->g_d0, 6, n->f_c0, n->d1, n->g_d1, H, W), cu, st);
+    if (!rc) rc = launch_conv3<32, 32, kPlain, 0, kOutUpGrad>(up_args(n->g_d0, 6, n->d1, n->g_d1, H, W), cu, st);
     // d1: input cat(up(d2), e1) at H/2
     if (!rc) rc = launch_wgrad3<128, 32, kUpCat, 64>(n->d2, n->e1, n->g_d1, n->part, GW(5), nb, H1, W1, cu, st);
-    if (!rc)
-        rc = launch_conv3<32, 128, kPlain, 0, kOutCatGrad>(cat_args(n->g_d1, 5, n->f_c1, n->d2, n->g_d2, H1, W1), cu, st);
+    if (!rc) rc = launch_conv3<32, 64, kPlain, 0, kOutUpGrad>(up_args(n->g_d1, 5, n->d2, n->g_d2, H1, W1), cu, st);
     // d2: input cat(up(e3), e2) at H/4
     if (!rc) rc = launch_wgrad3<256, 64, kUpCat, 128>(n->e3, n->e2, n->g_d2, n->part, GW(4), nb, H2, W2, cu, st);
-    if (!rc)
-        rc = launch_conv3<64, 256, kPlain, 0, kOutCatGrad>(cat_args(n->g_d2, 4, n->f_c2, n->e3, n->g_e3, H2, W2), cu, st);
+    if (!rc) rc = launch_conv3<64, 128, kPlain, 0, kOutUpGrad>(up_args(n->g_d2, 4, n->e3, n->g_e3, H2, W2), cu, st);
     // e3: input pool(e2) at H/8
     if (!rc) rc = launch_wgrad3<128, 128, kPlain, 0>(n->p2, nullptr, n->g_e3, n->part, GW(3), nb, H3, W3, cu, st);
     if (!rc) rc = launch_conv3<128, 128, kPlain, 0, kOutF32>(grad_args(n->g_e3, 3, n->f_p2, H3, W3), cu, st);
-    if (!rc) rc = route_pool<128>(n->f_c2, n->f_p2, n->e2, n->g_e2, nb, H2, W2, st);
+    if (!rc)
+        rc = launch_conv3<64, 128, kPlain, 0, kOutSkipGrad>(skip_args(n->g_d2, 4, n->f_p2, n->e2, n->g_e2, H2, W2), cu, st);
     // e2: input pool(e1) at H/4
     if (!rc) rc = launch_wgrad3<64, 128, kPlain, 0>(n->p1, nullptr, n->g_e2, n->part, GW(2), nb, H2, W2, cu, st);
     if (!rc) rc = launch_conv3<128, 64, kPlain, 0, kOutF32>(grad_args(n->g_e2, 2, n->f_p1, H2, W2), cu, st);
-    if (!rc) rc = route_pool<64>(n->f_c1, n->f_p1, n->e1, n->g_e1, nb, H1, W1, st);
+    if (!rc)
+        rc = launch_conv3<32, 64, kPlain, 0, kOutSkipGrad>(skip_args(n->g_d1, 5, n->f_p1, n->e1, n->g_e1, H1, W1), cu, st);
     // e1: input pool(e0) at H/2
     if (!rc) rc = launch_wgrad3<32, 64, kPlain, 0>(n->p0, nullptr, n->g_e1, n->part, GW(1), nb, H1, W1, cu, st);
     if (!rc) rc = launch_conv3<64, 32, kPlain, 0, kOutF32>(grad_args(n->g_e1, 1, n->f_p0, H1, W1), cu, st);
-    if (!rc) rc = route_pool<32>(n->f_c0, n->f_p0, n->e0, n->g_e0, nb, H, W, st);
+    if (!rc)
+        rc = launch_conv3<32, 32, kPlain, 0, kOutSkipGrad>(skip_args(n->g_d0, 6, n->f_p0, n->e0, n->g_e0, H, W), cu, st);
     // e0: input x (padded to 32 channels)
     if (!rc) rc = launch_wgrad_in(n->xp, n->g_e0, n->part, GW(0), nb, H, W, cu, st);
     return rc;

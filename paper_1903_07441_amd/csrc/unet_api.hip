@@ -66,7 +66,7 @@ int ensure_bwd(twg_unet *n, long long P)
     // bf16 gradients, FP32 input gradients, split-K partial sums
     const size_t parts = std::max<size_t>(kPartFloats, 34 * ((P0 + 255) / 256));
     const size_t sizes[] = {al(P0 * 32 * 2), al(P1 * 32 * 2), al(P2 * 64 * 2), al(P3 * 128 * 2), al(P2 * 128 * 2),
-                            al(P1 * 64 * 2), al(P0 * 32 * 2), al(P0 * 32 * 4), al(P1 * 64 * 4), al(P2 * 128 * 4),
+                            al(P1 * 64 * 2), al(P0 * 32 * 2),
                             al(P3 * 128 * 4), al(P2 * 64 * 4), al(P1 * 32 * 4), al(parts * 4),
                             al((size_t)65536 * 4)};
     size_t bytes = 0;
@@ -85,9 +85,6 @@ int ensure_bwd(twg_unet *n, long long P)
     n->g_e2 = reinterpret_cast<uint16_t *>(take());
     n->g_e1 = reinterpret_cast<uint16_t *>(take());
     n->g_e0 = reinterpret_cast<uint16_t *>(take());
-    n->f_c0 = reinterpret_cast<float *>(take());
-    n->f_c1 = reinterpret_cast<float *>(take());
-    n->f_c2 = reinterpret_cast<float *>(take());
     n->f_p2 = reinterpret_cast<float *>(take());
     n->f_p1 = reinterpret_cast<float *>(take());
     n->f_p0 = reinterpret_cast<float *>(take());
