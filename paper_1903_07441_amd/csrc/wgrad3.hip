@@ -370,11 +370,13 @@ __global__ __launch_bounds__(256) void k_sum_parts(const float *__restrict__ par
 
 int last_status() { return hipGetLastError() == hipSuccess ? TWG_OK : TWG_EDEVICE; }
 
-// Splits of the pixel reduction: two workgroups per CU, at most one per tile,
+// Splits of the pixel reduction: per_cu workgroups per CU (two; with 128 output
+// channels, whose products fill a CU by themselves, one: its partial sums are
+// half the bytes, 18 + 13 to 16 + 8 us at 32 x 32 x 16), at most one per tile,
 // and partial sums within the scratch.
-int choose_split(int nchunk, int ntile, int count, int num_cu)
+int choose_split(int nchunk, int ntile, int count, int per_cu, int num_cu)
 {
-    const int s = std::min(std::max(1, 2 * std::max(1, num_cu) / nchunk), (int)(kPartFloats / count));
+    const int s = std::min(std::max(1, per_cu * std::max(1, num_cu) / nchunk), (int)(kPartFloats / count));
     return std::max(1, std::min(s, ntile));
 }
 
@@ -397,7 +399,7 @@ int launch_wgrad3(const uint16_t *A, const uint16_t *Bs, const uint16_t *dout, f
                   int W, int num_cu, hipStream_t st)
 {
     constexpr int NCH = CIN / kCK, count = COUT * 9 * CIN + COUT;
-    const int ns = choose_split(NCH, tiles(nb, H, W, Shape<COUT>::TH), count, num_cu);
+    const int ns = choose_split(NCH, tiles(nb, H, W, Shape<COUT>::TH), count, COUT > 64 ? 1 : 2, num_cu);
     hipLaunchKernelGGL((k_wgrad3<CIN, COUT, MODE, CA>), dim3(NCH * ns), dim3(256), 0, st, A, Bs, dout, part, nb, H, W,
                        ns);
     return sum_parts<false>(part, g, count, ns, st);
@@ -407,7 +409,7 @@ int launch_wgrad_in(const uint16_t *x4, const uint16_t *dout, float *part, float
                     hipStream_t st)
 {
     constexpr int count = 32 * 32 + 32;
-    const int ns = choose_split(1, tiles(nb, H, W, 8), count, num_cu);
+    const int ns = choose_split(1, tiles(nb, H, W, 8), count, 2, num_cu);
     hipLaunchKernelGGL(k_wgrad_in, dim3(ns), dim3(256), 0, st, x4, dout, part, nb, H, W, ns);
     return sum_parts<true>(part, g, count, ns, st);
 }
