@@ -158,16 +158,33 @@ __device__ __forceinline__ bool disc_at(int j, bool per_object, double px, doubl
     return true;
 }
 
-// 32 x 8 threads of 8 cells.  VEC: pitch and bases allow 8-byte class and
-// 16-byte ring stores.  ELL: the elliptical metric (its FP64 code is kept out
-// of the other kernels).
-template <bool VEC, bool ELL>
-__global__ __launch_bounds__(256) void k_map(int nx, int ny, int pitch, int xr, int yr, int xg, int yg, int W,
-                                             float inv_w, int border, WarpMode wm,
-                                             const uint8_t *__restrict__ static_occ, uint8_t *__restrict__ cls,
-                                             uint16_t *__restrict__ ring)
+// arguments of a map update's kernels (pairs: (obstacle, ring); waves: those
+// that share them)
+struct MapArgs {
+    int nx, ny, pitch, xr, yr, xg, yg, W, border, J, per_object, vec;
+    float inv_w;
+    WarpMode wm;
+    const uint8_t *static_occ;
+    uint8_t *cls;
+    uint16_t *ring;
+    const double *pos, *vel, *rad, *cov;
+    double kappa, vr;
+    long long pairs, waves;
+};
+
+// Eight cells from x0 on.  VEC: pitch and bases allow 8-byte class and 16-byte
+// ring stores.  ELL: the elliptical metric (its FP64 code is kept out of the
+// other kernels).
+template <bool ELL>
+__device__ __forceinline__ void map_cells(const MapArgs &a, bool VEC, int x0, int y)
 {
-    const int x0 = (blockIdx.x * 32 + (threadIdx.x & 31)) * 8, y = blockIdx.y * 8 + (threadIdx.x >> 5);
+    const int nx = a.nx, ny = a.ny, pitch = a.pitch, xr = a.xr, yr = a.yr, xg = a.xg, yg = a.yg, W = a.W;
+    const int border = a.border;
+    const float inv_w = a.inv_w;
+    const WarpMode wm = a.wm;
+    const uint8_t *__restrict__ static_occ = a.static_occ;
+    uint8_t *__restrict__ cls = a.cls;
+    uint16_t *__restrict__ ring = a.ring;
     if (x0 >= nx || y >= ny) return;
     const size_t i = (size_t)y * pitch + x0;
     const bool whole = VEC && x0 + 8 <= nx;
@@ -209,20 +226,30 @@ __global__ __launch_bounds__(256) void k_map(int nx, int ny, int pitch, int xr, 
     }
 }
 
+// 32 x 8 threads of 8 cells
+template <bool VEC, bool ELL>
+__global__ __launch_bounds__(256) void k_map(MapArgs a)
+{
+    map_cells<ELL>(a, VEC, (blockIdx.x * 32 + (threadIdx.x & 31)) * 8, blockIdx.y * 8 + (threadIdx.x >> 5));
+}
+
 // Wave w of n_waves takes the (obstacle, ring) pairs w, w + n_waves, ..., one
 // a lane, so that the rings of one obstacle (a disc that moves with the rings
 // meets a hundred of them) go to different waves, then marks the discs that
 // survive one after another.
 template <bool ELL>
-__global__ __launch_bounds__(256) void k_discs(long long n_pairs, long long n_waves, int J, int per_object,
-                                               const double *__restrict__ pos, const double *__restrict__ vel,
-                                               const double *__restrict__ rad, const double *__restrict__ cov,
-                                               double kappa, WarpMode wm, int W, float inv_w, double vr, int nx, int ny,
-                                               int pitch, int xr, int yr, int xg, int yg, int border,
-                                               uint8_t *__restrict__ cls)
+__device__ __forceinline__ void mark_discs(const MapArgs &a, long long w)
 {
     const int lane = threadIdx.x & 63;
-    const long long w = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nx = a.nx, ny = a.ny, pitch = a.pitch, xr = a.xr, yr = a.yr, xg = a.xg, yg = a.yg, W = a.W, J = a.J;
+    const int border = a.border, per_object = a.per_object;
+    const float inv_w = a.inv_w;
+    const double kappa = a.kappa, vr = a.vr;
+    const WarpMode wm = a.wm;
+    const long long n_pairs = a.pairs, n_waves = a.waves;
+    const double *__restrict__ pos = a.pos, *__restrict__ vel = a.vel, *__restrict__ rad = a.rad;
+    const double *__restrict__ cov = a.cov;
+    uint8_t *cls = a.cls;
     if (w >= n_waves) return;
     // cells a disc may mark: not the border walls
     const int xa = border ? 1 : 0, xb = border ? nx - 2 : nx - 1, ya = border ? 1 : 0, yb = border ? ny - 2 : ny - 1;
@@ -276,6 +303,25 @@ __global__ __launch_bounds__(256) void k_discs(long long n_pairs, long long n_wa
     }
 }
 
+template <bool ELL>
+__global__ __launch_bounds__(256) void k_discs(MapArgs a)
+{
+    mark_discs<ELL>(a, (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+}
+
+// A small map whole in one workgroup: the cells, then the discs.  Each launch
+// costs a call 3 us on the host, which bounds small maps (64 x 64 with 10
+// discs: 10.5 us a call in two launches, 7.5 in one).
+constexpr int kSmallCells = 16384, kSmallWaves = 16, kSmallPairs = 12 * kSmallWaves;
+template <bool ELL>
+__global__ __launch_bounds__(64 * kSmallWaves) void k_map_small(MapArgs a)
+{
+    const int groups = (a.nx + 7) / 8;
+    for (int u = threadIdx.x; u < groups * a.ny; u += 64 * kSmallWaves) map_cells<ELL>(a, a.vec, u % groups * 8, u / groups);
+    __syncthreads();
+    mark_discs<ELL>(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+}
+
 int host_ring(long long dx, long long dy, int W)
 {
     unsigned long long d2 = (unsigned long long)(dx * dx + dy * dy);
@@ -309,27 +355,34 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
     const float inv_w = 1.0f / (float)p.ring_width;
     const auto al = [](const void *q, uintptr_t a) { return (reinterpret_cast<uintptr_t>(q) & (a - 1)) == 0; };
     const bool vec = pitch % 8 == 0 && al(cls, 8) && al(ring, 16) && al(static_occ, 8);
-    auto map = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((nx + 255) / 256, (ny + 7) / 8), dim3(256), 0, st, nx, ny, pitch, p.robot_x,
-                           p.robot_y, p.goal_x, p.goal_y, p.ring_width, inv_w, p.border_walls, wm, static_occ, cls,
-                           ring);
-    };
     const bool ell = p.ring_mode == 1;
-    if (vec) ell ? map(k_map<true, true>) : map(k_map<true, false>);
-    else ell ? map(k_map<false, true>) : map(k_map<false, false>);
-    if (hipGetLastError() != hipSuccess) return set_err(ctx, TWG_EDEVICE, "map launch failed");
-    if (n_obs == 0) return TWG_OK;
     // a full wave's worth of pairs each, but at least 2048 waves (or one pair
     // each): a wave marks its discs one after another
     const long long pairs = (long long)n_obs * (p.per_object ? 1 : J);
-    const long long waves = std::max((pairs + 63) / 64, std::min(pairs, 2048LL));
-    auto discs = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, st, pairs, waves, J, p.per_object,
-                           pos, vel, rad, p.cov, p.kappa, wm, p.ring_width, inv_w, p.robot_speed, nx, ny, pitch,
-                           p.robot_x, p.robot_y, p.goal_x, p.goal_y, p.border_walls, cls);
+    MapArgs a{nx, ny, pitch, p.robot_x, p.robot_y, p.goal_x, p.goal_y, p.ring_width, p.border_walls, J, p.per_object,
+              vec, inv_w, wm, static_occ, cls, ring, pos, vel, rad, p.cov, p.kappa, p.robot_speed, pairs,
+              std::max((pairs + 63) / 64, std::min(pairs, 2048LL))};
+    auto launch = [&](auto kernel, dim3 grid, int threads) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, a);
+        return hipGetLastError() == hipSuccess;
     };
-    ell ? discs(k_discs<true>) : discs(k_discs<false>);
-    if (hipGetLastError() != hipSuccess) return set_err(ctx, TWG_EDEVICE, "rasterize launch failed");
+    // one launch where 16 waves soon have every cell and disc: up to 12 discs a
+    // wave (7.5 to 9.3 us a call against 10.5 in two launches; with 20 discs a
+    // wave it is 11)
+    if ((long long)nx * ny <= kSmallCells && pairs > 0 && pairs <= kSmallPairs) {
+        a.waves = std::min<long long>(pairs, kSmallWaves);
+        const bool ok = ell ? launch(k_map_small<true>, dim3(1), 64 * kSmallWaves)
+                            : launch(k_map_small<false>, dim3(1), 64 * kSmallWaves);
+        return ok ? TWG_OK : set_err(ctx, TWG_EDEVICE, "map launch failed");
+    }
+    const dim3 grid((nx + 255) / 256, (ny + 7) / 8);
+    const bool ok = vec ? (ell ? launch(k_map<true, true>, grid, 256) : launch(k_map<true, false>, grid, 256))
+                        : (ell ? launch(k_map<false, true>, grid, 256) : launch(k_map<false, false>, grid, 256));
+    if (!ok) return set_err(ctx, TWG_EDEVICE, "map launch failed");
+    if (n_obs == 0) return TWG_OK;
+    const dim3 blocks((unsigned)((a.waves + 3) / 4));
+    if (!(ell ? launch(k_discs<true>, blocks, 256) : launch(k_discs<false>, blocks, 256)))
+        return set_err(ctx, TWG_EDEVICE, "rasterize launch failed");
     return TWG_OK;
 }
 
