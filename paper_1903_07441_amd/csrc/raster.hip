@@ -80,16 +80,22 @@ struct WarpMode {
     double hc, hs;  // heading
 };
 
-// floor(sqrt(n)) / W for the squared distance of two cells (n < 2^31, so the
-// root is below 46341): the hardware square root is within 0.02 of it and the
-// product with 1 / W within 0.01, so one step up or down makes each exact
+// floor(floor(sqrt(n)) / W) for a squared distance of two cells: the largest j
+// with (j W)^2 <= n.  n < 2^31, so the root is below 46341: the hardware root
+// is within 0.02 of it and the product with 1 / W within 0.01 of its quotient,
+// so one step up or down makes j exact.  Every product has 24-bit factors (a
+// 32-bit multiply takes four times as long): W counts up to 65536, where every
+// j is 0, and the next ring's edge up to 65535, beyond any root.
+__device__ __forceinline__ int ring_of_square(uint32_t n, uint32_t W, float inv_w)
+{
+    uint32_t j = (uint32_t)(__builtin_amdgcn_sqrtf((float)n) * inv_w);
+    const uint32_t t = __umul24(j, W), u = min(t + W, 65535u);
+    j -= __umul24(t, t) > n ? 1u : 0u;
+    return (int)(j + (__umul24(u, u) <= n ? 1u : 0u));
+}
 __device__ __forceinline__ int ring_of_cells(int dx, int dy, int W, float inv_w)
 {
-    const uint32_t n = (uint32_t)(dx * dx) + (uint32_t)dy * (uint32_t)dy;
-    uint32_t s = (uint32_t)__builtin_amdgcn_sqrtf((float)n);
-    s = s * s > n ? s - 1u : (s + 1u) * (s + 1u) <= n ? s + 1u : s;
-    uint32_t j = (uint32_t)((float)s * inv_w);
-    return (int)(j * (uint32_t)W > s ? j - 1u : (j + 1u) * (uint32_t)W <= s ? j + 1u : j);
+    return ring_of_square((uint32_t)(__mul24(dx, dx) + __mul24(dy, dy)), (uint32_t)min(W, 65536), inv_w);
 }
 
 // Disc radius with covariance inflation: r + min(W, kappa sqrt(lambda_max)),
@@ -188,39 +194,45 @@ __device__ __forceinline__ void map_cells(const MapArgs &a, bool VEC, int x0, in
     if (x0 >= nx || y >= ny) return;
     const size_t i = (size_t)y * pitch + x0;
     const bool whole = VEC && x0 + 8 <= nx;
-    uint8_t occ[8] = {};
+    // classes, a byte each: static occupancy, then the goal, then the walls
+    const uint64_t kOnes = 0x0101010101010101ull;
+    uint64_t c = 0ull;
     if (static_occ) {
         if (whole) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(static_occ + i);
-#pragma unroll
-            for (int k = 0; k < 8; ++k) occ[k] = (uint8_t)((k < 4 ? v.x >> (8 * k) : v.y >> (8 * (k - 4))) & 0xffu);
+            const uint64_t v = *reinterpret_cast<const uint64_t *>(static_occ + i);
+            c = ((((v & 0x7f * kOnes) + 0x7f * kOnes) | v) >> 7 & kOnes) * TWG_CELL_OBST;
         } else {
             for (int k = 0; k < 8; ++k)
-                if (x0 + k < nx) occ[k] = static_occ[i + k];
+                if (x0 + k < nx && static_occ[i + k]) c |= (uint64_t)TWG_CELL_OBST << 8 * k;
         }
     }
-    uint32_t c[8], r[8];
+    auto set = [&](int k, uint64_t v) { c = (c & ~(0xffull << 8 * k)) | v << 8 * k; };
+    if (y == yg && xg >= x0 && xg < x0 + 8) set(xg - x0, TWG_CELL_GOAL);
+    if (border) {
+        if (y == 0 || y == ny - 1) c = TWG_CELL_WALL * kOnes;
+        if (x0 == 0) set(0, TWG_CELL_WALL);
+        if (nx - 1 - x0 < 8) set(nx - 1 - x0, TWG_CELL_WALL);
+    }
+    uint32_t r[8];
+    if (ring) {
+        const int dx = x0 - xr, dy = y - yr;
+        const uint32_t Wc = (uint32_t)min(W, 65536);
+        uint32_t n = (uint32_t)(__mul24(dx, dx) + __mul24(dy, dy));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int x = x0 + k;
-        c[k] = occ[k] ? TWG_CELL_OBST : TWG_CELL_FREE;
-        if (x == xg && y == yg) c[k] = TWG_CELL_GOAL;
-        if (border && (x == 0 || y == 0 || x == nx - 1 || y == ny - 1)) c[k] = TWG_CELL_WALL;
-        r[k] = 0u;
-        if (ring)
-            r[k] = (uint32_t)(ELL ? ring_ellipse(x - xr, y - yr, wm.hc, wm.hs, W)
-                                  : ring_of_cells(x - xr, y - yr, W, inv_w));
+        for (int k = 0; k < 8; ++k) {
+            r[k] = (uint32_t)(ELL ? ring_ellipse(dx + k, dy, wm.hc, wm.hs, W) : ring_of_square(n, Wc, inv_w));
+            n += (uint32_t)(2 * (dx + k) + 1);
+        }
     }
     if (whole) {
-        *reinterpret_cast<uint2 *>(cls + i) = make_uint2(c[0] | c[1] << 8 | c[2] << 16 | c[3] << 24,
-                                                         c[4] | c[5] << 8 | c[6] << 16 | c[7] << 24);
+        *reinterpret_cast<uint64_t *>(cls + i) = c;
         if (ring)
             *reinterpret_cast<uint4 *>(ring + i) = make_uint4(r[0] | r[1] << 16, r[2] | r[3] << 16, r[4] | r[5] << 16,
                                                               r[6] | r[7] << 16);
     } else {
         for (int k = 0; k < 8; ++k)
             if (x0 + k < nx) {
-                cls[i + k] = (uint8_t)c[k];
+                cls[i + k] = (uint8_t)(c >> 8 * k);
                 if (ring) ring[i + k] = (uint16_t)r[k];
             }
     }
