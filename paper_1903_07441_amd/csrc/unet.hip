@@ -203,6 +203,17 @@ __device__ __forceinline__ float pair_sums(float a, float b)
     return __uint_as_float(x) + __uint_as_float(y);
 }
 
+// bytes of w that are zero
+__device__ __forceinline__ int zero_bytes(uint32_t w)
+{
+    return __popc(~(((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
+}
+
+// Rows a thread takes, four apart (a block: 64 columns, 4 kRows rows), in the
+// kernels that go over a map's cells: their loads are in flight together.
+constexpr int kRows = 4;
+dim3 rows_grid(int nx, int ny) { return dim3((nx + 63) / 64, (ny + 4 * kRows - 1) / (4 * kRows)); }
+
 // Training head: masked MSE over FREE cells.  Per pixel: y, diff = y - t
 // (0 outside the mask), loss += diff^2 / (n_b B), dy = 2 diff / (n_b B),
 // dd0 = bf16(dy * hw * [d0 > 0]); block partial sums of the head gradients
@@ -270,6 +281,19 @@ __global__ __launch_bounds__(256) void k_head_loss(const uint16_t *__restrict__ 
     }
 }
 
+// a network value into a cell of class c
+__device__ __forceinline__ void put_psi(uint8_t c, float v, float *psi, unsigned int *bad)
+{
+    if (c == TWG_CELL_FREE) {
+        if (!isfinite(v)) atomicOr(bad, 1u);
+        *psi = fminf(fmaxf(v, 0.f), 1.f);
+    } else if (c == TWG_CELL_OBST || c == TWG_CELL_WALL) {
+        *psi = 0.f;
+    } else if (c == TWG_CELL_GOAL) {
+        *psi = 1.f;
+    }
+}
+
 // Inference head into a field: FREE cells get clamp(y, 0, 1); OBST/WALL 0,
 // GOAL 1; FIXED cells keep their value.  The network runs on a padded
 // Hp x Wp frame; only the grid's nx x ny cells are written.
@@ -280,18 +304,20 @@ __global__ __launch_bounds__(256) void k_head_psi(const float *__restrict__ yv, 
                                                   unsigned int *bad)
 {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= nx || y >= ny) return;
-    const size_t i = (size_t)y * pitch + x;
-    const uint8_t c = cls[i];
-    if (c == TWG_CELL_FREE) {
-        const float v = yv[(size_t)y * Wp + x];
-        if (!isfinite(v)) atomicOr(bad, 1u);
-        psi[i] = fminf(fmaxf(v, 0.f), 1.f);
-    } else if (c == TWG_CELL_OBST || c == TWG_CELL_WALL) {
-        psi[i] = 0.f;
-    } else if (c == TWG_CELL_GOAL) {
-        psi[i] = 1.f;
+    const int y0 = blockIdx.y * 4 * kRows + (threadIdx.x >> 6);
+    if (x >= nx) return;
+    uint8_t c[kRows];
+    float v[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = min(y0 + 4 * k, ny - 1);
+        c[k] = cls[(size_t)y * pitch + x];
+        v[k] = yv[(size_t)y * Wp + x];
+    }
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = y0 + 4 * k;
+        if (y < ny) put_psi(c[k], v[k], psi + (size_t)y * pitch + x, bad);
     }
 }
 
@@ -342,24 +368,35 @@ __global__ __launch_bounds__(256) void k_features(const uint8_t *__restrict__ cl
     const unsigned int jm = ring ? *jmax : 0u;
     const float inv_jmax = jm > 0u ? 1.f / (float)jm : 0.f;
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= Wp || y >= Hp) return;
-    float occ = 1.f, rt = 0.f;
-    if (x < nx && y < ny) {
-        const size_t i = (size_t)y * pitch + x;
-        const uint8_t c = cls[i];
-        occ = (c == TWG_CELL_OBST || c == TWG_CELL_WALL) ? 1.f : 0.f;
-        if (ring) rt = (float)ring[i] * inv_jmax;
+    const int y0 = blockIdx.y * 4 * kRows + (threadIdx.x >> 6);
+    if (x >= Wp) return;
+    uint8_t c[kRows];
+    uint16_t j[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const size_t i = (size_t)min(y0 + 4 * k, ny - 1) * pitch + min(x, nx - 1);
+        c[k] = cls[i];
+        j[k] = ring ? ring[i] : (uint16_t)0;
     }
-    const float ddx = (float)(x - gx), ddy = (float)(y - gy);
-    const float gd = sqrtf(ddx * ddx + ddy * ddy) * inv_diag;
-    const size_t p = (size_t)y * Wp + x;
-    if (xf) {
-        xf[3 * p] = occ;
-        xf[3 * p + 1] = gd;
-        xf[3 * p + 2] = rt;
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = y0 + 4 * k;
+        if (y >= Hp) break;
+        float occ = 1.f, rt = 0.f;
+        if (x < nx && y < ny) {
+            occ = (c[k] == TWG_CELL_OBST || c[k] == TWG_CELL_WALL) ? 1.f : 0.f;
+            rt = (float)j[k] * inv_jmax;
+        }
+        const float ddx = (float)(x - gx), ddy = (float)(y - gy);
+        const float gd = sqrtf(ddx * ddx + ddy * ddy) * inv_diag;
+        const size_t p = (size_t)y * Wp + x;
+        if (xf) {
+            xf[3 * p] = occ;
+            xf[3 * p + 1] = gd;
+            xf[3 * p + 2] = rt;
+        }
+        if (xp) *reinterpret_cast<uint2 *>(xp + p * 4) = make_uint2(pack2(occ, gd), pack2(rt, 0.f));
     }
-    if (xp) *reinterpret_cast<uint2 *>(xp + p * 4) = make_uint2(pack2(occ, gd), pack2(rt, 0.f));
 }
 
 // ---- coarse-scale warm start ------------------------------------------------
@@ -384,18 +421,33 @@ __global__ __launch_bounds__(256) void k_features_coarse(const uint8_t *__restri
     const int X = blockIdx.x * 64 + (threadIdx.x & 63);
     const int Y = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (X >= Wc || Y >= Hc) return;
+    // a block inside the grid is read four cells at a time where rows are
+    // aligned for that
+    const bool words = !(f & 3) && !(pitch & 3) && !((uintptr_t)cls & 3);
     int blocked = 0, nfree = 0;
-    for (int dy = 0; dy < f; ++dy) {
-        const int y = Y * f + dy;
-        for (int dx = 0; dx < f; ++dx) {
-            const int x = X * f + dx;
-            if (x >= nx || y >= ny) {
-                ++blocked;
-                continue;
+    if (words && (X + 1) * f <= nx && (Y + 1) * f <= ny) {
+        const uint8_t *p = cls + (size_t)Y * f * pitch + X * f;
+        for (int q = 0; q < f / 4; ++q) {
+#pragma unroll 8
+            for (int dy = 0; dy < f; ++dy) {
+                const uint32_t w = *reinterpret_cast<const uint32_t *>(p + (size_t)dy * pitch + 4 * q);
+                blocked += zero_bytes(w ^ 0x01010101u * TWG_CELL_OBST) + zero_bytes(w ^ 0x01010101u * TWG_CELL_WALL);
+                nfree += zero_bytes(w);
             }
-            const uint8_t c = cls[(size_t)y * pitch + x];
-            blocked += (c == TWG_CELL_OBST || c == TWG_CELL_WALL) ? 1 : 0;
-            nfree += c == TWG_CELL_FREE ? 1 : 0;
+        }
+    } else {
+        for (int dy = 0; dy < f; ++dy) {
+            const int y = Y * f + dy;
+            for (int dx = 0; dx < f; ++dx) {
+                const int x = X * f + dx;
+                if (x >= nx || y >= ny) {
+                    ++blocked;
+                    continue;
+                }
+                const uint8_t c = cls[(size_t)y * pitch + x];
+                blocked += (c == TWG_CELL_OBST || c == TWG_CELL_WALL) ? 1 : 0;
+                nfree += c == TWG_CELL_FREE ? 1 : 0;
+            }
         }
     }
     const float occ = (float)blocked / (float)(f * f);
@@ -454,43 +506,68 @@ __global__ __launch_bounds__(256) void k_up_psi(const float *__restrict__ yc, in
                                                 int ny, int pitch, unsigned int *bad)
 {
     const int x = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int y = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (x >= nx || y >= ny) return;
-    const size_t i = (size_t)y * pitch + x;
-    const uint8_t c = cls[i];
-    if (c == TWG_CELL_FREE) {
-        const float inv_f = 1.f / (float)f;  // f is a power of two: exact
-        const float u = fminf(fmaxf(((float)x + 0.5f) * inv_f - 0.5f, 0.f), (float)(Wc - 1));
+    const int row = blockIdx.y * 4 * kRows + (threadIdx.x >> 6);
+    if (x >= nx) return;
+    const float inv_f = 1.f / (float)f;  // f is a power of two: exact
+    const float u = fminf(fmaxf(((float)x + 0.5f) * inv_f - 0.5f, 0.f), (float)(Wc - 1));
+    const int x0 = (int)u, x1 = min(x0 + 1, Wc - 1);
+    const float a = u - (float)x0;
+    uint8_t c[kRows];
+    float t[kRows][4], b[kRows];
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = min(row + 4 * k, ny - 1);
         const float v = fminf(fmaxf(((float)y + 0.5f) * inv_f - 0.5f, 0.f), (float)(Hc - 1));
-        const int x0 = (int)u, y0 = (int)v;
-        const int x1 = min(x0 + 1, Wc - 1), y1 = min(y0 + 1, Hc - 1);
-        const float a = u - (float)x0, b = v - (float)y0;
-        const float top = (1.f - a) * yc[(size_t)y0 * Wc + x0] + a * yc[(size_t)y0 * Wc + x1];
-        const float bot = (1.f - a) * yc[(size_t)y1 * Wc + x0] + a * yc[(size_t)y1 * Wc + x1];
-        const float val = (1.f - b) * top + b * bot;
-        if (!isfinite(val)) atomicOr(bad, 1u);
-        psi[i] = fminf(fmaxf(val, 0.f), 1.f);
-    } else if (c == TWG_CELL_OBST || c == TWG_CELL_WALL) {
-        psi[i] = 0.f;
-    } else if (c == TWG_CELL_GOAL) {
-        psi[i] = 1.f;
+        const int y0 = (int)v, y1 = min(y0 + 1, Hc - 1);
+        b[k] = v - (float)y0;
+        c[k] = cls[(size_t)y * pitch + x];
+        t[k][0] = yc[(size_t)y0 * Wc + x0];
+        t[k][1] = yc[(size_t)y0 * Wc + x1];
+        t[k][2] = yc[(size_t)y1 * Wc + x0];
+        t[k][3] = yc[(size_t)y1 * Wc + x1];
+    }
+#pragma unroll
+    for (int k = 0; k < kRows; ++k) {
+        const int y = row + 4 * k;
+        const float top = (1.f - a) * t[k][0] + a * t[k][1];
+        const float bot = (1.f - a) * t[k][2] + a * t[k][3];
+        const float val = (1.f - b[k]) * top + b[k] * bot;
+        if (y < ny) put_psi(c[k], val, psi + (size_t)y * pitch + x, bad);
     }
 }
 
-// largest ring number of a grid; *out must be zero beforehand.  Grid-stride
-// over rows, wave and block maxima, one atomic per block.
-__global__ __launch_bounds__(256) void k_ring_max(const uint16_t *__restrict__ ring, int nx, int ny, int pitch,
-                                                  unsigned int *out)
+// Largest ring number of a grid; *out must be zero beforehand.  A wave takes
+// runs of 512 cells of a row, eight a lane in one load where rows are aligned
+// for that; one atomic per block, of which there are few (they meet on one
+// address, 10 ns each: 512 blocks of single-cell loads took 16 us at
+// 2048 x 2048).
+constexpr int kRingThreads = 512, kRingBlocks = 128;
+__global__ __launch_bounds__(kRingThreads) void k_ring_max(const uint16_t *__restrict__ ring, int nx, int ny, int pitch,
+                                                           unsigned int *out)
 {
-    __shared__ unsigned int red[4];
+    constexpr int NW = kRingThreads / 64;
+    __shared__ unsigned int red[NW];
+    const int lane = threadIdx.x & 63;
+    const int runs = (nx + 511) / 512, items = ny * runs;
+    const bool quads = !((uintptr_t)ring & 15) && !(pitch & 7);
     unsigned int r = 0;
-    for (int y = blockIdx.x; y < ny; y += gridDim.x)
-        for (int x = threadIdx.x; x < nx; x += 256) r = max(r, (unsigned int)ring[(size_t)y * pitch + x]);
+#pragma unroll 4
+    for (int it = blockIdx.x * NW + (threadIdx.x >> 6); it < items; it += gridDim.x * NW) {
+        const int y = it / runs, x0 = (it - y * runs) * 512 + 8 * lane;
+        const uint16_t *p = ring + (size_t)y * pitch + x0;
+        if (quads && x0 + 8 <= nx) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(p);
+            r = max(r, max(max(v.x & 0xffffu, v.x >> 16), max(v.y & 0xffffu, v.y >> 16)));
+            r = max(r, max(max(v.z & 0xffffu, v.z >> 16), max(v.w & 0xffffu, v.w >> 16)));
+        } else {
+            for (int k = 0; k < 8 && x0 + k < nx; ++k) r = max(r, (unsigned int)p[k]);
+        }
+    }
     for (int o = 32; o > 0; o >>= 1) r = max(r, (unsigned int)__shfl_xor((int)r, o));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = r;
+    if (lane == 0) red[threadIdx.x >> 6] = r;
     __syncthreads();
     if (threadIdx.x == 0) {
-        r = max(max(red[0], red[1]), max(red[2], red[3]));
+        for (int k = 1; k < NW; ++k) r = max(r, red[k]);
         if (r) atomicMax(out, r);
     }
 }
@@ -611,14 +688,11 @@ __global__ __launch_bounds__(256) void k_count_free(const uint8_t *__restrict__ 
     const uint8_t *c = cls + (size_t)blockIdx.y * hw_pixels;
     unsigned int n = 0;
     const int first = blockIdx.x * 256 + threadIdx.x, step = gridDim.x * 256;
-    auto zeros = [](uint32_t w) {
-        return __popc(~(((w & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w) & 0x80808080u);
-    };
     if (!((uintptr_t)c & 15)) {  // images are multiples of 64 cells
 #pragma unroll 8
         for (int p = first; p < hw_pixels / 16; p += step) {
             const uint4 v = reinterpret_cast<const uint4 *>(c)[p];
-            n += (zeros(v.x) + zeros(v.y)) + (zeros(v.z) + zeros(v.w));
+            n += (zero_bytes(v.x) + zero_bytes(v.y)) + (zero_bytes(v.z) + zero_bytes(v.w));
         }
     } else {
         for (int p = first; p < hw_pixels; p += step) n += c[p] == TWG_CELL_FREE;
@@ -820,7 +894,7 @@ int net_head_psi(twg_unet *n, const uint8_t *cls, float *psi, int nx, int ny, in
                  hipStream_t st)
 {
     const dim3 grid((nx + 63) / 64, (ny + 3) / 4);
-    hipLaunchKernelGGL(k_head_psi, grid, dim3(256), 0, st, n->y, cls, psi, nx, ny, pitch, Wp, n->words + 1);
+    hipLaunchKernelGGL(k_head_psi, rows_grid(nx, ny), dim3(256), 0, st, n->y, cls, psi, nx, ny, pitch, Wp, n->words + 1);
     hipLaunchKernelGGL(k_net_fallback, grid, dim3(256), 0, st, cls, psi, nx, ny, pitch, n->words + 1, status);
     return last_status();
 }
@@ -847,7 +921,7 @@ int net_up_psi(twg_unet *n, const float *yc, int Hc, int Wc, int f, const uint8_
                int pitch, int32_t *status, hipStream_t st)
 {
     const dim3 grid((nx + 63) / 64, (ny + 3) / 4);
-    hipLaunchKernelGGL(k_up_psi, grid, dim3(256), 0, st, yc, Hc, Wc, f, cls, psi, nx, ny, pitch, n->words + 1);
+    hipLaunchKernelGGL(k_up_psi, rows_grid(nx, ny), dim3(256), 0, st, yc, Hc, Wc, f, cls, psi, nx, ny, pitch, n->words + 1);
     hipLaunchKernelGGL(k_net_fallback, grid, dim3(256), 0, st, cls, psi, nx, ny, pitch, n->words + 1, status);
     return last_status();
 }
@@ -862,14 +936,14 @@ int net_features(const uint8_t *cls, const uint16_t *ring, int nx, int ny, int p
                  int gy, const unsigned int *jmax, float *xf, uint16_t *xp, hipStream_t st)
 {
     const float inv_diag = (float)(1.0 / ((double)std::max(nx, ny) * std::sqrt(2.0)));
-    hipLaunchKernelGGL(k_features, dim3((Wp + 63) / 64, (Hp + 3) / 4), dim3(256), 0, st, cls, ring, nx, ny, pitch,
+    hipLaunchKernelGGL(k_features, rows_grid(Wp, Hp), dim3(256), 0, st, cls, ring, nx, ny, pitch,
                        Hp, Wp, gx, gy, inv_diag, jmax, xf, xp);
     return last_status();
 }
 
 int net_ring_max(const uint16_t *ring, int nx, int ny, int pitch, unsigned int *out, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_ring_max, dim3(std::min(ny, 512)), dim3(256), 0, st, ring, nx, ny, pitch, out);
+    hipLaunchKernelGGL(k_ring_max, dim3(kRingBlocks), dim3(kRingThreads), 0, st, ring, nx, ny, pitch, out);
     return last_status();
 }
 
