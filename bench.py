@@ -321,7 +321,7 @@ def main():
 
     # ---- kernel rooflines ----
     tl = roofline_leg()
-    kname = f"k_relax_slot<{S}, true>" if nx % 2 == 0 else f"k_relax_slot<{S}, false>"
+    kname = f"k_relax_slot<{S}, 1, true>" if nx % 2 == 0 else f"k_relax_slot<{S}, 1, false>"
     passes_plain = plain["sweeps"] / S
     passes_corr = pol["polish_sweeps"] / S
     roofs = [

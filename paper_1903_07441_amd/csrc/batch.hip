@@ -611,7 +611,7 @@ __global__ __launch_bounds__(256) void k_batch_begin(BatchArgs a, const uint8_t 
         const int x = bk.y * 64 + 4 * (threadIdx.x & 15);
         const bool quads = setup_quads(s);
         const int y1 = min(32 * (int)blockIdx.y + 32, g.ny);
-        for (int y = 32 * (int)blockIdx.y + (threadIdx.x >> 4); y < y1; y += 16) setup_four(s, x, y, quads);
+        setup_rows<2>(s, x, 32 * (int)blockIdx.y + (threadIdx.x >> 4), 16, y1, quads);
         return;
     }
     if (blockIdx.x != 0) return;

@@ -1030,7 +1030,21 @@ __global__ __launch_bounds__(256) void k_relax_begin(RelaxCtl *c, RelaxConfig cf
         __hip_atomic_store(&c->part[i][1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (threadIdx.x != 0) return;
-    c->c = cfg;
+    // member by member: a copy of the whole would be staged by every thread
+    c->c.tol = cfg.tol;
+    c->c.need = cfg.need;
+    c->c.wbound = cfg.wbound;
+    c->c.max_sweeps = cfg.max_sweeps;
+    c->c.omega = cfg.omega;
+    c->c.omega_dc = cfg.omega_dc;
+    c->c.omega_lead = cfg.omega_lead;
+    c->c.lead_passes = cfg.lead_passes;
+    c->c.S = cfg.S;
+    c->c.polish = cfg.polish;
+    c->c.check_passes = cfg.check_passes;
+    c->c.max_rounds = cfg.max_rounds;
+    c->c.fuse = cfg.fuse;
+    c->c.kept = cfg.kept;
     c->h.phase = cfg.kept ? PH_DEFECT32 : PH_PLAIN;
     c->h.parity = c->h.cparity = c->h.fresh = c->h.wide = 0;
     c->h.pass = 0;
