@@ -352,7 +352,7 @@ typedef struct {
  * back once, before the first pass.  Its field after N sweeps has the bits
  * of N sweeps on the tiled path (its sweep count is a multiple of S).  On
  * MI355X the tiled passes are faster even for grids of 64 to 160 cells a
- * side (1024 such grids: 8.6 against 19.8 ms), so it is not the default.  The host never waits for a
+ * side (1024 such grids: 5.2 against 17.6 ms), so it is not the default.  The host never waits for a
  * residual: it only keeps launches queued (it reads the device's decisions
  * from pinned memory).  Sweeps per tile load and rows per tile come from
  * hpf_autotune_batched if it ran on this context, else from the

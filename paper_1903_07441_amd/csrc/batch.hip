@@ -339,7 +339,8 @@ __device__ void batch_stats(const BatchArgs &a, int slot, bool forced)
 
 // At least three waves per SIMD (at most 168 VGPRs): the batch has several
 // tiles per SIMD, and the deepest tiling (S = 8) otherwise takes 171 and
-// runs at two (46.9 against 46.1 ms for the 256-grid batch).
+// runs at two (46.9 against 46.1 ms for the 256-grid batch, before tile heights
+// were chosen on the device).
 template <int S, bool EVEN>
 __global__ __launch_bounds__(256, 3) void k_batch_slot(BatchArgs a)
 {
@@ -468,8 +469,8 @@ __global__ __launch_bounds__(256) void k_batch_ctrl(BatchArgs a)
 // cells), and the check is the fused check's expression.  The field goes
 // back to HBM once; there is no launch per pass.  Every sweep still reads
 // and writes each cell in LDS, where a streamed tile keeps S sweeps in
-// registers per load: 1024 grids of 64 to 160 cells a side take 19.8 ms
-// here against 8.6 ms in the tiled passes, so this is opt-in.
+// registers per load: 1024 grids of 64 to 160 cells a side take 17.6 ms
+// here against 5.2 ms in the tiled passes, so this is opt-in.
 constexpr int kLdsThreads = 1024;
 constexpr int kLdsWaves = kLdsThreads / 64;
 

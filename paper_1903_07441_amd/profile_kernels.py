@@ -87,7 +87,7 @@ def main(argv=None):
             pl.solve(robot)
         torch.cuda.synchronize()
         info = pl.info
-        print(f"profiled {args.passes} replanning steps on {nx}x{ny} (each opens with k_raster_base; the "
+        print(f"profiled {args.passes} replanning steps on {nx}x{ny} (each opens with k_map; the "
               f"autotuner before them rasterises nothing); last descent {info.tolist()}", flush=True)
         ctx.close()
         return 0
