@@ -90,14 +90,18 @@ __device__ int64_t predict_passes(GridCtl *c, double r, const BatchArgs &a, int6
     return passes;
 }
 
-// the controller's work on grid k at event slot `slot` (one thread)
-__device__ void grid_event(const BatchArgs &a, int k, int slot)
+// the controller's work on grid k at event slot `slot` (one thread); true if
+// the grid's solve ends here.  *next receives the slot of its next check.
+__device__ bool grid_event(const BatchArgs &a, int k, int slot, int *next)
 {
     GridRun *gr = a.run + k;
-    if (gr->mode != BG_ACTIVE) return;
+    if (gr->mode != BG_ACTIVE) return false;
     const int dk = slot - gr->run_slot;
     const int64_t pass = (int64_t)gr->pass0 + dk;
-    if (pass < gr->next_check) return;  // not this grid's check
+    if (pass < gr->next_check) {  // not this grid's check
+        *next = min(*next, gr->run_slot + (gr->next_check - gr->pass0));
+        return false;
+    }
     GridCtl *c = a.ctl + k;
     const int par = (gr->parity0 ^ dk) & 1;
     const double r = bitsd(__hip_atomic_exchange(a.rmax + k, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -149,7 +153,7 @@ __device__ void grid_event(const BatchArgs &a, int k, int slot)
         gr->status = status;
         gr->parity0 = par;
         c->sweeps = pass * a.S;
-        return;
+        return true;
     }
     // the pass ran: the next run starts at the next slot with its output;
     // the check's slot is rounded up to a multiple of the event quantum
@@ -163,6 +167,8 @@ __device__ void grid_event(const BatchArgs &a, int k, int slot)
     gr->run_slot = slot + 1;
     gr->parity0 = par ^ 1;
     gr->next_check = (int32_t)pcheck;
+    *next = min(*next, slot + 1 + (int)(pcheck - (pass + 1)));
+    return false;
 }
 
 // decision published for a blocking caller: the slot of the next event
@@ -448,9 +454,20 @@ __global__ __launch_bounds__(256) void k_batch_ctrl(BatchArgs a)
         return;
     }
     if (slot < __builtin_amdgcn_readfirstlane(h.next_event)) return;
-    for (int k = threadIdx.x; k < a.n; k += 256) grid_event(a, k, slot);
-    __syncthreads();
-    build_list(a, hp, slot);
+    bool ended = false;
+    int next = INT_MAX;
+    for (int k = threadIdx.x; k < a.n; k += 256) ended = grid_event(a, k, slot, &next) || ended;
+    if (__syncthreads_or(ended)) {
+        build_list(a, hp, slot);
+    } else {
+        // the same grids go on: their table stands, only the next event moves
+        // (7.5 instead of 15 us for 64 grids)
+        __shared__ int least[4];
+        for (int o = 32; o > 0; o >>= 1) next = min(next, __shfl_xor(next, o));
+        if ((threadIdx.x & 63) == 0) least[threadIdx.x >> 6] = next;
+        __syncthreads();
+        if (threadIdx.x == 0) hp->next_event = min(min(least[0], least[1]), min(least[2], least[3]));
+    }
     if (threadIdx.x == 0) {
         hp->events += 1;
         publish_b(a.mirror, hp, slot, a.quantum);
