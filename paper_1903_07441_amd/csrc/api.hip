@@ -735,7 +735,9 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     const size_t o_rrel = align(o_rmax + n * sizeof(unsigned long long));
     const size_t o_stats = align(o_rrel + n * sizeof(unsigned long long));
     const size_t bytes = align(o_stats + n * sizeof(hpf_stats));
-    const void *old_batch = ctx->batch;
+    // a buffer that is replaced holds no tables, also where the new one has the
+    // old one's address
+    if (bytes > ctx->batch_bytes) ctx->batch_sig.clear();
     int rc = ensure(ctx, &ctx->batch, &ctx->batch_bytes, bytes);
     if (!rc) rc = ensure(ctx, &ctx->alt, &ctx->alt_bytes, (size_t)total * sizeof(float));
     if (!rc) rc = ensure(ctx, &ctx->fmask, &ctx->fmask_bytes, (size_t)total + 1);
@@ -753,7 +755,8 @@ int relax_batch_device(twg_ctx *ctx, int n, const twg_grid_desc *grids, const ui
     std::memcpy(sig.data(), bg.data(), sz_g);
     std::memcpy(sig.data() + sz_g, bl.data(), sz_b);
     if (sz_l) std::memcpy(sig.data() + sz_g + sz_b, lds.data(), sz_l);
-    if (old_batch != ctx->batch || sig != ctx->batch_sig) {
+    if (sig != ctx->batch_sig) {
+        ctx->batch_sig.clear();  // until all of them are there
         if (hipMemcpyAsync(d_grids, bg.data(), sz_g, hipMemcpyHostToDevice, st) != hipSuccess ||
             hipMemcpyAsync(d_blocks, bl.data(), sz_b, hipMemcpyHostToDevice, st) != hipSuccess ||
             (sz_l && hipMemcpyAsync(d_lds, lds.data(), sz_l, hipMemcpyHostToDevice, st) != hipSuccess) ||
