@@ -1475,6 +1475,12 @@ int32_t hpf_index_matrix(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const flo
     return rc ? set_err(ctx, rc, "index launch failed") : TWG_OK;
 }
 
+static int ensure_descend(twg_ctx *ctx, const twg_grid &g)
+{
+    const int rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, (size_t)g.pitch * g.ny);
+    return rc ? rc : ensure(ctx, &ctx->hopbuf, &ctx->hopbuf_bytes, descend_bytes(g.nx, g.ny));
+}
+
 int32_t hpf_descend(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const float *psi,
                     const double *psi64, const hpf_descend_params *p, int32_t *path_xy,
                     int32_t *info, void *stream)
@@ -1490,10 +1496,7 @@ int32_t hpf_descend(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const float *p
         return set_err(ctx, TWG_EINVAL, "start outside the grid");
     hipSetDevice(ctx->device);
     hipStream_t st = as_stream(stream);
-    rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, (size_t)g.pitch * g.ny);
-    if (rc) return rc;
-    rc = ensure(ctx, &ctx->hopbuf, &ctx->hopbuf_bytes, descend_bytes(g.nx, g.ny));
-    if (rc) return rc;
+    if ((rc = ensure_descend(ctx, g))) return rc;
     rc = launch_descend(cls, psi, psi64, reinterpret_cast<uint8_t *>(ctx->idxbuf), ctx->hopbuf, g.nx, g.ny, g.pitch,
                         p->start_x, p->start_y, p->cap, path_xy, info, st);
     return rc ? set_err(ctx, rc, "descent launch failed") : TWG_OK;
@@ -1588,6 +1591,9 @@ int32_t hpf_descent_all(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const floa
     if (steps_pitch < g.nx) return set_err(ctx, TWG_EINVAL, "steps_pitch must be >= nx");
     hipSetDevice(ctx->device);
     hipStream_t st = as_stream(stream);
+    // hpf_descend's scratch too: a program may capture its descent after this
+    // call alone
+    if ((rc = ensure_descend(ctx, g))) return rc;
     rc = ensure(ctx, &ctx->jumpbuf, &ctx->jumpbuf_bytes, descent_all_bytes(g.nx, g.ny));
     if (rc) return rc;
     rc = launch_descent_all(cls, psi, psi64, ctx->jumpbuf, g.nx, g.ny, g.pitch, steps, steps_pitch, st);
