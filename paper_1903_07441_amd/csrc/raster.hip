@@ -7,8 +7,9 @@
 //            Kalman prediction of Eq. (9) to the ring's horizon, its Q.8 disc (optionally grown by the
 //            predicted position covariance), and a conservative test of
 //            whether the disc can touch the ring and the grid; the survivors
-//            are marked by the whole wave: an exact integer test of every
-//            cell of the disc's bounding box (ring match + inside the disc).
+//            are marked by the whole wave, or by several: an exact integer test
+//            (ring match + inside the disc) of the cells of the disc's bounding
+//            box, in large discs of those near its ring.
 //            A marked cell that is not a border wall or the goal becomes
 //            OBST: nothing is read back, and every writer stores the same
 //            byte, so the result does not depend on the order.  With the
@@ -19,7 +20,13 @@
 // the copy rate): two launches instead of four (a counter cleared, cells, a
 // list of (obstacle, ring) pairs built with atomics, and its scatter), squares
 // and ring numbers in 32 bits instead of FP64 square roots and 64-bit
-// divisions.
+// divisions.  Large discs are bound by their cells' tests.  The four launches,
+// then a wave that walks a disc's whole box, then this (us a call):
+//   2048 x 2048, 500 discs of radius 3 to 12      27.9    14.5    14.4
+//   2048 x 2048, 10 discs of radius 300            826     743      34
+//   the same, elliptical                          3860    4820     945
+//   512 x 512, 10 discs of radius 100, elliptical  219     606      67
+//   128 x 128, 8 discs of radius 30 (one launch)    20      49      10
 //
 // Exactness: the horizon, the product and the sum of the prediction are each
 // rounded once (contraction is off for this file), 256*mu is exact, and the
@@ -27,6 +34,7 @@
 #include "twg_internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace twg {
 
@@ -61,7 +69,7 @@ __host__ __device__ inline bool ellipse_reaches(double u, double v, int j, int W
 {
     const double q = 4.0 * (u * u) + 12.16 * (v * v);
     const double rhs = 0.38 * ((double)j * (double)W) + 1.8 * u;
-    return rhs <= 0.0 || q >= rhs * rhs;
+    return (rhs <= 0.0) | (q >= rhs * rhs);
 }
 
 __host__ __device__ inline int ring_ellipse(long long dx, long long dy, double hc, double hs, int W)
@@ -93,10 +101,6 @@ __device__ __forceinline__ int ring_of_square(uint32_t n, uint32_t W, float inv_
     j -= __umul24(t, t) > n ? 1u : 0u;
     return (int)(j + (__umul24(u, u) <= n ? 1u : 0u));
 }
-__device__ __forceinline__ int ring_of_cells(int dx, int dy, int W, float inv_w)
-{
-    return ring_of_square((uint32_t)(__mul24(dx, dx) + __mul24(dy, dy)), (uint32_t)min(W, 65536), inv_w);
-}
 
 // Disc radius with covariance inflation: r + min(W, kappa sqrt(lambda_max)),
 // lambda_max the larger eigenvalue of the position covariance after horizon
@@ -114,11 +118,6 @@ __device__ __forceinline__ double inflated_radius(double r, const double *P, dou
     double g = kappa * sqrt(lam > 0.0 ? lam : 0.0);
     if (!(g <= (double)W)) g = (double)W;
     return r + g;
-}
-
-__device__ __forceinline__ long long floor_div256(long long a)
-{
-    return a >= 0 ? a / 256 : -((-a + 255) / 256);
 }
 
 // The obstacle's disc at ring j's horizon, to be marked on the cells of ring
@@ -245,93 +244,158 @@ __global__ __launch_bounds__(256) void k_map(MapArgs a)
     map_cells<ELL>(a, VEC, (blockIdx.x * 32 + (threadIdx.x & 31)) * 8, blockIdx.y * 8 + (threadIdx.x >> 5));
 }
 
-// Wave w of n_waves takes the (obstacle, ring) pairs w, w + n_waves, ..., one
+// Cells x0 .. x1, y0 .. y1 (inclusive).
+struct Box {
+    int x0, x1, y0, y1;
+};
+
+// Marks the cells of disc p in box b, one wave, the strips of 8 rows that are
+// slice `slice` of `slices`: 8 x 8 cells at a time, each with the exact disc
+// and ring test.  ELL: a cell is of ring j where the metric reaches j and not
+// j + 1 (it is monotone in j), which spares the ring number's square root and
+// divisions.  A strip wider than 32 cells is first cut, row by row, to the
+// disc's chord and the circular ring's two intervals (a square root in FP32
+// and a margin each), so that a large disc costs a wave the cells of its ring
+// and not its bounding box.  I: int while the squares of the box fit 32 bits,
+// else long long.
+template <bool ELL, typename I>
+__device__ __forceinline__ void mark_disc(const MapArgs &a, const Disc &p, const Box &b, int slice, int slices)
+{
+    using U = std::make_unsigned_t<I>;
+    const int lane = threadIdx.x & 63;
+    const int W = a.W, j = p.j;
+    const I cx = (I)p.cx, cy = (I)p.cy, R = (I)p.R;
+    const U R2 = (U)R * (U)R;
+    // squared distances of ring j's cells: [lo, hi] (no two cells are 2^31 apart)
+    const unsigned long long far = 0x7fffffffull, jw = (unsigned long long)max(j, 0) * W, kw = jw + W;
+    const uint32_t lo = (uint32_t)(jw < 46341 ? jw * jw : far), hi = (uint32_t)(kw < 46341 ? kw * kw - 1 : far);
+    const bool ringed = j >= 0, wide = b.x1 - b.x0 >= 32;
+    for (int y = b.y0 + slice * 8 + (lane >> 3); y <= b.y1; y += 8 * slices) {
+        const I dy = (I)256 * y - cy;
+        const U dy2 = (U)dy * (U)dy;
+        if (dy2 > R2) continue;
+        const U in2 = R2 - dy2;
+        const int ry = y - a.yr;
+        const uint32_t ry2 = (uint32_t)__mul24(ry, ry);
+        int from[2] = {b.x0, 1}, to[2] = {b.x1, 0};
+        if (wide) {
+            const I h = (I)__builtin_amdgcn_sqrtf((float)in2) + (R >> 20) + 2;
+            const int xa = max(b.x0, (int)((cx - h) >> 8)), xb = min(b.x1, (int)((cx + h) >> 8) + 1);
+            from[0] = xa;
+            to[0] = xb;
+            if (!ELL && ringed) {
+                if (ry2 > hi) continue;
+                const int out = (int)__builtin_amdgcn_sqrtf((float)(hi - ry2)) + 2;
+                const int in = ry2 < lo ? max((int)__builtin_amdgcn_sqrtf((float)(lo - ry2)) - 2, 0) : 0;
+                from[0] = max(xa, a.xr - out);
+                to[0] = min(xb, a.xr - in);
+                from[1] = max(xa, a.xr + in);
+                to[1] = min(xb, a.xr + out);
+            }
+        }
+        const double ny = (double)ry;
+        uint8_t *row = a.cls + (size_t)y * a.pitch;
+        auto mark = [&](int x, int last) {
+            const I dx = (I)256 * x - cx;
+            bool ok = x <= last && (U)dx * (U)dx <= in2 && !(x == a.xg && y == a.yg);
+            if (ringed) {
+                const int rx = x - a.xr;
+                if constexpr (ELL) {
+                    const double u = a.wm.hc * (double)rx + a.wm.hs * ny, v = a.wm.hs * (double)rx - a.wm.hc * ny;
+                    ok = ok & ((j == 0) | ellipse_reaches(u, v, j, W)) & !ellipse_reaches(u, v, j + 1, W);
+                } else {
+                    const uint32_t n = ry2 + (uint32_t)__mul24(rx, rx);
+                    ok = ok && n >= lo && n <= hi;
+                }
+            }
+            if (ok) row[x] = TWG_CELL_OBST;
+        };
+        if (!ELL && !wide) {
+            for (int x = b.x0 + (lane & 7); x <= b.x1; x += 8) mark(x, b.x1);
+            continue;
+        }
+#pragma unroll
+        for (int s = 0; s < (ELL ? 1 : 2); ++s)
+            for (int x = from[s] + (lane & 7); x <= to[s]; x += 16) {
+                mark(x, to[s]);
+                mark(x + 8, to[s]);
+            }
+    }
+}
+
+// Wave w of a.waves takes the (obstacle, ring) pairs w, w + a.waves, ..., one
 // a lane, so that the rings of one obstacle (a disc that moves with the rings
 // meets a hundred of them) go to different waves, then marks the discs that
-// survive one after another.
+// survive one after another in the cells of `clip` (their slice of them).
 template <bool ELL>
-__device__ __forceinline__ void mark_discs(const MapArgs &a, long long w)
+__device__ __forceinline__ void mark_discs(const MapArgs &a, long long w, const Box &clip, int slice, int slices)
 {
     const int lane = threadIdx.x & 63;
-    const int nx = a.nx, ny = a.ny, pitch = a.pitch, xr = a.xr, yr = a.yr, xg = a.xg, yg = a.yg, W = a.W, J = a.J;
-    const int border = a.border, per_object = a.per_object;
-    const float inv_w = a.inv_w;
-    const double kappa = a.kappa, vr = a.vr;
-    const WarpMode wm = a.wm;
-    const long long n_pairs = a.pairs, n_waves = a.waves;
+    const int W = a.W, J = a.J, per_object = a.per_object;
     const double *__restrict__ pos = a.pos, *__restrict__ vel = a.vel, *__restrict__ rad = a.rad;
     const double *__restrict__ cov = a.cov;
-    uint8_t *cls = a.cls;
-    if (w >= n_waves) return;
-    // cells a disc may mark: not the border walls
-    const int xa = border ? 1 : 0, xb = border ? nx - 2 : nx - 1, ya = border ? 1 : 0, yb = border ? ny - 2 : ny - 1;
-    const long long id = w + lane * n_waves;
+    if (w >= a.waves) return;
+    const long long id = w + lane * a.waves;
     Disc d{};
+    Box b{};
     bool hit = false;
-    if (id < n_pairs) {
+    if (id < a.pairs) {
         const long long i = per_object ? id : id >> 32 ? id / J : (long long)((uint32_t)id / (uint32_t)J);
         const int j = per_object ? 0 : (int)(id - i * J);
         hit = disc_at<ELL>(j, per_object, pos[2 * i], pos[2 * i + 1], vel[2 * i], vel[2 * i + 1], rad[i],
-                      cov ? cov + 16 * i : nullptr, kappa, wm, W, vr, nx, ny, xr, yr, &d);
+                           cov ? cov + 16 * i : nullptr, a.kappa, a.wm, W, a.vr, a.nx, a.ny, a.xr, a.yr, &d);
+        // the disc's cells, rounded inwards, in the clip
+        b = Box{(int)max((d.cx - d.R + 255) >> 8, (long long)clip.x0), (int)min((d.cx + d.R) >> 8, (long long)clip.x1),
+                (int)max((d.cy - d.R + 255) >> 8, (long long)clip.y0), (int)min((d.cy + d.R) >> 8, (long long)clip.y1)};
+        hit = hit && b.x0 <= b.x1 && b.y0 <= b.y1;
     }
-    {
-        for (unsigned long long todo = __ballot(hit); todo; todo &= todo - 1) {
-            const int l = __builtin_ctzll(todo);
-            const Disc p{__shfl(d.cx, l), __shfl(d.cy, l), __shfl(d.R, l), __shfl(d.j, l)};
-            const int x0 = (int)max(-floor_div256(-(p.cx - p.R)), (long long)xa);
-            const int x1 = (int)min(floor_div256(p.cx + p.R), (long long)xb);
-            const int y0 = (int)max(-floor_div256(-(p.cy - p.R)), (long long)ya);
-            const int y1 = (int)min(floor_div256(p.cy + p.R), (long long)yb);
-            auto mark = [&](int x, int y) {
-                if (p.j >= 0 && (ELL ? ring_ellipse(x - xr, y - yr, wm.hc, wm.hs, W)
-                                     : ring_of_cells(x - xr, y - yr, W, inv_w)) != p.j)
-                    return;
-                if (x != xg || y != yg) cls[(size_t)y * pitch + x] = TWG_CELL_OBST;
-            };
-            // 8 x 8 cells at a time
-            if (p.R < 65000) {  // squares within the box fit 32 bits
-                const uint32_t R2 = (uint32_t)p.R * (uint32_t)p.R;
-                for (int y = y0 + (lane >> 3); y <= y1; y += 8) {
-                    const int dy = (int)(256LL * y - p.cy);
-                    const uint32_t dy2 = (uint32_t)dy * (uint32_t)dy;
-                    if (dy2 > R2) continue;
-                    for (int x = x0 + (lane & 7); x <= x1; x += 8) {
-                        const int dx = (int)(256LL * x - p.cx);
-                        if ((uint32_t)dx * (uint32_t)dx <= R2 - dy2) mark(x, y);
-                    }
-                }
-            } else {
-                const long long R2 = p.R * p.R;
-                for (int y = y0 + (lane >> 3); y <= y1; y += 8) {
-                    const long long dy = 256LL * y - p.cy, in2 = R2 - dy * dy;
-                    if (in2 < 0) continue;
-                    for (int x = x0 + (lane & 7); x <= x1; x += 8) {
-                        const long long dx = 256LL * x - p.cx;
-                        if (dx * dx <= in2) mark(x, y);
-                    }
-                }
-            }
-        }
+    // (a lane's words in scalar registers: the marking's uniform part is
+    // scalar work)
+    for (unsigned long long todo = __ballot(hit); todo; todo &= todo - 1) {
+        const int l = __builtin_ctzll(todo);
+        auto word = [&](int v) { return __builtin_amdgcn_readlane(v, l); };
+        auto both = [&](long long v) {
+            return (long long)((unsigned long long)(uint32_t)word((int)(v >> 32)) << 32 | (uint32_t)word((int)v));
+        };
+        const Disc p{both(d.cx), both(d.cy), both(d.R), word(d.j)};
+        const Box q{word(b.x0), word(b.x1), word(b.y0), word(b.y1)};
+        if (p.R < 65000) mark_disc<ELL, int>(a, p, q, slice, slices);
+        else mark_disc<ELL, long long>(a, p, q, slice, slices);
     }
 }
 
+// cells a disc may mark: not the border walls
+__device__ __forceinline__ Box markable(const MapArgs &a)
+{
+    const int e = a.border ? 1 : 0;
+    return Box{e, a.nx - 1 - e, e, a.ny - 1 - e};
+}
+
+// gridDim.y waves share a group of pairs
 template <bool ELL>
 __global__ __launch_bounds__(256) void k_discs(MapArgs a)
 {
-    mark_discs<ELL>(a, (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    mark_discs<ELL>(a, (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), markable(a),
+                    blockIdx.y, gridDim.y);
 }
 
-// A small map whole in one workgroup: the cells, then the discs.  Each launch
-// costs a call 3 us on the host, which bounds small maps (64 x 64 with 10
-// discs: 10.5 us a call in two launches, 7.5 in one).
+// A small map in one launch: a workgroup writes the cells of its tile (64
+// columns of `rows`, at most 64, rows), then marks every disc's part of it: the
+// predictions are made again in every tile, large discs are shared by them.
+// Each launch costs a call 3 us on the host, which bounds small maps (64 x 64
+// with 10 discs: 10.5 us a call in two launches, 8.2 in one; 128 x 128 with 190
+// discs of radius 30, 18 us, 144 when one workgroup took the whole map).
 constexpr int kSmallCells = 16384, kSmallWaves = 16, kSmallPairs = 12 * kSmallWaves;
+constexpr int kSmallW = 64;
 template <bool ELL>
-__global__ __launch_bounds__(64 * kSmallWaves) void k_map_small(MapArgs a)
+__global__ __launch_bounds__(64 * kSmallWaves) void k_map_small(MapArgs a, int rows)
 {
-    const int groups = (a.nx + 7) / 8;
-    for (int u = threadIdx.x; u < groups * a.ny; u += 64 * kSmallWaves) map_cells<ELL>(a, a.vec, u % groups * 8, u / groups);
+    const int x0 = blockIdx.x * kSmallW, y0 = blockIdx.y * rows, u = threadIdx.x;
+    if (u < kSmallW / 8 * rows) map_cells<ELL>(a, a.vec, x0 + u % (kSmallW / 8) * 8, y0 + u / (kSmallW / 8));
     __syncthreads();
-    mark_discs<ELL>(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6));
+    const Box m = markable(a);
+    mark_discs<ELL>(a, __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                    Box{max(m.x0, x0), min(m.x1, x0 + kSmallW - 1), max(m.y0, y0), min(m.y1, y0 + rows - 1)}, 0, 1);
 }
 
 int host_ring(long long dx, long long dy, int W)
@@ -375,17 +439,17 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
     MapArgs a{nx, ny, pitch, p.robot_x, p.robot_y, p.goal_x, p.goal_y, p.ring_width, p.border_walls, J, p.per_object,
               vec, inv_w, wm, static_occ, cls, ring, pos, vel, rad, p.cov, p.kappa, p.robot_speed, pairs,
               std::max((pairs + 63) / 64, std::min(pairs, 4096LL))};
-    auto launch = [&](auto kernel, dim3 grid, int threads) {
-        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, a);
+    auto launch = [&](auto kernel, dim3 grid, int threads, auto... more) {
+        hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, st, a, more...);
         return hipGetLastError() == hipSuccess;
     };
-    // one launch where 16 waves soon have every cell and disc: up to 12 discs a
-    // wave (7.5 to 9.3 us a call against 10.5 in two launches; with 20 discs a
-    // wave it is 11)
+    // one launch where 16 waves a tile soon have every pair: up to 12 a wave
     if ((long long)nx * ny <= kSmallCells && pairs > 0 && pairs <= kSmallPairs) {
         a.waves = std::min<long long>(pairs, kSmallWaves);
-        const bool ok = ell ? launch(k_map_small<true>, dim3(1), 64 * kSmallWaves)
-                            : launch(k_map_small<false>, dim3(1), 64 * kSmallWaves);
+        const int rows = std::max(8, std::min(64, 512 / ((nx + 7) / 8 * 8)));
+        const dim3 grid((nx + kSmallW - 1) / kSmallW, (ny + rows - 1) / rows);
+        const bool ok = ell ? launch(k_map_small<true>, grid, 64 * kSmallWaves, rows)
+                            : launch(k_map_small<false>, grid, 64 * kSmallWaves, rows);
         return ok ? TWG_OK : set_err(ctx, TWG_EDEVICE, "map launch failed");
     }
     const dim3 grid((nx + 255) / 256, (ny + 7) / 8);
@@ -393,7 +457,14 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
                         : (ell ? launch(k_map<false, true>, grid, 256) : launch(k_map<false, false>, grid, 256));
     if (!ok) return set_err(ctx, TWG_EDEVICE, "map launch failed");
     if (n_obs == 0) return TWG_OK;
-    const dim3 blocks((unsigned)((a.waves + 3) / 4));
+    // few pairs, whose discs may be large: several waves share each, 4096 in
+    // all; four where a wave has one pair or a few and a cell's ring test is FP64
+    // (512 x 512, 10 discs of radius 100, elliptical: 230 -> 72 us; for small
+    // discs the predictions made again outweigh it: 64 x 64 with 20, 16384 waves
+    // 17.1 us, 4096 14.5)
+    const unsigned slices = ell && a.waves == 4096 && !p.per_object
+                                ? 4 : (unsigned)std::max(1LL, std::min(16LL, 4096 / a.waves));
+    const dim3 blocks((unsigned)((a.waves + 3) / 4), slices);
     if (!(ell ? launch(k_discs<true>, blocks, 256) : launch(k_discs<false>, blocks, 256)))
         return set_err(ctx, TWG_EDEVICE, "rasterize launch failed");
     return TWG_OK;
