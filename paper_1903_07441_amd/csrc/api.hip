@@ -1477,7 +1477,7 @@ int32_t hpf_index_matrix(twg_ctx *ctx, twg_grid g, const uint8_t *cls, const flo
 
 static int ensure_descend(twg_ctx *ctx, const twg_grid &g)
 {
-    const int rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, (size_t)g.pitch * g.ny);
+    const int rc = ensure(ctx, &ctx->idxbuf, &ctx->idxbuf_bytes, descend_code_bytes(g.nx, g.ny));
     return rc ? rc : ensure(ctx, &ctx->hopbuf, &ctx->hopbuf_bytes, descend_bytes(g.nx, g.ny));
 }
 

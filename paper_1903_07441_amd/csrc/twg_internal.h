@@ -57,7 +57,7 @@ struct twg_ctx {
     // walk codes of hpf_descend
     void *idxbuf = nullptr;
     size_t idxbuf_bytes = 0;
-    // tile exits of hpf_descend (and the path's parts)
+    // tile exits of hpf_descend
     void *hopbuf = nullptr;
     size_t hopbuf_bytes = 0;
     // tile exits and in-tile descents of hpf_descent_all
@@ -272,10 +272,11 @@ int launch_rasterize(twg_ctx *ctx, const twg_grid &g, int n_obs, const double *p
 int launch_kalman(int n, double *x, double *P, const double *z, double dt, const double *Q, const double *R,
                   double *pos, double *vel, hipStream_t st);
 
-// descend.hip: the index matrix; one cell's path (code: pitch * ny bytes,
+// descend.hip: the index matrix; one cell's path (code: descend_code_bytes,
 // scratch: descend_bytes); every cell's descent length (descent_all_bytes)
 int launch_index(const uint8_t *cls, const float *psi, const double *psi64, uint8_t *idx, int nx, int ny, int pitch,
                  hipStream_t st);
+size_t descend_code_bytes(int nx, int ny);
 size_t descend_bytes(int nx, int ny);
 int launch_descend(const uint8_t *cls, const float *psi, const double *psi64, uint8_t *code, void *scratch, int nx,
                    int ny, int pitch, int sx, int sy, int cap, int32_t *path, int32_t *info, hipStream_t st);
