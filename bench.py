@@ -40,7 +40,7 @@ SINGLE_SWEEP_BYTES = 8.125
 # SIMD x 16 lanes x 2.4 GHz lane-instructions per second (packed FP32 off)
 VALU_PER_UPDATE = 5.0
 VALU_PEAK = 256 * 4 * 16 * 2.4e9
-TRAFFIC_SOURCES = ("solve.hip", "sor_stream.hip", "stream_tile.h", "update.h")
+TRAFFIC_SOURCES = ("solve.hip", "sor_stream.hip", "stream_tile.h", "tile_map.h", "update.h")
 
 
 def log(msg):

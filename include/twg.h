@@ -134,6 +134,10 @@ typedef struct {
  * v = hy dx - hx dy, r_x = (-1.8 u + sqrt(4 u^2 + 12.16 v^2)) / 0.38, and
  * j = floor(r_x / W), decided exactly: r_x >= j W when 0.38 j W + 1.8 u <= 0
  * or 4 u^2 + 12.16 v^2 >= (0.38 j W + 1.8 u)^2 (each operation rounded once).
+ * Known fault, with per_object 0: a disc is left out of the rings j whose
+ * 0.1 j W lies more than 2 cells beyond its far edge (seen from the robot), but
+ * behind the robot such a ring reaches in to 0.0922 j W, so the outer parts of
+ * discs there can be FREE that should be OBST.
  * per_object 1 follows Algorithm 1 literally: obstacle i is predicted once,
  * to the horizon of the ring of the cell nearest its current centre (round
  * half to even), and every cell of that disc is marked, whatever its ring.

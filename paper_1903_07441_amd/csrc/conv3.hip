@@ -13,10 +13,12 @@
 // bank conflicts.  A pixel's products are added in the order chunk, tap,
 // whatever the tile, so every tiling gives the same bits.
 //
-// The tile height is chosen for the number of workgroups: R = 8 (67 KB of
-// LDS reads feed 1152 products per chunk, so the matrix cores bound it) as
-// long as that leaves two workgroups per CU, else lower tiles (a 32 x 32 layer
-// has four 16 x 16 tiles, on a device of 256 CUs).
+// The tile height is chosen for the number of workgroups: R = 8 (a wave reads
+// 67 KB of LDS per chunk for 144 products of 16 x 16 x 32; with R = 4, 43 KB for
+// 72) as long as that leaves two workgroups per CU, else lower tiles (a 32 x 32
+// layer has four 16 x 16 tiles, on a device of 256 CUs).  At 2048 x 2048 the
+// layers of R = 8 reach 19 to 43 % of the matrix cores' rate: the rest is
+// waiting for the halos at two workgroups a CU.
 //
 // The epilogue goes through LDS: stores are 16-byte runs of channels, the
 // layers that the encoder pools write the 2x2 means as well (their consumers

@@ -149,9 +149,13 @@ __device__ __forceinline__ bool disc_at(int j, bool per_object, double px, doubl
     if (cx + R < 0 || cx - R > 256LL * (nx - 1) || cy + R < 0 || cy - R > 256LL * (ny - 1)) return false;
     if (!per_object) {
         // ...and ring j: cells of the disc lie within R of its centre; ring j
-        // holds Euclidean distances [jW, (j+1)W) (circular) or, since the
-        // elliptical r_x lies between d / 1.9 and 10 d, [jW / 10, 1.9 (j+1) W)
-        // (elliptical); two cells of margin absorb rounding
+        // holds Euclidean distances [jW, (j+1)W) (circular); two cells of margin
+        // absorb rounding.  Elliptical: [jW / 10, 1.9 (j+1) W) is taken, from
+        // r_x between d / 1.9 and 10 d.  The upper end is wrong: r_x / d is
+        // 10.85 at 130.6 degrees off the heading, so ring j begins at
+        // 0.0922 jW, and a disc that ends between 0.0922 jW - 2 and
+        // 0.1 jW - 2 cells from the robot is not marked on ring j (seen from
+        // rings of r_x = 256 on, behind the robot).  Changing it changes maps.
         const double dx = (double)cx / 256.0 - xr, dy = (double)cy / 256.0 - yr;
         const double D = sqrt(dx * dx + dy * dy), Rc = (double)R / 256.0;
         const double lo = ELL ? (double)j * W / 10.0 : (double)j * W;

@@ -158,11 +158,12 @@ constexpr int kSrcNone = 0, kSrcF = 1, kSrcC = 2;
 // grid read as zeros with factor 0, straight from the out-of-range loads.
 //
 // Measured at 2048 x 2048 (S = 6, 46 rows: 900 waves on 1024 SIMDs, bound by
-// VALU issue): the trimmed first turn took a replanning step from 6.16 to
-// 5.65 ms; 256 FP64 sweeps (S = 4) from 1.13 to 1.10 ms, and to 0.92 ms with
-// lower tiles that end at their own last row.  1001 x 743 to residual 1e-6
-// (unpaired): 5.5 to 2.96 ms, where the mask bytes used to be loaded at their
-// use.
+// VALU issue): the trimmed first turn, tiles that end at their own last row and
+// their heights took a replanning step from 6.16 to 5.65 ms and 256 FP64 sweeps
+// from 1.13 to 0.92 ms at S = 4 (0.63 at the S = 6 of an untuned context).
+// 1001 x 743 to residual 1e-6, with the mask bytes loaded at their use before:
+// 5.5 to 2.96 ms, and 1.69 with two columns in one access at any width and
+// passes fused between the checks.
 //
 // CHECK: the pass also measures the residual of its INPUT field, in FP64:
 // r = ((E + W) + (S + N)) / 4 (+ f) - c over the FREE cells of its output

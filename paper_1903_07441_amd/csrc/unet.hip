@@ -727,7 +727,6 @@ __global__ __launch_bounds__(256) void k_sum_loss(const float *__restrict__ part
     }
 }
 
-// ---- launch helpers -----------------------------------------------------------
 }  // namespace
 
 // ---- host side ----------------------------------------------------------------

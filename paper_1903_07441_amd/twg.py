@@ -150,8 +150,8 @@ def _ptr(t):
 
 
 def _stream():
-    # the raw handle: building a torch stream object takes 2.7 us of a call
-    # (a map update of 64 x 64 cells is 11)
+    # the raw handle, by a function private to torch: building a stream object
+    # takes 2.3 us of a call (a map update of 64 x 64 cells takes 8.2)
     torch.cuda.init()
     return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
 
