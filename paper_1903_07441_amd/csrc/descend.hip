@@ -324,14 +324,12 @@ __global__ __launch_bounds__(kThreads) void k_tiles(const uint8_t *__restrict__ 
 // tile, 0 where the descent ends or leaves it), followed from the entered cell,
 // one LDS read a step; lane k keeps the k-th cell of the current group of 64,
 // stored in one coalesced write per group.
-constexpr int kParts = 256;
 __global__ __launch_bounds__(64) void k_path(const uint8_t *__restrict__ cls, const uint8_t *__restrict__ code,
                                              const unsigned long long *__restrict__ nodes, int nx, int ny, int pitch,
                                              int tiles_x, int start, int sx, int sy, int cap,
                                              int32_t *__restrict__ path, int32_t *__restrict__ info)
 {
     __shared__ __align__(8) int16_t move[kTile * kTile];
-    __shared__ int2 parts[kParts];
     const int lane = threadIdx.x, code_pitch = local_pitch(nx);
     if (!walkable(cls[(size_t)sy * pitch + sx])) {
         if (blockIdx.x == 0 && lane == 0) {
@@ -343,21 +341,22 @@ __global__ __launch_bounds__(64) void k_path(const uint8_t *__restrict__ cls, co
     // parts past the buffer's end are not written: the walk stops there
     int at = start, n = 0, turn = blockIdx.x;  // turn: parts until this wave's next one
     while (at >= 0 && n < cap) {
-        int own = 0;
-        while (at >= 0 && n < cap && own < kParts) {
+        // up to 64 parts at a time: lane k keeps the k-th
+        int own = 0, part_at = 0, part_n = 0;
+        while (at >= 0 && n < cap && own < 64) {
+            const Node v = unpack(nodes[at]);
             if (turn == 0) {
-                if (lane == 0) parts[own] = make_int2(at, n);
+                part_at = lane == own ? at : part_at;
+                part_n = lane == own ? n : part_n;
                 ++own;
                 turn = gridDim.x;
             }
             --turn;
-            const Node v = unpack(nodes[at]);
             n += v.moves;
             at = v.next;
         }
-        __syncthreads();
         for (int k = 0; k < own; ++k) {
-            const int2 s = parts[k];
+            const int2 s = make_int2(__builtin_amdgcn_readlane(part_at, k), __builtin_amdgcn_readlane(part_n, k));
             int x = sx, y = sy;
             if (s.x != start) {
                 const int t = s.x / kNodes;
@@ -413,7 +412,6 @@ __global__ __launch_bounds__(64) void k_path(const uint8_t *__restrict__ cls, co
                 if (on) m = *reinterpret_cast<const int16_t *>(moves + a);
             }
         }
-        __syncthreads();
     }
     // the descent's last cell has path index n when it has ended (a part
     // that goes on has its next cell there)
