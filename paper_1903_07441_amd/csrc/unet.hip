@@ -421,33 +421,30 @@ __global__ __launch_bounds__(256) void k_features_coarse(const uint8_t *__restri
     const int X = blockIdx.x * 64 + (threadIdx.x & 63);
     const int Y = blockIdx.y * 4 + (threadIdx.x >> 6);
     if (X >= Wc || Y >= Hc) return;
-    // a block inside the grid is read four cells at a time where rows are
-    // aligned for that
+    // blocks inside the grid are read four cells at a time where rows are
+    // aligned for that; a wave with a block at the edge goes cell by cell whole
+    // (both ways one after the other took 45 us for f = 16 on 1001 columns, this 25)
     const bool words = !(f & 3) && !(pitch & 3) && !((uintptr_t)cls & 3);
+    const int lf = __builtin_ctz(f);  // f is a power of two
     int blocked = 0, nfree = 0;
-    if (words && (X + 1) * f <= nx && (Y + 1) * f <= ny) {
+    if (words && __all((X + 1) * f <= nx && (Y + 1) * f <= ny)) {
         const uint8_t *p = cls + (size_t)Y * f * pitch + X * f;
-        for (int q = 0; q < f / 4; ++q) {
+        const int lw = lf - 2;  // words of a row
 #pragma unroll 8
-            for (int dy = 0; dy < f; ++dy) {
-                const uint32_t w = *reinterpret_cast<const uint32_t *>(p + (size_t)dy * pitch + 4 * q);
-                blocked += zero_bytes(w ^ 0x01010101u * TWG_CELL_OBST) + zero_bytes(w ^ 0x01010101u * TWG_CELL_WALL);
-                nfree += zero_bytes(w);
-            }
+        for (int q = 0; q < f << lw; ++q) {
+            const uint32_t w = *reinterpret_cast<const uint32_t *>(p + (size_t)(q >> lw) * pitch + 4 * (q & ((1 << lw) - 1)));
+            blocked += zero_bytes(w ^ 0x01010101u * TWG_CELL_OBST) + zero_bytes(w ^ 0x01010101u * TWG_CELL_WALL);
+            nfree += zero_bytes(w);
         }
     } else {
-        for (int dy = 0; dy < f; ++dy) {
-            const int y = Y * f + dy;
-            for (int dx = 0; dx < f; ++dx) {
-                const int x = X * f + dx;
-                if (x >= nx || y >= ny) {
-                    ++blocked;
-                    continue;
-                }
-                const uint8_t c = cls[(size_t)y * pitch + x];
-                blocked += (c == TWG_CELL_OBST || c == TWG_CELL_WALL) ? 1 : 0;
-                nfree += c == TWG_CELL_FREE ? 1 : 0;
-            }
+        // (every load unconditional: cells outside the grid read one inside)
+#pragma unroll 8
+        for (int q = 0; q < f * f; ++q) {
+            const int y = Y * f + (q >> lf), x = X * f + (q & (f - 1));
+            const uint8_t c = cls[(size_t)min(y, ny - 1) * pitch + min(x, nx - 1)];
+            const bool in = x < nx && y < ny;
+            blocked += !in || c == TWG_CELL_OBST || c == TWG_CELL_WALL ? 1 : 0;
+            nfree += in && c == TWG_CELL_FREE ? 1 : 0;
         }
     }
     const float occ = (float)blocked / (float)(f * f);
@@ -537,8 +534,8 @@ __global__ __launch_bounds__(256) void k_up_psi(const float *__restrict__ yc, in
 }
 
 // Largest ring number of a grid; *out must be zero beforehand.  A wave takes
-// runs of 512 cells of a row, eight a lane in one load where rows are aligned
-// for that; one atomic per block, of which there are few (they meet on one
+// runs of 512 cells of a row, eight a lane, in one load where rows are aligned
+// for that, else 64 apart; one atomic per block, of which there are few (they meet on one
 // address, 10 ns each: 512 blocks of single-cell loads took 16 us at
 // 2048 x 2048).
 constexpr int kRingThreads = 512, kRingBlocks = 128;
@@ -553,14 +550,18 @@ __global__ __launch_bounds__(kRingThreads) void k_ring_max(const uint16_t *__res
     unsigned int r = 0;
 #pragma unroll 4
     for (int it = blockIdx.x * NW + (threadIdx.x >> 6); it < items; it += gridDim.x * NW) {
-        const int y = it / runs, x0 = (it - y * runs) * 512 + 8 * lane;
-        const uint16_t *p = ring + (size_t)y * pitch + x0;
-        if (quads && x0 + 8 <= nx) {
-            const uint4 v = *reinterpret_cast<const uint4 *>(p);
+        const int y = it / runs, x0 = (it - y * runs) * 512, x = x0 + 8 * lane;
+        const uint16_t *p = ring + (size_t)y * pitch;
+        if (!quads) {
+            // (a row's end reads its last cell again)
+#pragma unroll
+            for (int k = 0; k < 8; ++k) r = max(r, (unsigned int)p[min(x0 + 64 * k + lane, nx - 1)]);
+        } else if (x + 8 <= nx) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(p + x);
             r = max(r, max(max(v.x & 0xffffu, v.x >> 16), max(v.y & 0xffffu, v.y >> 16)));
             r = max(r, max(max(v.z & 0xffffu, v.z >> 16), max(v.w & 0xffffu, v.w >> 16)));
         } else {
-            for (int k = 0; k < 8 && x0 + k < nx; ++k) r = max(r, (unsigned int)p[k]);
+            for (int k = 0; k < 8 && x + k < nx; ++k) r = max(r, (unsigned int)p[x + k]);
         }
     }
     for (int o = 32; o > 0; o >>= 1) r = max(r, (unsigned int)__shfl_xor((int)r, o));
