@@ -626,10 +626,8 @@ __global__ __launch_bounds__(256) void k_batch_begin(BatchArgs a, const uint8_t 
         const int2 bk = a.blocks[blockIdx.x];
         const BatchGrid g = a.grids[bk.x];
         const CellSetup s{cls + g.off, a.psi + g.off, a.mask + g.off, g.nx, g.ny, g.pitch, mode, 0, 0};
-        const int x = bk.y * 64 + 4 * (threadIdx.x & 15);
-        const bool quads = setup_quads(s);
         const int y1 = min(32 * (int)blockIdx.y + 32, g.ny);
-        setup_rows<2>(s, x, 32 * (int)blockIdx.y + (threadIdx.x >> 4), 16, y1, quads);
+        setup_rows<8>(s, bk.y * 64 + (threadIdx.x & 63), 32 * (int)blockIdx.y + (threadIdx.x >> 6), 4, y1);
         return;
     }
     if (blockIdx.x != 0) return;

@@ -41,74 +41,50 @@ __device__ __forceinline__ bool init_value(const CellSetup &s, uint32_t code, in
     }
 }
 
-// Bound by memory: 1 byte read and 5 written a cell.  A lane takes four
-// neighbouring cells, read as one word and written as one mask word and one
-// 16-byte store, where rows are aligned for that (`quads`: wave-uniform);
-// else, at a row's end and where a cell keeps its value, cell by cell.  K
-// rows, dy apart, are read before any is written.  2048 x 2048: field 9 and
-// mask 6 us cell by cell in two launches, 9 us here.
+// Bound by memory: 1 byte read and 5 written a cell.  A lane takes one column of
+// K rows, dy apart, read before any is written.  2048 x 2048, one launch for field
+// and mask: 8.7 us (9.2 at an odd pitch); with four neighbouring cells a lane,
+// written as words where rows are aligned, 10.1 (13.5 where they are not), and
+// cell by cell in two launches 9 + 6.  Beyond the caches the wide words were
+// faster (8192 x 8192, the field alone: 84 us, 110 here, 157 a row a wave).
 template <int K>
-__device__ __forceinline__ void setup_rows(const CellSetup &s, int x, int y0, int dy, int yend, bool quads)
+__device__ __forceinline__ void setup_rows(const CellSetup &s, int x, int y0, int dy, int yend)
 {
     if (x >= s.nx) return;
-    const bool wide = quads && x + 4 <= s.nx;
-    uint32_t c[K];
+    uint8_t c[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k)
-        if (wide) c[k] = *reinterpret_cast<const uint32_t *>(s.cls + (size_t)min(y0 + k * dy, yend - 1) * s.pitch + x);
+    for (int k = 0; k < K; ++k) c[k] = s.cls[(size_t)min(y0 + k * dy, yend - 1) * s.pitch + x];
 #pragma unroll
     for (int k = 0; k < K; ++k) {
         const int y = y0 + k * dy;
         if (y >= yend) return;
         const size_t i = (size_t)y * s.pitch + x;
-        if (wide) {
-            float v[4];
-            bool all = true, set[4];
-            uint32_t m = 0u;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t code = c[k] >> 8 * j & 0xffu;
-                set[j] = init_value(s, code, x + j, y, &v[j]);
-                all = all && set[j];
-                m |= code == TWG_CELL_FREE ? 0xffu << 8 * j : 0u;
-            }
-            if (s.mask) *reinterpret_cast<uint32_t *>(s.mask + i) = m;
-            if (!s.psi) continue;
-            if (all) {
-                *reinterpret_cast<float4 *>(s.psi + i) = make_float4(v[0], v[1], v[2], v[3]);
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (set[j]) s.psi[i + j] = v[j];
-            }
-            continue;
-        }
-        for (int j = 0; j < 4 && x + j < s.nx; ++j) {
-            const uint32_t code = s.cls[i + j];
-            float v;
-            if (init_value(s, code, x + j, y, &v) && s.psi) s.psi[i + j] = v;
-            if (s.mask) s.mask[i + j] = code == TWG_CELL_FREE ? 0xff : 0;
-        }
+        float v;
+        if (init_value(s, c[k], x, y, &v) && s.psi) s.psi[i] = v;
+        if (s.mask) s.mask[i] = c[k] == TWG_CELL_FREE ? 0xff : 0;
     }
 }
 
-__device__ __forceinline__ bool setup_quads(const CellSetup &s)
-{
-    return !((uintptr_t)s.cls & 3) && !((uintptr_t)s.psi & 15) && !((uintptr_t)s.mask & 3) && !(s.pitch & 3);
-}
-
-// one grid: a wave takes runs of 256 columns of kSetupRows rows (a block: of
-// four times as many)
+// One grid: a wave takes 64 columns of kSetupRows rows, of narrow grids several
+// rows at once (1 << lane_bits lanes a row; 8 x 32767 cells: 5.5 us a call, 9.4
+// with two lanes of 64 at work).
 constexpr int kSetupRows = 4;
-inline int setup_blocks(int nx, int ny)
+inline int setup_lane_bits(int nx)
 {
-    return (int)(((long long)ny + 4 * kSetupRows - 1) / (4 * kSetupRows) * ((nx + 255) / 256));
+    int b = 0;
+    while (b < 6 && (1 << b) < nx) ++b;
+    return b;
 }
-__device__ __forceinline__ void setup_grid(const CellSetup &s)
+inline dim3 setup_blocks(int nx, int ny)
 {
-    const int runs = (s.nx + 255) / 256, band = blockIdx.x / runs;
-    setup_rows<kSetupRows>(s, (blockIdx.x - band * runs) * 256 + 4 * (threadIdx.x & 63),
-                           band * 4 * kSetupRows + (threadIdx.x >> 6), 4, s.ny, setup_quads(s));
+    const int b = setup_lane_bits(nx), rows = kSetupRows * (256 >> b);
+    return dim3((nx + (1 << b) - 1) >> b, (ny + rows - 1) / rows);
+}
+__device__ __forceinline__ void setup_grid(const CellSetup &s, int lane_bits)
+{
+    const int at_once = 256 >> lane_bits;  // rows a block takes at once
+    setup_rows<kSetupRows>(s, (blockIdx.x << lane_bits) + (threadIdx.x & ((1 << lane_bits) - 1)),
+                           blockIdx.y * kSetupRows * at_once + (threadIdx.x >> lane_bits), at_once, s.ny);
 }
 
 }  // namespace twg

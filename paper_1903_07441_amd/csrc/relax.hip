@@ -145,7 +145,11 @@ __global__ void k_merge_prev(const uint8_t *__restrict__ cls, const uint8_t *__r
 
 // ---- element-wise helpers --------------------------------------------------
 // field and mask set-up of one grid, either left out
-__global__ __launch_bounds__(256) void k_setup(CellSetup s) { setup_grid(s); }
+__global__ __launch_bounds__(256) void k_setup(CellSetup s, int lane_bits) { setup_grid(s, lane_bits); }
+void launch_setup(const CellSetup &s, hipStream_t st)
+{
+    hipLaunchKernelGGL(k_setup, setup_blocks(s.nx, s.ny), dim3(256), 0, st, s, setup_lane_bits(s.nx));
+}
 
 __global__ void k_update64(const uint8_t *__restrict__ cls, double *u, const float *__restrict__ e,
                            float *psi, int nx, int ny, int pitch)
@@ -208,16 +212,14 @@ int last_status()
 
 int launch_fmask(const uint8_t *cls, uint8_t *fmask, int nx, int ny, int pitch, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_setup, dim3(setup_blocks(nx, ny)), dim3(256), 0, st,
-                       CellSetup{cls, nullptr, fmask, nx, ny, pitch, HPF_INIT_KEEP, 0, 0});
+    launch_setup(CellSetup{cls, nullptr, fmask, nx, ny, pitch, HPF_INIT_KEEP, 0, 0}, st);
     return last_status();
 }
 
 int launch_field_init(const uint8_t *cls, float *psi, int nx, int ny, int pitch, int mode, int gx, int gy,
                       hipStream_t st)
 {
-    hipLaunchKernelGGL(k_setup, dim3(setup_blocks(nx, ny)), dim3(256), 0, st,
-                       CellSetup{cls, psi, nullptr, nx, ny, pitch, mode, gx, gy});
+    launch_setup(CellSetup{cls, psi, nullptr, nx, ny, pitch, mode, gx, gy}, st);
     return last_status();
 }
 

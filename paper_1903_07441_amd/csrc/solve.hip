@@ -1021,10 +1021,10 @@ __global__ __launch_bounds__(256) void k_relax_resident(void *ctl, int slot, Slo
 
 // Set-up of a solve: the cells (boundary and initial values, free mask), and
 // in the first block the control block.
-__global__ __launch_bounds__(256) void k_relax_begin(RelaxCtl *c, RelaxConfig cfg, CellSetup cells)
+__global__ __launch_bounds__(256) void k_relax_begin(RelaxCtl *c, RelaxConfig cfg, CellSetup cells, int lane_bits)
 {
-    setup_grid(cells);
-    if (blockIdx.x != 0) return;
+    setup_grid(cells, lane_bits);
+    if (blockIdx.x != 0 || blockIdx.y != 0) return;
     for (int i = threadIdx.x; i < kParts; i += blockDim.x) {
         __hip_atomic_store(&c->part[i][0], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&c->part[i][1], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1125,8 +1125,8 @@ int launch_relax_resident(const SlotArgs &a, hipStream_t st)
 
 int launch_relax_begin(void *ctl, const RelaxConfig &cfg, const CellSetup &cells, hipStream_t st)
 {
-    hipLaunchKernelGGL(k_relax_begin, dim3(setup_blocks(cells.nx, cells.ny)), dim3(256), 0, st,
-                       static_cast<RelaxCtl *>(ctl), cfg, cells);
+    hipLaunchKernelGGL(k_relax_begin, setup_blocks(cells.nx, cells.ny), dim3(256), 0, st, static_cast<RelaxCtl *>(ctl),
+                       cfg, cells, setup_lane_bits(cells.nx));
     return last_status();
 }
 
